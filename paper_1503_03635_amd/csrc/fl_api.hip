@@ -612,7 +612,7 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
   FL_LAUNCH_CHECK();
   SsspWork wk;
   sssp_alloc(c, wk, n, g.m);
-  sssp_run(c, g, gl, fac_list, nF, wk, 0);
+  sssp_run(c, g, gl, fac_list, nF, wk);
   fill_u64(c, ctr, (size_t)G * CL_NFIELD * stripes, 0);
   k_clients<<<vb, 256, 0, s>>>(n, gid, is_client, gl, fac_cost, ceff, ctr, stripes);
   FL_LAUNCH_CHECK();
@@ -691,7 +691,7 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
     FL_HIP(hipMemcpyAsync(c.h_status, pos + n, 8, hipMemcpyDeviceToHost, s));
     c.sync();
     const uint32_t nS = (uint32_t)c.h_status[0];
-    sssp_run(c, g, al, slist, nS, wk, 0);
+    sssp_run(c, g, al, slist, nS, wk);
     if (!directed || pass == 1) break;
     fill_u32(c, rgc, 1, 0);
     k_reach_guard<<<vb, 256, 0, s>>>(n, ceff, al, gl, open_u, rgc);

@@ -456,15 +456,20 @@ void ads_totals(Ctx &c, const Graph &g, const uint32_t *gid, uint32_t G, const u
 // Labels move along arcs by adding w << 32.  `labels` holds the initial
 // labels (INF64 = none) and receives the fixed point; `seeds` lists the
 // vertices whose label was lowered since the last call (the first frontier).
+struct SsspState {
+  uint32_t nf;      // vertices of the current frontier (0: the search has ended)
+  uint32_t cur;     // its list
+  uint32_t iter;    // iterations done on this workspace (stamps grow across searches)
+  uint32_t nnext;   // wide iterations: vertices appended to the other list
+  uint32_t nheavy;  // wide iterations: queued pieces of long rows
+};
 struct SsspWork {
   uint32_t *front[2];
-  uint32_t *flag;  // n: iteration stamp of the last frontier a vertex joined
-  uint64_t *heavy; // pieces of the long rows of the current iteration
-  uint64_t *ctr;   // device counters: u32 [0], [1] frontier sizes, [2] long rows
-  uint32_t stamp = 0;  // stamps grow across calls on this workspace
+  uint32_t *flag;   // n: iteration stamp of the last frontier a vertex joined
+  uint64_t *heavy;  // pieces of the long rows of the current iteration
+  SsspState *st;    // device
 };
 void sssp_alloc(Ctx &c, SsspWork &wk, uint32_t n, uint64_t m);
-uint32_t sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, uint32_t nseeds,
-                  SsspWork &wk, uint64_t cap_value);
+void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, uint32_t nseeds, SsspWork &wk);
 
 }  // namespace fl

@@ -736,7 +736,7 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     if (opened) {
       k_seed_opened<<<(uint32_t)ceil_div(opened, 256), 256, 0, c.s>>>(A.opened, A.opened_cnt, dlab);
       FL_LAUNCH_CHECK();
-      sssp_run(c, g, dlab, A.opened, (uint32_t)opened, wk, 0);
+      sssp_run(c, g, dlab, A.opened, (uint32_t)opened, wk);
     }
     if (any_freeze) {
       upload();
