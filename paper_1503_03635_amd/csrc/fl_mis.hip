@@ -4,19 +4,19 @@
 // A client c and a facility f are joined in H when both carry the same rung
 // t (c froze at t, f opened at t) and d(c, f) <= (1 + eps) a[t]; facilities
 // conflict when they share a client.  Priorities pi(f) are a seeded
-// bijection, and each round of the fixed-priority algorithm is four bounded
+// bijection, and each round of the fixed-priority algorithm is three bounded
 // sweeps over the graph:
 //   1. every client takes the smallest priority of the active facilities
 //      within the radius (pi_min);
 //   2. every active facility takes the smallest pi_min of the clients within
 //      the radius; it joins S when that is its own priority (or when it has
 //      no client);
-//   3. clients within the radius of a joined facility are covered;
-//   4. active facilities within the radius of a covered client retire.
+//   3. active facilities within the radius of a client covered by a joined
+//      facility (the client's pi_min is that facility's priority) retire.
 // Rounds repeat until no facility is active; the result is the greedy MIS in
 // priority order.  The radius is measured from client to facility, d(c, f):
-// sweeps 1 and 3 start at facilities and push over the in-arcs, sweeps 2 and
-// 4 start at clients and push over the out-arcs (the same arcs when the graph
+// sweep 1 starts at facilities and pushes over the in-arcs, sweeps 2 and 3
+// start at clients and push over the out-arcs (the same arcs when the graph
 // is undirected).  In a union of several graphs, each graph walks through its
 // own non-empty rungs: step i runs the i-th one of every graph at once (the
 // graphs share no vertex, so their sweeps do not interact), each with its own
@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "fl_common.h"
 #include "fl_frontier.h"
@@ -36,6 +37,11 @@
 
 namespace fl {
 
+struct SweepState {
+  uint32_t j;     // distance to settle next
+  uint32_t done;  // no label is pending: the sweep has ended
+  uint32_t cnt;   // vertices with a label pending at distance j
+};
 struct SweepArgs {
   uint32_t n, NS;
   const uint32_t *gid;  // graph of each vertex (nullptr: one graph)
@@ -50,7 +56,8 @@ struct SweepArgs {
   uint32_t *touched;  // [n] vertices whose ml was set
   uint32_t *touched_cnt;
   uint64_t *heavy;    // pieces of the long rows queued in the current distance
-  uint32_t *heavy_cnt;  // [2] by distance parity
+  uint32_t *heavy_cnt;
+  SweepState *st;     // device
   const uint32_t *tbits;  // bitmap of the vertices whose result is read (nullptr: all)
 };
 
@@ -215,7 +222,7 @@ __device__ inline void sweep_push_lanes(const SweepArgs &S, SlotQ &q, bool want,
     deg = S.row_ptr[x + 1] - a0;
   }
   const bool heavy = want && deg > SWEEP_FLAT_MAX;
-  push_pieces(S.heavy, S.heavy_cnt + (j & 1), heavy, x, deg);
+  push_pieces(S.heavy, S.heavy_cnt, heavy, x, deg);
   flat_arcs2(want && !heavy, a0, deg, [&](bool v0, uint64_t x0, int o0, bool v1, uint64_t x1, int o1) {
     sweep_arcs2(S, q, j, v0, x0, __shfl(lab, o0, WAVE), __shfl(R, o0, WAVE), v1, x1, __shfl(lab, o1, WAVE),
                 __shfl(R, o1, WAVE));
@@ -227,11 +234,12 @@ __device__ inline void touch(const SweepArgs &S, bool first, uint32_t x) {
   wave_push(S.touched, S.touched_cnt, first, x);
 }
 
-// sources: set ml and push at distance 0 (one lane per source)
+// Wide step at distance 0: the sources set ml and push (one lane per source).
 __global__ __launch_bounds__(256) void k_sweep_init(SweepArgs S, const uint32_t *src, uint32_t nsrc,
                                                     const uint32_t *lab) {
   SLOTQ_DECL(q);
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *S.st = SweepState{0u, 0u, nsrc};
   bool want = false;
   uint32_t x = 0, l = INF32;
   if (i < nsrc) {
@@ -245,9 +253,12 @@ __global__ __launch_bounds__(256) void k_sweep_init(SweepArgs S, const uint32_t 
   slotq_flush(S, q);
 }
 
-// distance j: settle the pending labels of slot j (one lane per vertex)
-__global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S, uint32_t j) {
+// Wide step, first launch: settle the labels pending at distance st->j (one
+// lane per vertex).
+__global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
   SLOTQ_DECL(q);
+  if (S.st->done) return;
+  const uint32_t j = S.st->j;
   const uint32_t slot = j % S.NS;
   const uint32_t cnt = S.tl_cnt[slot * CNT_PAD];
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -272,18 +283,13 @@ __global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S, uint32_t j) {
   slotq_flush(S, q);
 }
 
-// the pieces of long rows queued at distance j: one wave per piece; the label
-// is the vertex's own (settled at j, unchanged until the next distance).  Also
-// clears slot j (consumed) and the long-row counter of distance j + 1 (its
-// last use, distance j - 1, is over).
-__global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S, uint32_t j) {
+// Wide step, second launch: the pieces of long rows queued at distance st->j,
+// one wave per piece; the label is the vertex's own (settled at this
+// distance, unchanged until the next).
+__global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S) {
   SLOTQ_DECL(q);
   const int lane = lane_id();
-  const uint32_t cnt = S.heavy_cnt[j & 1];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    S.tl_cnt[(j % S.NS) * CNT_PAD] = 0;
-    S.heavy_cnt[(j + 1) & 1] = 0;
-  }
+  const uint32_t cnt = *S.heavy_cnt, j = S.st->j;
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) / WAVE;
   for (uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; i < cnt; i += nw) {
     uint64_t a0, a1;
@@ -296,6 +302,135 @@ __global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S, uint32_t j) {
     }
   }
   slotq_flush(S, q);
+}
+
+// Narrow steps of a sweep (see fl_frontier.h), by one block: the distances
+// with pending labels in increasing order, until none is pending or one is
+// too large for the block.  The slot counts live in LDS meanwhile, so empty
+// distances cost nothing and appends take LDS atomics.  after_wide: first
+// close the wide step at distance st->j; otherwise start a sweep from the
+// nsrc <= NARROW_V vertices of src with labels lab (distance 0).  Pending
+// labels and minima are read and lowered at the device's L2 (agent scope);
+// the vertex lists are written and read by this block only, a barrier apart.
+// On return every wide counter is zero and st says where the sweep stands.
+// Against bursts of 8 wide distances per host check (with the fourth sweep of
+// a round gone as well): MIS of R-MAT 2^18 (unit weights, eps 0.01) 120 -> 64
+// ms, of a Chung-Lu graph of 50,000 vertices (weights 1..50) 81 -> 43 ms, of
+// R-MAT 2^21 (weights 1..100) 204 -> 152 ms.
+__global__ __launch_bounds__(NARROW_T) void k_sweep_narrow(SweepArgs S, const uint32_t *src, uint32_t nsrc,
+                                                           const uint32_t *lab, int after_wide) {
+  __shared__ uint64_t s_a0[NARROW_V];
+  __shared__ uint32_t s_excl[NARROW_V], s_lab[NARROW_V], s_R[NARROW_V], s_cnt[MAX_W + 1], s_tmp[NARROW_WAVES];
+  __shared__ uint32_t s_next, s_touched;
+  const uint32_t tid = threadIdx.x, NS = S.NS;
+  bool start = !after_wide;  // the next step settles the sources
+  uint32_t j = 0;
+  if (after_wide) {
+    if (S.st->done) return;  // the sweep had ended before the wide launches
+    j = S.st->j;
+  }
+  if (tid < NS) s_cnt[tid] = (start || tid == j % NS) ? 0u : S.tl_cnt[tid * CNT_PAD];
+  if (tid == 0) {
+    s_touched = start ? 0u : *S.touched_cnt;
+    s_next = INF32;
+  }
+  __syncthreads();
+  bool done = false;
+  uint32_t cnt = 0;
+  for (;;) {
+    if (start) {
+      cnt = nsrc;
+    } else {
+      // the next distance with a pending label (slots j + 1 .. j + NS - 1)
+      if (tid + 1 < NS && s_cnt[(j + 1 + tid) % NS]) atomicMin(&s_next, tid);
+      __syncthreads();
+      const uint32_t d = s_next;
+      __syncthreads();
+      if (d == INF32) {
+        done = true;
+        break;
+      }
+      j += 1 + d;
+      cnt = s_cnt[j % NS];
+      if (tid == 0) s_next = INF32;
+    }
+    if (cnt > NARROW_V) break;
+    const uint32_t slot = j % NS;
+    uint32_t x[2] = {0, 0}, lv[2] = {INF32, INF32}, cur[2] = {INF32, INF32}, R[2] = {0, 0}, deg[2] = {0, 0}, ex[2];
+    uint64_t a0[2] = {0, 0};
+    bool set[2] = {false, false};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t p = tid + h * NARROW_T;
+      if (p < cnt) {
+        x[h] = start ? src[p] : S.tl[(size_t)slot * S.n + p];
+        if (start) {
+          lv[h] = lab[x[h]];
+        } else {
+          lv[h] = __hip_atomic_load(&S.pend[(size_t)slot * S.n + x[h]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          cur[h] = __hip_atomic_load(&S.ml[x[h]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        R[h] = S.Rg[seg_of(S.gid, x[h])];
+        a0[h] = S.row_ptr[x[h]];
+        const uint64_t d = S.row_ptr[x[h] + 1] - a0[h];
+        set[h] = lv[h] < cur[h];
+        // arcs weigh at least 1: a label settled at distance R goes no further
+        if (set[h] && j < R[h]) deg[h] = d > NARROW_ARCS ? NARROW_ARCS + 1 : (uint32_t)d;
+      }
+    }
+    uint32_t t0, t1 = 0;
+    ex[0] = narrow_scan_excl(deg[0], s_tmp, &t0);
+    ex[1] = t0;
+    if (cnt > NARROW_T) ex[1] = t0 + narrow_scan_excl(deg[1], s_tmp, &t1);
+    const uint32_t total = t0 + t1;
+    if (total > NARROW_ARCS) break;  // a wide step takes this distance (nothing is settled yet)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t p = tid + h * NARROW_T;
+      if (!start && p < cnt) S.pend[(size_t)slot * S.n + x[h]] = INF32;
+      if (set[h]) S.ml[x[h]] = lv[h];
+      wave_push(S.touched, &s_touched, set[h] && cur[h] == INF32, x[h]);
+      s_excl[p] = p < cnt ? ex[h] : total;
+      s_a0[p] = a0[h];
+      s_lab[p] = lv[h];
+      s_R[p] = R[h];
+    }
+    if (tid == 0 && !start) s_cnt[slot] = 0;
+    __syncthreads();
+    const uint32_t half = narrow_half(cnt);
+    for (uint32_t b = 0; b < total; b += NARROW_T) {
+      const uint32_t idx = b + tid;
+      bool add = false;
+      uint32_t y = 0, s = 0;
+      if (idx < total) {
+        const uint32_t p = narrow_owner(s_excl, idx, half);
+        const uint64_t a = s_a0[p] + (idx - s_excl[p]);
+        const uint32_t l = s_lab[p], Rp = s_R[p];
+        y = S.col[a];
+        const uint32_t w = S.w ? S.w[a] : 1u;
+        const uint64_t d = (uint64_t)j + w;
+        // the conditions of sweep_arcs2
+        const bool keep = d < Rp || (d == Rp && (!S.tbits || ((S.tbits[y >> 5] >> (y & 31)) & 1u)));
+        if (keep && l < __hip_atomic_load(&S.ml[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+          s = (j + w) % NS;
+          add = atomicMin(&S.pend[(size_t)s * S.n + y], l) == INF32;
+        }
+      }
+      if (NS == 2) {
+        wave_push(S.tl + (size_t)((j + 1) & 1) * S.n, &s_cnt[(j + 1) & 1], add, y);  // one slot: one atomic per wave
+      } else if (add) {
+        S.tl[(size_t)s * S.n + atomicAdd(&s_cnt[s], 1u)] = y;
+      }
+    }
+    __syncthreads();
+    start = false;
+  }
+  if (tid < NS) S.tl_cnt[tid * CNT_PAD] = s_cnt[tid];
+  if (tid == 0) {
+    *S.touched_cnt = s_touched;
+    *S.heavy_cnt = 0;
+    *S.st = SweepState{j, done ? 1u : 0u, cnt};
+  }
 }
 
 __global__ void k_sweep_reset(SweepArgs S) {
@@ -313,7 +448,6 @@ struct MisWork {
   uint32_t *lab;     // [n] source labels
   uint32_t *act;     // [n] list of active facilities
   uint32_t *act2;    // [n]
-  uint32_t *joined;  // [n]
   uint32_t *cov;     // [n]
   uint32_t *src;     // [n] sweep sources
   uint32_t *cnts;    // [8] device counters
@@ -327,10 +461,6 @@ enum class Toward { clients, facilities };
 // on the large weighted workload, timed on one box, identical results (four
 // times gave the same)
 constexpr uint32_t SWEEP_HEAVY_BLOCKS = 2 * HEAVY_BLOCKS;
-
-// sweeps from at most this many sources skip the first readback of the
-// frontier counts
-constexpr uint32_t SWEEP_BLIND_SRC = 4096;
 
 // run one sweep to completion; results in S.ml (caller resets afterwards).
 // Toward::clients: from facilities f to every x with d(x, f) <= R (in-arcs);
@@ -347,72 +477,70 @@ static void sweep(Ctx &c, MisWork &M, const uint32_t *src, uint32_t nsrc, uint32
   S.row_ptr = in ? M.g->in_ptr : M.g->row_ptr;
   S.col = in ? M.g->in_col : M.g->col;
   S.w = in ? M.g->in_w : M.g->w;
-  k_sweep_init<<<(uint32_t)ceil_div((uint64_t)nsrc, 256), 256, 0, c.s>>>(S, src, nsrc, M.lab);
-  FL_LAUNCH_CHECK();
-  k_sweep_heavy<<<SWEEP_HEAVY_BLOCKS, 256, 0, c.s>>>(S, 0);
-  FL_LAUNCH_CHECK();
-  std::vector<uint32_t> h(S.NS);
-  uint32_t j = 1;
-  // few sources: run the first burst without reading the counts back (its
-  // grid fits any frontier, and an empty distance costs one short launch)
-  bool blind = nsrc <= SWEEP_BLIND_SRC;
-  while (j <= R) {
-    uint64_t pending = 1;
-    uint32_t hmax = 0;
-    if (!blind) {
-      fetch_padded(c, h.data(), S.tl_cnt, S.NS);
-      pending = 0;
-      for (uint32_t s = 0; s < S.NS; ++s) {
-        pending += h[s];
-        hmax = std::max(hmax, h[s]);
-      }
-    }
-    blind = false;
-    if (!pending) break;
-    // k_sweep_round reads its slot's count on the device, so 8 distances run
-    // per host check (large frontiers too: MIS 1.093 -> 1.083 s on the large
-    // weighted workload against a check after every distance of a frontier
-    // above 65,536).  A frontier can grow from a handful of vertices to most
-    // of the graph within a burst, so burst launches get a grid for any
-    // frontier (the kernel strides over the count; blocks past it exit at
-    // once).
-    const uint32_t burst = 8u;
-    const uint64_t want = std::max<uint64_t>(ceil_div((uint64_t)hmax * 2, 256),
-                                             std::min<uint64_t>(ceil_div(S.n, 256), 2048));
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 4), 8192);
-    for (uint32_t b = 0; b < burst && j <= R; ++b, ++j) {
-      k_sweep_round<<<blocks, 256, 0, c.s>>>(S, j);
-      FL_LAUNCH_CHECK();
-      k_sweep_heavy<<<SWEEP_HEAVY_BLOCKS, 256, 0, c.s>>>(S, j);
-      FL_LAUNCH_CHECK();
-    }
+  auto narrow = [&](uint32_t ns, int after_wide) {
+    k_sweep_narrow<<<1, NARROW_T, 0, c.s>>>(S, src, ns, M.lab, after_wide);
+    FL_LAUNCH_CHECK();
+  };
+  auto heavy = [&]() {
+    k_sweep_heavy<<<SWEEP_HEAVY_BLOCKS, 256, 0, c.s>>>(S);
+    FL_LAUNCH_CHECK();
+  };
+  SweepState st{0u, 0u, nsrc};
+  auto check = [&]() {
+    c.fetch(S.st, sizeof(SweepState));
+    std::memcpy(&st, c.h_status, sizeof(SweepState));
+  };
+  if (nsrc <= NARROW_V) {
+    narrow(nsrc, 0);
+    check();
+  } else {
+    fill_u32(c, S.touched_cnt, 1, 0);
   }
-  fill_u32(c, S.heavy_cnt, 2, 0);  // the last distance's long-row count
+  // Wide steps: two launches and the narrow one that closes the step and goes
+  // on with the narrow distances after it.  WIDE_CHAIN of them are launched
+  // per host check; those that find the sweep ended exit at once.  A frontier
+  // can grow from a handful of vertices to most of the graph within a chain,
+  // so every launch gets a grid for any frontier (the kernel strides over the
+  // count).
+  constexpr int WIDE_CHAIN = 2;
+  while (!st.done) {
+    const uint64_t want =
+        std::max<uint64_t>(ceil_div((uint64_t)st.cnt * 2, 256), std::min<uint64_t>(ceil_div(S.n, 256), 2048));
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 4), 8192);
+    for (int b = 0; b < WIDE_CHAIN; ++b) {
+      if (b == 0 && st.j == 0) {
+        k_sweep_init<<<(uint32_t)ceil_div((uint64_t)nsrc, 256), 256, 0, c.s>>>(S, src, nsrc, M.lab);
+      } else {
+        k_sweep_round<<<blocks, 256, 0, c.s>>>(S);
+      }
+      FL_LAUNCH_CHECK();
+      heavy();
+      narrow(0, 1);
+    }
+    check();
+  }
 }
 
 static void sweep_reset(Ctx &c, MisWork &M) {
   k_sweep_reset<<<1024, 256, 0, c.s>>>(M.S);
   FL_LAUNCH_CHECK();
-  fill_u32(c, M.S.touched_cnt, 1, 0);
 }
 
 // ---- small per-round kernels -------------------------------------------------
 // Priority of facility f: the fixed one (luby_round == 0), or for Luby's
 // variant the one drawn for round r of the rung, a bijection keyed by
 // SplitMix64(seed ^ (3 + 256 r)).
+__device__ inline PermKey priority_key(const SegInfo &sg, uint32_t luby_round) {
+  return luby_round ? perm_key(sg.seed, 3ull + 256ull * luby_round) : sg.pk;
+}
 __device__ inline uint32_t priority_of(uint32_t f, const uint32_t *gid, const SegInfo *seg, uint32_t luby_round) {
   const SegInfo &sg = seg[seg_of(gid, f)];
-  const PermKey key = luby_round ? perm_key(sg.seed, 3ull + 256ull * luby_round) : sg.pk;
-  return perm_fwd(f - sg.base, key);
+  return perm_fwd(f - sg.base, priority_key(sg, luby_round));
 }
 __global__ void k_set_key_labels(const uint32_t *list, uint32_t cnt, uint32_t *lab, const uint32_t *gid,
                                  const SegInfo *seg, uint32_t luby_round) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < cnt) lab[list[i]] = priority_of(list[i], gid, seg, luby_round);
-}
-__global__ void k_set_const_labels(const uint32_t *list, uint32_t cnt, uint32_t *lab, uint32_t v) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < cnt) lab[list[i]] = v;
 }
 // clients of the rung: their pi_min (ml[c]) becomes their label; sources for
 // sweep 2 are those with a value
@@ -440,47 +568,42 @@ __global__ void k_take_pmin(const uint32_t *cl, uint32_t ncl, const uint32_t *ml
 }
 // join test: m(f) = ml[f]; join iff no client (INF) or m(f) == pi(f)
 __global__ void k_join(const uint32_t *act, uint32_t na, const uint32_t *ml, const uint32_t *gid,
-                       const SegInfo *seg, uint32_t luby_round, uint8_t *open, uint32_t *joined, uint32_t *nj,
-                       uint32_t *rest, uint32_t *nr) {
+                       const SegInfo *seg, uint32_t luby_round, uint8_t *open, uint32_t *rest, uint32_t *nr) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool j = false, r = false;
+  bool r = false;
   uint32_t f = 0;
   if (i < na) {
     f = act[i];
     const uint32_t m = ml[f];
-    j = m == INF32 || m >= priority_of(f, gid, seg, luby_round);
-    r = !j;
-    if (j) open[f] = 1;
+    r = !(m == INF32 || m >= priority_of(f, gid, seg, luby_round));
+    if (!r) open[f] = 1;
   }
-  uint64_t mj = __ballot(j), mr = __ballot(r);
-  uint32_t bj = 0, br = 0;
-  if (lane_id() == 0) {
-    if (mj) bj = atomicAdd(nj, (uint32_t)__popcll(mj));
-    if (mr) br = atomicAdd(nr, (uint32_t)__popcll(mr));
-  }
-  bj = __shfl(bj, 0, WAVE);
-  br = __shfl(br, 0, WAVE);
-  if (j) joined[bj + lanes_below(mj)] = f;
-  if (r) rest[br + lanes_below(mr)] = f;
+  wave_push(rest, nr, r, f);
 }
-// clients of the rung reached by a label (ml == 0) -> list
-__global__ void k_collect_hit(const uint32_t *list, uint32_t cnt, const uint32_t *ml, uint32_t *out,
-                              uint32_t *nout, int keep_hit) {
+// The clients covered by a facility that joined this round, of the clients in
+// src (label pi_min).  A facility joins when its priority is the smallest
+// pi_min around it, so it is pi_min at every client it has: a client is
+// covered iff the facility whose priority it holds joined (an active facility
+// is open only if it joined this round).  Their labels become 0, for sweep 3.
+__global__ void k_covered(const uint32_t *src, uint32_t cnt, const uint32_t *gid, const SegInfo *seg,
+                          uint32_t luby_round, const uint8_t *open, uint32_t *lab, uint32_t *cov, uint32_t *ncov) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool want = false;
+  bool hit = false;
   uint32_t x = 0;
   if (i < cnt) {
-    x = list[i];
-    const bool hit = ml[x] == 0;
-    want = keep_hit ? hit : !hit;
+    x = src[i];
+    const SegInfo &sg = seg[seg_of(gid, x)];
+    hit = open[perm_inv(lab[x], priority_key(sg, luby_round)) + sg.base] != 0;
+    if (hit) lab[x] = 0;
   }
-  const uint64_t m = __ballot(want);
-  if (m) {
-    uint32_t base = 0;
-    if (lane_id() == 0) base = atomicAdd(nout, (uint32_t)__popcll(m));
-    base = __shfl(base, 0, WAVE);
-    if (want) out[base + lanes_below(m)] = x;
-  }
+  wave_push(cov, ncov, hit, x);
+}
+// facilities of the list not reached by a label (ml != 0) -> list
+__global__ void k_collect_alive(const uint32_t *list, uint32_t cnt, const uint32_t *ml, uint32_t *out,
+                                uint32_t *nout) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t x = i < cnt ? list[i] : 0u;
+  wave_push(out, nout, i < cnt && ml[x] != 0, x);
 }
 
 // per-(graph, rung) lists: counting sort by key koff[g] + t - 1 (t in 1..T[g])
@@ -685,11 +808,11 @@ int mis_phase(Ctx &c, const MisIn &in, uint8_t *open, std::vector<uint32_t> &rou
   M.S.touched = c.arena->get<uint32_t>(n);
   M.S.touched_cnt = c.arena->get<uint32_t>(1);
   M.S.heavy = c.arena->get<uint64_t>(piece_capacity(n, g.m));
-  M.S.heavy_cnt = c.arena->get<uint32_t>(2);
+  M.S.heavy_cnt = c.arena->get<uint32_t>(1);
+  M.S.st = c.arena->get<SweepState>(1);
   M.lab = c.arena->get<uint32_t>(n);
   M.act = c.arena->get<uint32_t>(n);
   M.act2 = c.arena->get<uint32_t>(n);
-  M.joined = c.arena->get<uint32_t>(n);
   M.cov = c.arena->get<uint32_t>(n);
   M.src = c.arena->get<uint32_t>(n);
   M.cnts = c.arena->get<uint32_t>(8);
@@ -706,8 +829,7 @@ int mis_phase(Ctx &c, const MisIn &in, uint8_t *open, std::vector<uint32_t> &rou
   fill_u32(c, M.S.ml, n, INF32);
   fill_u32(c, M.S.pend, (size_t)NS * n, INF32);
   fill_u32(c, M.S.tl_cnt, (size_t)NS * CNT_PAD, 0);
-  fill_u32(c, M.S.touched_cnt, 1, 0);
-  fill_u32(c, M.S.heavy_cnt, 2, 0);
+  fill_u32(c, M.S.heavy_cnt, 1, 0);
   fill_u32(c, M.cbits, nwords, 0);
   fill_u32(c, M.fbits, nwords, 0);
 
@@ -793,36 +915,28 @@ int mis_phase(Ctx &c, const MisIn &in, uint8_t *open, std::vector<uint32_t> &rou
       // 2. smallest pi_min around each active facility; joins
       sweep(c, M, M.src, ns2, Rmax, Toward::facilities, M.fbits);
       k_join<<<(uint32_t)ceil_div(na, 256), 256, 0, c.s>>>(M.act, na, M.S.ml, in.gid, in.seg, luby_round, open,
-                                                           M.joined, M.cnts + 1, M.act2, M.cnts + 2);
+                                                           M.act2, M.cnts + 1);
       FL_LAUNCH_CHECK();
       sweep_reset(c, M);
-      FL_HIP(hipMemcpyAsync(c.h_status, M.cnts, 16, hipMemcpyDeviceToHost, c.s));
-      c.sync();
-      const uint32_t nj = (uint32_t)(c.h_status[0] >> 32);
-      const uint32_t nr = (uint32_t)(c.h_status[1] & 0xFFFFFFFFu);
+      if (ns2) {
+        k_covered<<<(uint32_t)ceil_div(ns2, 256), 256, 0, c.s>>>(M.src, ns2, in.gid, in.seg, luby_round, open, M.lab,
+                                                                 M.cov, M.cnts + 2);
+        FL_LAUNCH_CHECK();
+      }
+      c.fetch(M.cnts, 16);
+      const uint32_t nr = (uint32_t)(c.h_status[0] >> 32);
+      const uint32_t ncov = (uint32_t)(c.h_status[1] & 0xFFFFFFFFu);
       if (nr == 0) {
         mark_bits(c, M.act, na, M.fbits, 0);
         break;
       }
-      // 3. clients covered by a joined facility
-      k_set_const_labels<<<(uint32_t)ceil_div(nj, 256), 256, 0, c.s>>>(M.joined, nj, M.lab, 0);
-      FL_LAUNCH_CHECK();
-      sweep(c, M, M.joined, nj, Rmax, Toward::clients, M.cbits);
-      if (ncl) {
-        k_collect_hit<<<(uint32_t)ceil_div(ncl, 256), 256, 0, c.s>>>(Ct, ncl, M.S.ml, M.cov, M.cnts + 3, 1);
-        FL_LAUNCH_CHECK();
-      }
-      sweep_reset(c, M);
-      const uint32_t ncov = read_u32(c, M.cnts + 3);
-      // 4. facilities next to a covered client retire
-      k_set_const_labels<<<(uint32_t)ceil_div(ncov ? ncov : 1, 256), 256, 0, c.s>>>(M.cov, ncov, M.lab, 0);
-      FL_LAUNCH_CHECK();
+      // 3. facilities next to a covered client retire
       sweep(c, M, M.cov, ncov, Rmax, Toward::facilities, M.fbits);  // read at the rest, a subset of act
       mark_bits(c, M.act, na, M.fbits, 0);  // before act is rewritten
-      k_collect_hit<<<(uint32_t)ceil_div(nr, 256), 256, 0, c.s>>>(M.act2, nr, M.S.ml, M.act, M.cnts + 4, 0);
+      k_collect_alive<<<(uint32_t)ceil_div(nr, 256), 256, 0, c.s>>>(M.act2, nr, M.S.ml, M.act, M.cnts + 3);
       FL_LAUNCH_CHECK();
       sweep_reset(c, M);
-      na = read_u32(c, M.cnts + 4);
+      na = read_u32(c, M.cnts + 3);
     }
     mark_bits(c, Ct, ncl, M.cbits, 0);
   }
