@@ -17,6 +17,8 @@
 // between the launches, whatever its size.
 #pragma once
 
+#include <algorithm>
+
 #include "fl_common.h"
 
 namespace fl {
@@ -54,6 +56,31 @@ __device__ inline uint32_t piece_arcs(uint64_t e, const uint64_t *row_ptr, uint6
   *b0 = a0 + p * HCHUNK;
   *b1 = *b0 + HCHUNK < a1 ? *b0 + HCHUNK : a1;
   return x;
+}
+
+// Frontier vertices per wave of a wide step: a full wave of 64, or fewer (a
+// power of two, at least 4) while that keeps the launch at SHARE_WAVES busy
+// waves or fewer, so that a frontier of some thousand vertices is spread over
+// the chip.  A wave walks its rows' arcs 64 or 128 at a time, one dependent
+// chain after another: with 64 vertices of average degree 12 that is six
+// chains, with 4 it is one.  More waves than that cost more in appends (each
+// wave reserves room per distinct slot) than they hide: with 8,192 the MIS
+// of R-MAT 2^21 (weights 1..100) took 164 ms, with 2,048 144 ms; with one
+// vertex per lane throughout 152 ms.
+constexpr uint32_t SHARE_WAVES = 2048;
+__device__ inline uint32_t wave_share(uint32_t cnt) {
+  const uint64_t all = (uint64_t)gridDim.x * (blockDim.x / WAVE);
+  const uint64_t nw = all < SHARE_WAVES ? all : SHARE_WAVES;
+  uint32_t vw = WAVE;
+  while (vw > 4 && nw * (vw / 2) >= cnt) vw /= 2;
+  return vw;
+}
+// Blocks of a wide step over n vertices: 2,048 (32 waves per CU on 256 CUs)
+// for any frontier that may arise, fewer where n cannot fill them, more for a
+// frontier known to be larger (`want` vertices).
+inline uint32_t wide_blocks(uint32_t n, uint64_t want) {
+  const uint64_t any = std::min<uint64_t>(ceil_div(n, 16), 2048);
+  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(any, ceil_div(want, 256)), 8192);
 }
 
 // ---------------------------------------------------------------------------

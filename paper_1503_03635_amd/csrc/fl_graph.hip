@@ -532,10 +532,11 @@ __global__ __launch_bounds__(256) void k_sssp_push(SsspArgs S) {
   const uint32_t nf = S.st->nf, cur = S.st->cur, iter = S.st->iter + 1;
   WaveQ q{s_q[threadIdx.x / WAVE], 0u, S.front[cur ^ 1], &S.st->nnext};
   const uint32_t *front = S.front[cur];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x; b < nf; b += stride) {
-    const uint64_t i = b + threadIdx.x;
-    const bool want = i < nf;
+  const uint32_t vw = wave_share(nf), lane = (uint32_t)lane_id();
+  const uint64_t stride = (uint64_t)gridDim.x * (blockDim.x / WAVE) * vw;
+  for (uint64_t b = ((uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE) * vw; b < nf; b += stride) {
+    const uint64_t i = b + lane;
+    const bool want = lane < vw && i < nf;
     uint32_t v = 0;
     uint64_t a0 = 0, deg = 0, L = 0;
     if (want) {
@@ -702,10 +703,9 @@ void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, u
     // a frontier can grow by orders of magnitude within a chain: every launch
     // gets a grid for any frontier (blocks past the count exit)
     constexpr int WIDE_CHAIN = 2;
-    uint64_t blocks = std::max<uint64_t>(ceil_div((uint64_t)nf, 256), std::min<uint64_t>(ceil_div(g.n, 256), 2048));
-    if (blocks > 16384) blocks = 16384;
+    const uint32_t blocks = wide_blocks(g.n, nf);
     for (int b = 0; b < WIDE_CHAIN; ++b) {
-      k_sssp_push<<<(uint32_t)blocks, 256, 0, c.s>>>(S);
+      k_sssp_push<<<blocks, 256, 0, c.s>>>(S);
       FL_LAUNCH_CHECK();
       k_sssp_heavy<<<HEAVY_BLOCKS, 256, 0, c.s>>>(S);
       FL_LAUNCH_CHECK();

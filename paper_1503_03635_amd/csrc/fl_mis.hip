@@ -67,28 +67,38 @@ struct SweepArgs {
 // on the slot's one count.
 struct SlotQ {
   uint32_t *ys, *ss;  // this wave's LDS staging: vertices and their slots
+  uint32_t *cs;       // this wave's count per slot (MAX_W + 1 words, zero between calls)
   uint32_t cnt;       // staged entries (wave-uniform, < WAVE between calls)
 };
 
-// append y to the list of slot s on the lanes with have set: one atomic per
-// distinct slot among them
-__device__ inline void slotq_write(const SweepArgs &S, bool have, uint32_t y, uint32_t s) {
-  const int lane = lane_id();
-  uint64_t pendm = __ballot(have);
-  while (pendm) {
-    const int lead = __ffsll((long long)pendm) - 1;
-    const uint32_t sl = __shfl(s, lead, WAVE);
-    const bool mine = have && s == sl;
-    const uint64_t grp = __ballot(mine);
-    uint32_t base = 0;
-    if (lane == lead) base = atomicAdd(&S.tl_cnt[sl * CNT_PAD], (uint32_t)__popcll(grp));
-    base = __shfl(base, lead, WAVE);
-    if (mine) {
-      S.tl[(size_t)sl * S.n + base + lanes_below(grp)] = y;
-      have = false;
-    }
-    pendm &= ~grp;
+// Append y to the list of slot s on the lanes with have set: the lanes of a
+// slot are counted in LDS, and one lane per distinct slot reserves room for
+// all of them.  The reservations are one instruction, so a write waits for one
+// atomic's return; a loop over the distinct slots (about 47 among 64 entries
+// at weights 1..100) waited for one after another, and that wait was most of
+// a wide step: with it and wave_share gone from 35 to 16 us a launch on a
+// Chung-Lu graph of 50,000 vertices, half of the launches empty (MIS 43 -> 33 ms).
+// With unit weights every entry of a step goes to the same slot.
+__device__ inline void slotq_write(const SweepArgs &S, const SlotQ &q, bool have, uint32_t y, uint32_t s) {
+  if (S.NS == 2) {
+    const uint64_t m = __ballot(have);
+    const int lead = __ffsll((long long)m) - 1;  // m != 0
+    const uint32_t s0 = __shfl(s, lead, WAVE);
+    wave_push(S.tl + (size_t)s0 * S.n, &S.tl_cnt[s0 * CNT_PAD], have, y);
+    return;
   }
+  uint32_t r = 0, v = 0;
+  if (have) r = atomicAdd(&q.cs[s], 1u);
+  wave_lds_sync();
+  if (have) v = q.cs[s];
+  wave_lds_sync();
+  if (have && r == 0) q.cs[s] = atomicAdd(&S.tl_cnt[s * CNT_PAD], v);
+  wave_lds_sync();
+  if (have) v = q.cs[s];
+  wave_lds_sync();
+  if (have && r == 0) q.cs[s] = 0;
+  wave_lds_sync();
+  if (have) S.tl[(size_t)s * S.n + v + r] = y;
 }
 
 // every lane calls, converged
@@ -103,7 +113,7 @@ __device__ inline void slotq_push(const SweepArgs &S, SlotQ &q, bool add, uint32
   q.cnt += (uint32_t)__popcll(m);
   if (q.cnt < (uint32_t)WAVE) return;
   wave_lds_sync();
-  slotq_write(S, true, q.ys[lane], q.ss[lane]);
+  slotq_write(S, q, true, q.ys[lane], q.ss[lane]);
   q.cnt -= WAVE;
   const bool more = (uint32_t)lane < q.cnt;
   const uint32_t ry = more ? q.ys[WAVE + lane] : 0u, rs = more ? q.ss[WAVE + lane] : 0u;
@@ -121,15 +131,18 @@ __device__ inline void slotq_flush(const SweepArgs &S, SlotQ &q) {
   const int lane = lane_id();
   wave_lds_sync();
   const bool have = (uint32_t)lane < q.cnt;
-  slotq_write(S, have, have ? q.ys[lane] : 0u, have ? q.ss[lane] : 0u);
+  slotq_write(S, q, have, have ? q.ys[lane] : 0u, have ? q.ss[lane] : 0u);
   q.cnt = 0;
 }
 
 // LDS staging for the 256 / WAVE waves of a block
-#define SLOTQ_DECL(q)                                   \
-  __shared__ uint32_t q##_ys[256 / WAVE][2 * WAVE];     \
-  __shared__ uint32_t q##_ss[256 / WAVE][2 * WAVE];     \
-  SlotQ q{q##_ys[threadIdx.x / WAVE], q##_ss[threadIdx.x / WAVE], 0u}
+#define SLOTQ_DECL(q)                                                                                   \
+  __shared__ uint32_t q##_ys[256 / WAVE][2 * WAVE];                                                     \
+  __shared__ uint32_t q##_ss[256 / WAVE][2 * WAVE];                                                     \
+  __shared__ uint32_t q##_cs[256 / WAVE][MAX_W + 1];                                                    \
+  SlotQ q{q##_ys[threadIdx.x / WAVE], q##_ss[threadIdx.x / WAVE], q##_cs[threadIdx.x / WAVE], 0u};      \
+  for (uint32_t i_ = (uint32_t)lane_id(); i_ < S.NS; i_ += WAVE) q.cs[i_] = 0;                          \
+  wave_lds_sync()
 
 // Two arc steps of a push (every lane calls, converged; a lane with v0 or v1
 // false has no arc in that group): per arc, lower the pending label of the
@@ -256,17 +269,18 @@ __global__ __launch_bounds__(256) void k_sweep_init(SweepArgs S, const uint32_t 
 // Wide step, first launch: settle the labels pending at distance st->j (one
 // lane per vertex).
 __global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
-  SLOTQ_DECL(q);
   if (S.st->done) return;
+  SLOTQ_DECL(q);
   const uint32_t j = S.st->j;
   const uint32_t slot = j % S.NS;
   const uint32_t cnt = S.tl_cnt[slot * CNT_PAD];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x; b < cnt; b += stride) {
-    const uint64_t i = b + threadIdx.x;
+  const uint32_t vw = wave_share(cnt), lane = (uint32_t)lane_id();
+  const uint64_t stride = (uint64_t)gridDim.x * (blockDim.x / WAVE) * vw;
+  for (uint64_t b = ((uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE) * vw; b < cnt; b += stride) {
+    const uint64_t i = b + lane;
     bool want = false, first = false;
     uint32_t y = 0, v = INF32;
-    if (i < cnt) {
+    if (lane < vw && i < cnt) {
       y = S.tl[(size_t)slot * S.n + i];
       v = S.pend[(size_t)slot * S.n + y];
       const uint32_t cur = S.ml[y];
@@ -287,9 +301,10 @@ __global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
 // one wave per piece; the label is the vertex's own (settled at this
 // distance, unchanged until the next).
 __global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S) {
+  const uint32_t cnt = *S.heavy_cnt, j = S.st->j;
+  if (blockIdx.x * (blockDim.x / WAVE) >= cnt) return;
   SLOTQ_DECL(q);
   const int lane = lane_id();
-  const uint32_t cnt = *S.heavy_cnt, j = S.st->j;
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) / WAVE;
   for (uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; i < cnt; i += nw) {
     uint64_t a0, a1;
@@ -504,9 +519,7 @@ static void sweep(Ctx &c, MisWork &M, const uint32_t *src, uint32_t nsrc, uint32
   // count).
   constexpr int WIDE_CHAIN = 2;
   while (!st.done) {
-    const uint64_t want =
-        std::max<uint64_t>(ceil_div((uint64_t)st.cnt * 2, 256), std::min<uint64_t>(ceil_div(S.n, 256), 2048));
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 4), 8192);
+    const uint32_t blocks = wide_blocks(S.n, (uint64_t)st.cnt * 2);
     for (int b = 0; b < WIDE_CHAIN; ++b) {
       if (b == 0 && st.j == 0) {
         k_sweep_init<<<(uint32_t)ceil_div((uint64_t)nsrc, 256), 256, 0, c.s>>>(S, src, nsrc, M.lab);
