@@ -1021,13 +1021,18 @@ __device__ inline uint32_t half_count_below(uint32_t setv, uint32_t r) {
   return q;
 }
 
+// Levels of at most this many survivors in both halves are decided by
+// comparing all pairs instead of sorting (a level has 4 survivors on average
+// on the large weighted workload, and most have none).
+constexpr uint32_t PAIR_FEW = 12;
+static_assert(PAIR_FEW <= HALF, "one survivor per lane");
 // 6 waves per SIMD (80 registers, a few spilled) measured 2% faster than 5 on
 // the large weighted workload; 8 (64 registers) slower
 template <bool UNITW>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *task_sub, const uint32_t *task_slot,
                  const uint64_t *d_ntasks, uint8_t *pend) {
-  __shared__ uint32_t s_id[2][2 * HALF];            // survivors of the level (ids)
+  __shared__ __align__(16) uint32_t s_id[2][2 * HALF];  // survivors of the level (ranks, then ids)
   __shared__ uint32_t s_acc[2][2 * HALF];           // accepted ids, in id order
   __shared__ uint32_t s_set[2][HALF];               // the set at the level start
   __shared__ __align__(16) uint32_t s_r[2][HALF];   // chunk ranks
@@ -1049,10 +1054,17 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
       const uint32_t sD = D % P.NS;
       atomicAnd(&P.flags[(size_t)u * P.FW + (sD >> 5)], ~(1u << (sD & 31)));
     }
+    // the task's row, set and count are loaded together: one wait
     const RankMap rm = rank_map(P.seg[seg_of(P.gid, u)]);
     const uint32_t cu = act ? P.cnt[u] : 0u;
+    const uint32_t bkv = act && hl < k ? P.bk[(size_t)u * k + hl] : INF32;
+    uint64_t a0 = 0, a1 = 0;
+    if (act) {
+      a0 = P.row_ptr[u];
+      a1 = P.row_ptr[u + 1];
+    }
     const uint32_t nset0 = cu < k ? cu : k;
-    const uint32_t setv = (act && hl < nset0) ? P.bk[(size_t)u * k + hl] : INF32;
+    const uint32_t setv = hl < nset0 ? bkv : INF32;
     s_set[h][hl] = setv;
     wave_lds_sync();
     const bool full0 = nset0 == k;
@@ -1078,7 +1090,7 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
         defer = true;  // more survivors than one chunk: the one-wave kernel
         act = false;
       } else {
-        if (pass) s_id[h][ns + half_below(m)] = id_of(r, rm);
+        if (pass) s_id[h][ns + half_below(m)] = r;
         ns += np;
       }
       wave_lds_sync();
@@ -1150,14 +1162,9 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
         offer(ok, r);
       }
     };
-    uint64_t a0 = 0, a1 = 0;
-    if (act) {
-      a0 = P.row_ptr[u];
-      a1 = P.row_ptr[u + 1];
-      if (a1 - a0 > PAIR_ROW_MAX) {
-        defer = true;  // a long row: the one-wave kernel
-        act = false;
-      }
+    if (act && a1 - a0 > PAIR_ROW_MAX) {
+      defer = true;  // a long row: the one-wave kernel
+      act = false;
     }
     if (flagged) {
       // only the arcs flagged in this round's plane
@@ -1210,15 +1217,85 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
         batch(more && b + hl < a1, b + hl);
       }
     }
+    // The level's accepted ids (s_acc, in id order), their ranks ascending (ra,
+    // then rb) and number (m), and the set they leave (set1, nset1).  nmax, the
+    // larger half's survivors, picks the way; it is the same in every lane.
+    uint32_t m = 0, nset1 = nset0, set1 = setv, ra = INF32, rb = INF32, x0 = INF32, x1 = INF32;
+    uint32_t nmax = act ? ns : 0u;
+    {
+      const uint32_t o = __shfl_xor(nmax, (int)HALF, WAVE);
+      nmax = __builtin_amdgcn_readfirstlane(nmax > o ? nmax : o);
+    }
+    if (nmax && nmax <= PAIR_FEW) {
+      // Few survivors: every lane compares its own with the half's, four per
+      // LDS read, instead of sorting.  A repeated id keeps its lowest lane.
+      const uint32_t nc = act ? ns : 0u;
+      uint32_t r = hl < nc ? s_id[h][hl] : INF32;
+      wave_lds_sync();
+      uint32_t x = hl < nc ? id_of(r, rm) : INF32;
+      s_r[h][hl] = r;
+      wave_lds_sync();
+      bool dup = false;
+      for (uint32_t j4 = 0; j4 < nmax; j4 += 4) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[h][j4]);
+        dup |= (v.x == r && j4 + 0 < hl) || (v.y == r && j4 + 1 < hl) || (v.z == r && j4 + 2 < hl) ||
+               (v.w == r && j4 + 3 < hl);
+      }
+      wave_lds_sync();
+      if (dup) x = r = INF32;
+      s_r[h][hl] = r;
+      s_id[h][hl] = x;
+      wave_lds_sync();
+      // accepted: fewer than k ranks below its own in the set or among the
+      // candidates with a smaller id (none is in the set: the offers checked)
+      const uint32_t q = half_count_below(setv, r);
+      uint32_t cb = 0;
+      for (uint32_t j4 = 0; j4 < nmax; j4 += 4) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[h][j4]);
+        const uint4 w = *reinterpret_cast<const uint4 *>(&s_id[h][j4]);
+        cb += (v.x < r && w.x < x) ? 1u : 0u;
+        cb += (v.y < r && w.y < x) ? 1u : 0u;
+        cb += (v.z < r && w.z < x) ? 1u : 0u;
+        cb += (v.w < r && w.w < x) ? 1u : 0u;
+      }
+      wave_lds_sync();
+      const bool acc = x != INF32 && q + cb < k;
+      m = (uint32_t)__popc(half_ballot(acc));
+      if (!acc) x = r = INF32;
+      s_r[h][hl] = r;
+      s_id[h][hl] = x;
+      wave_lds_sync();
+      // each accepted one's place by id and by rank, and how many rank below
+      // this lane's set element
+      uint32_t pi = 0, pr = 0, add = 0;
+      for (uint32_t j4 = 0; j4 < nmax; j4 += 4) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[h][j4]);
+        const uint4 w = *reinterpret_cast<const uint4 *>(&s_id[h][j4]);
+        pi += (w.x < x ? 1u : 0u) + (w.y < x ? 1u : 0u) + (w.z < x ? 1u : 0u) + (w.w < x ? 1u : 0u);
+        pr += (v.x < r ? 1u : 0u) + (v.y < r ? 1u : 0u) + (v.z < r ? 1u : 0u) + (v.w < r ? 1u : 0u);
+        add += (v.x < setv ? 1u : 0u) + (v.y < setv ? 1u : 0u) + (v.z < setv ? 1u : 0u) + (v.w < setv ? 1u : 0u);
+      }
+      wave_lds_sync();
+      if (acc) {
+        s_acc[h][pi] = x;
+        s_r[h][pr] = r;
+        if (q + pr < k) s_set[h][q + pr] = r;
+      }
+      if (hl < nset0 && hl + add < k) s_set[h][hl + add] = setv;
+      wave_lds_sync();
+      nset1 = nset0 + m < k ? nset0 + m : k;
+      set1 = hl < nset1 ? s_set[h][hl] : INF32;
+      ra = hl < m ? s_r[h][hl] : INF32;
+    } else if (nmax) {
     // Up to 64 survivors, sorted by id and decided in chunks of 32: each id
     // is accepted if fewer than k ranks below its own are in the set (which
     // by the second chunk holds the first chunk's accepted ranks) or among
     // the chunk's earlier candidates.  (Every shuffle here runs on all lanes:
     // a lane reads another only while that lane is active.)
-    const bool two = __ballot(act && ns > HALF) != 0;  // some half has a second chunk
-    uint32_t lo = half_sort((act && hl < ns) ? s_id[h][hl] : INF32), hi = INF32;
+    const bool two = nmax > HALF;  // some half has a second chunk
+    uint32_t lo = half_sort((act && hl < ns) ? id_of(s_id[h][hl], rm) : INF32), hi = INF32;
     if (two) {
-      const uint32_t xb = half_sort((act && HALF + hl < ns) ? s_id[h][HALF + hl] : INF32);
+      const uint32_t xb = half_sort((act && HALF + hl < ns) ? id_of(s_id[h][HALF + hl], rm) : INF32);
       const uint32_t xbr = half_shfl(xb, HALF - 1 - hl);
       const uint32_t l2 = lo < xbr ? lo : xbr, h2 = lo < xbr ? xbr : lo;
       lo = half_bitonic_merge(l2);  // the 32 smallest ids
@@ -1264,9 +1341,10 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
     const uint32_t m1 = (uint32_t)__popc(am1);
     if (acc1) s_acc[h][half_below(am1)] = lo;
     const uint32_t xs1 = half_sort(acc1 ? r1 : INF32);
-    uint32_t set1 = merge_set(setv, xs1);
-    uint32_t nset1 = nset0 + m1 < k ? nset0 + m1 : k;
-    uint32_t ra = xs1, rb = INF32, m = m1;  // the level's ranks ascending: ra, then rb
+    set1 = merge_set(setv, xs1);
+    nset1 = nset0 + m1 < k ? nset0 + m1 : k;
+    ra = xs1;
+    m = m1;
     if (two) {
       const uint32_t prevx = half_shfl(lo, HALF - 1);  // the first chunk is full when there is a second
       uint32_t r2 = INF32;
@@ -1284,7 +1362,9 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
       m = m1 + m2;
     }
     wave_lds_sync();  // s_acc is read below
-    const uint32_t x0 = half_shfl(ra, 0), x1 = half_shfl(ra, 1);
+    }
+    x0 = half_shfl(ra, 0);
+    x1 = half_shfl(ra, 1);
     bool committed = false;
     if (act && m) {
       if (cu + m > P.cap) {
