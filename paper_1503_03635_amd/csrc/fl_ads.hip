@@ -11,7 +11,7 @@
 // vertices that reach u, at d(v, u) (an undirected graph is read as both arcs).
 //
 // Work items.  A vertex with at most TASK_ARCS arcs (TASK_ARCS_SPARSE in
-// rounds run from worklists) is one task; a larger one is split into tasks of
+// rounds run from marks) is one task; a larger one is split into tasks of
 // that many arcs.  Each task (one wave64) streams the
 // entries its neighbours inserted at distance D - w (pull), drops those whose
 // rank is not below T_u (the k-th smallest rank of u's sketch so far: k
@@ -20,14 +20,14 @@
 // sets in scratch; a merge wave prunes their union (the prune is associative
 // and idempotent, so the split does not change the result).
 //
-// Level records and arc planes.  The level a vertex commits at distance D is
+// Level records and marks.  The level a vertex commits at distance D is
 // described in slot D % NS of its record ring (start, count and its two
 // smallest ranks), so a level of one or two entries needs no further read and
 // a level whose smallest rank fails the reader's threshold is skipped whole.
-// In rounds run from worklists, the committing vertex also sets, for each arc
-// it marks, the bit of the arc's position in the head's in-arc row in the
-// bit plane of the round the level reaches the head; a task then reads only
-// the arcs whose bits are set instead of every in-arc.
+// In rounds run from marks, the committing vertex sets, for each arc out of it,
+// the bit of the arc's position in the head's in-arc row in the bit plane of
+// the round the level reaches the head; that round's tasks are the vertices
+// with a bit in their row, and a task reads only the arcs whose bits are set.
 //
 // Level prune.  A candidate of level D is accepted iff fewer than k ranks
 // below its own belong to entries that come first: the sketch so far, or
@@ -47,6 +47,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 
 #include "fl_ads.h"
 #include "fl_common.h"
@@ -64,23 +65,16 @@ constexpr uint32_t ADS_SB = 1024;
 static_assert((ADS_SB & (ADS_SB - 1)) == 0, "wave_sort_lds pads to a power of two inside the buffer");
 inline uint32_t ads_full_sb(uint32_t k) { return k > 64 ? 2 * ADS_SB : ADS_SB; }
 constexpr uint32_t TASK_ARCS = 1024;  // arcs per task of a split vertex in dense rounds (the fewest)
-// Sparse rounds (worklists) cut only longer rows: there a hub is active in
+// Sparse rounds (run from marks) cut only longer rows: there a hub is active in
 // most rounds but few of its arcs bring candidates, and every split costs a
 // merge that prunes the tasks' kept sets again.  Results do not depend on the
 // cut (a candidate accepted over all arcs is accepted within its piece, and
 // the merge prunes the union exactly).
 constexpr uint32_t TASK_ARCS_SPARSE = 2048;
 static_assert(TASK_ARCS_SPARSE >= TASK_ARCS, "scratch slots are sized for TASK_ARCS");
-// With arc bit planes a task reads only the arcs that carry a level, so its
-// cost follows those, not its length: rows are cut far less often.
+// With marks by arc a task reads only the arcs that carry a level, so its cost
+// follows those, not its length: rows are cut far less often.
 constexpr uint32_t TASK_ARCS_FLAGGED = 8192;
-// Rounds read flagged arcs only from FLAG_FROM_RINGS times the slot ring
-// (max weight + 1) on, and commits set plane bits from a ring earlier (the
-// levels those rounds read).  With one task per wave, scanning every in-arc
-// cost less while most vertices were active (1 ring); with two small tasks
-// per wave the planes pay from the first round (0): a task reads only the
-// arcs that carry a level, and rows split at TASK_ARCS_FLAGGED from the start.
-constexpr uint32_t FLAG_FROM_RINGS = 0;
 static_assert(TASK_ARCS_FLAGGED >= TASK_ARCS, "scratch slots are sized for TASK_ARCS");
 constexpr uint32_t NBKT = 64;       // id buckets of the level prune (one per lane)
 constexpr uint32_t LONG_LIST = 64;  // entry lists at least this long are streamed one arc at a time
@@ -97,12 +91,11 @@ enum CtrField : uint32_t {
   CF_PRUNES,        // level prunes
   CF_SCANNED,       // arcs scanned (dbg)
   CF_MATCHED,       // level records matched (dbg)
-  CF_MARK_ARCS,     // arcs examined for marking (dbg)
-  CF_MARKED,        // heads that passed the marking filter (dbg)
+  CF_REACH,         // largest distance any arc was marked for (a maximum)
   CF_COUNT
 };
 struct AdsArgs {
-  uint32_t n, k, cap, W, NS, FW;
+  uint32_t n, k, cap, W, NS;
   const uint32_t *gid;  // graph of each vertex (nullptr: one graph)
   const SegInfo *seg;   // per-graph rank keys, base, bucket shift
   // entries travel along arcs: a vertex gathers over its in-arcs and, when
@@ -119,15 +112,15 @@ struct AdsArgs {
   uint32_t *bk;
   uint32_t *cnt;
   uint4 *lvl;          // [NS * n] level records, slot (D % NS) of each vertex
-  uint32_t *flags;
-  uint32_t *wl;
-  uint32_t *wl_cnt;
-  // arc bit planes of the rounds run from worklists (nullptr: scan every in-arc)
-  uint32_t *plane;            // [NS * pw] bit of in-arc position p set in plane D % NS: a level reaches it in round D
-  uint64_t pw;                // words per plane
-  uint32_t flag_from;         // first round whose tasks read only flagged arcs
-  uint32_t plane_from;        // first round whose commits set plane bits (flag_from - max weight)
-  const uint32_t *out_to_in;  // [m] out-arc -> in-arc position
+  // Marks of the rounds to come, in planes of pw words, plane D % NS for round
+  // D.  With by_arc, bit p of a plane says that a level reaches in-arc position
+  // p in that round; otherwise (arc positions do not fit 32 bits) bit u says
+  // that some level reaches vertex u, and a task scans all its in-arcs.
+  uint32_t *plane;
+  uint64_t pw;
+  uint32_t by_arc;
+  const uint32_t *out_to_in;  // [m] out-arc -> in-arc position (by_arc)
+  uint32_t *reach;            // [1] CF_REACH as of the start of the current round
   uint32_t *kept;      // [slots * sb] kept ids of split tasks
   uint32_t sb;         // survivor buffer of the build (the round kernels' template argument)
   uint32_t *kept_cnt;  // [slots]
@@ -156,30 +149,31 @@ __device__ inline uint4 level_record(uint32_t D, uint32_t r0, uint32_t r1, uint3
   return make_uint4(D, r0, r1, start | (count << 16));
 }
 
-// Append y to the worklist of slot s once (flag bit per (vertex, slot)).
-// Lanes with want=false do nothing.
+// The out-arc a leads to a level in round D + w: set its bit in that round's
+// plane (Dm = D % NS), with no wait.  A larger distance than any marked before
+// goes to the block's stripe of CF_REACH (few arcs: from the first rounds on
+// only the heaviest exceed what earlier rounds reached; with unit weights
+// every arc of a round reaches as far, and one lane speaks for the wave).
 template <bool UNITW>
-__device__ inline void mark_targets(const AdsArgs &P, bool want, uint32_t y, uint32_t s) {
-  bool add = false;
-  if (want) {
-    uint32_t *word = &P.flags[(size_t)y * P.FW + (s >> 5)];
-    const uint32_t bit = 1u << (s & 31);
-    if (!(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
-      add = !(atomicOr(word, bit) & bit);
+__device__ inline void mark_arc(const AdsArgs &P, uint64_t a, uint32_t D, uint32_t Dm, uint32_t seen) {
+  const uint32_t wv = UNITW ? 1u : P.out_w[a];
+  uint32_t s = Dm + wv;
+  if (s >= P.NS) s -= P.NS;
+  uint32_t *pl = P.plane + (size_t)s * P.pw;
+  if (P.by_arc) {
+    const uint32_t p = P.out_to_in[a];
+    atomicOr(&pl[p >> 5], 1u << (p & 31));
+  } else {
+    const uint32_t y = P.out_col[a];
+    const uint32_t bit = 1u << (y & 31);
+    if (!(__hip_atomic_load(&pl[y >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(&pl[y >> 5], bit);
   }
-  if (UNITW) {
-    // every lane's slot is D + 1: one atomic per wave
-    wave_push(P.wl + (size_t)s * P.n, &P.wl_cnt[s * CNT_PAD], add, y);
-  } else if (add) {
-    // the lanes' slots are mostly distinct (about 47 of 64 for weights
-    // 1..100): one atomic per lane costs less than grouping them by slot
-    const uint32_t pos = atomicAdd(&P.wl_cnt[s * CNT_PAD], 1u);
-    P.wl[(size_t)s * P.n + pos] = y;
-  }
+  if (D + wv > seen && (!UNITW || lane_id() == __ffsll((long long)__ballot(1)) - 1))
+    atomicMax((unsigned long long *)&P.ctr[(blockIdx.x % CTR_STRIPES) * CTR_FIELDS + CF_REACH],
+              (unsigned long long)(D + wv));
 }
 
-// u committed a level at distance D: queue each head y of an arc u -> y for
-// round D + w, and set the arc's bit in that round's plane.  Several waves
+// u committed a level at distance D: mark the arcs out of u.  Several waves
 // can share a long row: wave `part` of `parts` takes every parts-th group of
 // 64 arcs.
 template <bool UNITW>
@@ -187,28 +181,9 @@ __device__ inline void mark_neighbours(const AdsArgs &P, uint32_t u, uint32_t D,
                                        uint32_t parts = 1) {
   const int lane = lane_id();
   const uint64_t a0 = P.out_ptr[u], a1 = P.out_ptr[u + 1];
-  for (uint64_t b = a0 + (uint64_t)part * WAVE; b < a1; b += (uint64_t)parts * WAVE) {
-    const uint64_t a = b + lane;
-    bool want = a < a1;
-    uint32_t y = 0, s = 0;
-    if (want) {
-      y = P.out_col[a];
-      const uint32_t wv = UNITW ? 1u : P.out_w[a];
-      s = (D + wv) % P.NS;
-      if (P.plane && D >= P.plane_from) {
-        const uint32_t p = P.out_to_in[a];
-        atomicOr(&P.plane[(size_t)s * P.pw + (p >> 5)], 1u << (p & 31));
-      }
-    }
-    if (P.dbg) {
-      const uint64_t wm = __ballot(want);
-      if (lane == 0) {
-        ctr_add(P, CF_MARK_ARCS, a1 - b < WAVE ? a1 - b : WAVE);
-        ctr_add(P, CF_MARKED, __popcll(wm));
-      }
-    }
-    mark_targets<UNITW>(P, want, y, s);
-  }
+  const uint32_t Dm = D % P.NS, seen = *P.reach;
+  for (uint64_t a = a0 + (uint64_t)part * WAVE + lane; a < a1; a += (uint64_t)parts * WAVE)
+    mark_arc<UNITW>(P, a, D, Dm, seen);
 }
 
 // Round 0: every vertex holds (r(v), 0).  One wave per vertex.
@@ -629,29 +604,30 @@ __device__ inline void level_init(const AdsArgs &P, uint32_t u, Level<KR> &L, ui
   L.nsurv = L.nprune = L.nmatch = 0;
 }
 
-// One candidate per lane (valid, rank r, id if known): keep it if its rank is
+// One candidate per lane (valid, rank r): keep it if its rank is
 // below T0 and it is not already in the set; buffer kept ids, shrinking the
 // buffer by a prune against the set when full.
 template <int KR, uint32_t SB>
-__device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, uint32_t r, bool have_id, uint32_t id,
-                                   uint32_t *s_id, uint32_t *s_tmp, uint32_t *s_cnt) {
+__device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, uint32_t r, uint32_t *s_id,
+                                   uint32_t *s_tmp, uint32_t *s_cnt) {
   const uint32_t *s_set0 = s_cnt + WAVE;  // LDS copy of the set at the level start
   const int lane = lane_id();
   bool pass = valid && (!L.full0 || r < L.T0);
   if (!__ballot(pass)) return;
-  if (pass) {
-    // already in the set (same vertex at a shorter distance)?
-    uint32_t lo = 0, hi = L.nset0;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (s_set0[mid] < r) lo = mid + 1;
-      else hi = mid;
-    }
+  {
+    // already in the set (same vertex at a shorter distance)?  A search of
+    // fixed length over the padded set, without branches: a loop that each
+    // lane leaves at its own step cost more (round kernels of R-MAT 2^22, k =
+    // 64: 743 -> 703 ms)
+    uint32_t lo = 0;
+#pragma unroll
+    for (uint32_t s = 32 * KR; s >= 1; s >>= 1)
+      if (s_set0[lo + s - 1] < r) lo += s;
     if (lo < L.nset0 && s_set0[lo] == r) pass = false;
   }
   // bucket bound from the last prune: all candidates of earlier id buckets
   // come first, and k of them (or of the set) already rank below it
-  const uint32_t cid = pass ? (have_id ? id : id_of(r, L.rm)) : L.rm.base;
+  const uint32_t cid = pass ? id_of(r, L.rm) : L.rm.base;
   const uint32_t bnd = __shfl(L.tb, (int)bucket_of(cid, L.rm), WAVE);
   if (pass && r >= bnd) pass = false;
   uint64_t msk = __ballot(pass);
@@ -689,6 +665,7 @@ template <bool UNITW, int KR, uint32_t SB>
 __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a, bool valid, Level<KR> &L,
                                         uint32_t *s_id, uint32_t *s_tmp, uint32_t *s_cnt) {
   const int lane = lane_id();
+  const uint32_t Dm = D % P.NS;
   uint64_t examined = 0;
   {
     uint32_t v = 0, st = 0, cn = 0, r0 = INF32, r1 = INF32;
@@ -697,7 +674,8 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
       const uint32_t wv = UNITW ? 1u : P.w[a];
       if (wv <= D) {
         const uint32_t src = D - wv;
-        const uint4 rec = P.lvl[(size_t)(src % P.NS) * P.n + v];
+        const uint32_t sl = Dm >= wv ? Dm - wv : Dm + P.NS - wv;
+        const uint4 rec = P.lvl[(size_t)sl * P.n + v];
         // a level whose smallest rank is not below T0 has nothing for u
         if (P.dbg && rec.x == src) ++L.nmatch;
         if (rec.x == src && (!L.full0 || rec.y < L.T0)) {
@@ -708,18 +686,13 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
         }
       }
     }
-    // levels of one or two entries: the ranks are in the record
-    {
-      const bool one = cn != 0 && cn <= 2;
-      const bool two = cn == 2;
-      examined += __popcll(__ballot(one)) + __popcll(__ballot(two));
-      level_offer<KR, SB>(P, L, one, r0, false, 0, s_id, s_tmp, s_cnt);
-      if (__ballot(two) && !L.overflow) level_offer<KR, SB>(P, L, two, r1, false, 0, s_id, s_tmp, s_cnt);
-      if (cn <= 2) cn = 0;
-    }
-    // long lists: one arc at a time, the whole wave on its list, four loads in
-    // flight.  A level is stored in increasing rank order, so once a rank
-    // reaches T0 the rest of the list cannot enter u's sketch.
+    // Long lists: one arc at a time, the whole wave on its list, four loads in
+    // flight (r0 is offered while r1, r2 and r3 arrive).  A level is stored in
+    // increasing rank order, so once a rank reaches T0 the rest of the list
+    // cannot enter u's sketch.  (A block past the stop test is loaded, not
+    // counted.)  The filter and prune of an offer are a few thousand
+    // instructions inlined, so there is one offer for long lists and one for
+    // short ones; seven copies cost instruction fetches and scalar registers.
     uint64_t lm = __ballot(cn >= LONG_LIST);
     while (lm && !L.overflow) {
       const int j = __ffsll((long long)lm) - 1;
@@ -728,35 +701,23 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
       const uint32_t stj = __shfl(st, j, WAVE);
       const uint32_t cnj = __shfl(cn, j, WAVE);
       const uint32_t *src = P.sk_rank + (size_t)vj * P.cap + stj;
-      for (uint32_t c0 = 0; c0 < cnj && !L.overflow; c0 += 4 * WAVE) {
-        const uint32_t i0 = c0 + lane, i1 = i0 + WAVE, i2 = i1 + WAVE, i3 = i2 + WAVE;
-        const uint32_t r0 = i0 < cnj ? src[i0] : INF32;
-        const uint32_t r1 = i1 < cnj ? src[i1] : INF32;
-        const uint32_t r2 = i2 < cnj ? src[i2] : INF32;
-        const uint32_t r3 = i3 < cnj ? src[i3] : INF32;
-        // entries offered (a block past the stop test is loaded, not counted)
-        const uint32_t left = cnj - c0;
-        examined += left < WAVE ? left : WAVE;
-        level_offer<KR, SB>(P, L, i0 < cnj, r0, false, 0, s_id, s_tmp, s_cnt);
-        if (L.full0 && __ballot(i0 < cnj && r0 >= L.T0)) break;
-        if (c0 + WAVE < cnj) {
-          examined += left - WAVE < WAVE ? left - WAVE : WAVE;
-          level_offer<KR, SB>(P, L, i1 < cnj, r1, false, 0, s_id, s_tmp, s_cnt);
-        }
-        if (L.full0 && __ballot(i1 < cnj && r1 >= L.T0)) break;
-        if (c0 + 2 * WAVE < cnj) {
-          examined += left - 2 * WAVE < WAVE ? left - 2 * WAVE : WAVE;
-          level_offer<KR, SB>(P, L, i2 < cnj, r2, false, 0, s_id, s_tmp, s_cnt);
-        }
-        if (L.full0 && __ballot(i2 < cnj && r2 >= L.T0)) break;
-        if (c0 + 3 * WAVE < cnj) {
-          examined += left - 3 * WAVE < WAVE ? left - 3 * WAVE : WAVE;
-          level_offer<KR, SB>(P, L, i3 < cnj, r3, false, 0, s_id, s_tmp, s_cnt);
-        }
-        if (L.full0 && __ballot(i3 < cnj && r3 >= L.T0)) break;
+      auto load = [&](uint32_t i) -> uint32_t { return i < cnj ? src[i] : INF32; };
+      uint32_t q0 = load(lane), q1 = load(lane + WAVE), q2 = load(lane + 2 * WAVE), q3 = load(lane + 3 * WAVE);
+      for (uint32_t c0 = 0; c0 < cnj && !L.overflow; c0 += WAVE) {
+        const bool in = c0 + lane < cnj;
+        const uint32_t r = q0;
+        q0 = q1;
+        q1 = q2;
+        q2 = q3;
+        q3 = load(c0 + lane + 4 * WAVE);
+        examined += cnj - c0 < WAVE ? cnj - c0 : WAVE;
+        level_offer<KR, SB>(P, L, in, r, s_id, s_tmp, s_cnt);
+        if (L.full0 && __ballot(in && r >= L.T0)) break;
       }
     }
-    // short lists: flattened over the group, owner lane found by binary search
+    // Short lists: flattened over the wave, the owner lane of an entry found by
+    // binary search.  A level of one or two entries has its ranks in the
+    // record.
     const uint32_t cs = cn < LONG_LIST ? cn : 0u;
     const uint32_t incl = wave_scan_incl(cs);
     const uint32_t total = __shfl(incl, WAVE - 1, WAVE);
@@ -770,13 +731,15 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
         const uint32_t val = __shfl(incl, (int)(pos + s - 1), WAVE);
         if (val <= idx) pos += s;
       }
-      const bool valid = idx < total;
+      const bool in = idx < total;
       const uint32_t ov = __shfl(v, (int)pos, WAVE);
       const uint32_t ost = __shfl(st, (int)pos, WAVE);
-      const uint32_t oex = __shfl(excl, (int)pos, WAVE);
-      uint32_t r = INF32;
-      if (valid) r = P.sk_rank[(size_t)ov * P.cap + ost + (idx - oex)];
-      level_offer<KR, SB>(P, L, valid, r, false, 0, s_id, s_tmp, s_cnt);
+      const uint32_t ocn = __shfl(cs, (int)pos, WAVE);
+      const uint32_t i = idx - __shfl(excl, (int)pos, WAVE);
+      const uint32_t o0 = __shfl(r0, (int)pos, WAVE), o1 = __shfl(r1, (int)pos, WAVE);
+      uint32_t r = i == 0 ? o0 : o1;
+      if (in && ocn > 2) r = P.sk_rank[(size_t)ov * P.cap + ost + i];
+      level_offer<KR, SB>(P, L, in, r, s_id, s_tmp, s_cnt);
     }
   }
   return examined;
@@ -794,7 +757,7 @@ __device__ inline uint64_t gather_arcs(const AdsArgs &P, uint32_t D, uint64_t a0
   return examined;
 }
 
-// Rounds run from worklists: a tail that committed a level set the bit of
+// Rounds run from marks: a tail that committed a level set the bit of
 // each arc it marked, at the arc's position in the in-arc rows, in the plane
 // of the round the level reaches the head.  Only those arcs of [a0, a1) are
 // read: 64 plane words per step, their set bits compacted over the wave.
@@ -909,10 +872,6 @@ __device__ inline void ads_task(const AdsArgs &P, uint32_t D, uint32_t u, uint32
                                 uint32_t task_arcs, int sparse, int mark, uint32_t *s_id, uint32_t *s_tmp,
                                 uint32_t *s_cnt) {
   const int lane = lane_id();
-  if (sparse && sub == 0 && lane == 0) {
-    const uint32_t sD = D % P.NS;
-    atomicAnd(&P.flags[(size_t)u * P.FW + (sD >> 5)], ~(1u << (sD & 31)));
-  }
   Level<KR> L;
   level_init(P, u, L, s_cnt);
   const uint64_t r0 = P.row_ptr[u], r1 = P.row_ptr[u + 1];
@@ -921,9 +880,8 @@ __device__ inline void ads_task(const AdsArgs &P, uint32_t D, uint32_t u, uint32
     a0 = r0 + (uint64_t)sub * task_arcs;
     a1 = a0 + task_arcs < r1 ? a0 + task_arcs : r1;
   }
-  const uint64_t examined = (sparse && P.plane && D >= P.flag_from)
-                                ? gather_flagged<UNITW, KR, SB>(P, D, a0, a1, L, s_id, s_tmp, s_cnt)
-                                                 : gather_arcs<UNITW, KR, SB>(P, D, a0, a1, L, s_id, s_tmp, s_cnt);
+  const uint64_t examined = sparse && P.by_arc ? gather_flagged<UNITW, KR, SB>(P, D, a0, a1, L, s_id, s_tmp, s_cnt)
+                                               : gather_arcs<UNITW, KR, SB>(P, D, a0, a1, L, s_id, s_tmp, s_cnt);
   if (lane == 0) {
     ctr_add(P, CF_EXAMINED, examined);
     ctr_add(P, CF_SURVIVORS, L.nsurv);
@@ -955,17 +913,22 @@ __device__ inline void ads_task(const AdsArgs &P, uint32_t D, uint32_t u, uint32
 }
 
 // ---------------------------------------------------------------------------
-// Two small tasks per wave (k <= 32, rounds run from worklists).  Lanes
+// Two small tasks per wave (k <= 32, rounds run from marks).  Lanes
 // 0..31 run one task and lanes 32..63 the next; every step works within the
 // lane's half (shuffles of width 32, ballots cut to the half), so the fixed
 // per-task instructions are shared by two tasks.  A task the halves cannot
 // finish -- a slice of a split vertex, a row of more than PAIR_ROW_MAX arcs,
-// more than 64 survivors in its level -- is left to the one-wave kernel, which runs after this one in the same round
-// (pend[t] = 1); it is left before it has written anything but its own flag
-// bit, which that kernel clears again.  Tasks of a round are independent and
+// more than 64 survivors in its level -- is left, before it has written
+// anything, to the one-wave kernel, which runs after this one in the same
+// round on the list of tasks left.  Tasks of a round are independent and
 // the prune does not depend on how candidates are grouped, so both kernels
 // give the same levels.
 // ---------------------------------------------------------------------------
+// Device totals of one round run from marks.
+struct RoundTot {
+  unsigned long long tasks, slots, splits;  // task list, kept slots, split vertices
+  unsigned long long left;                  // tasks the two-task kernel left
+};
 constexpr uint32_t HALF = 32;
 // Rows longer than this go to the one-wave kernel too: a wave runs two
 // unrelated tasks, and a long row would keep its partner half idle (2,048
@@ -1031,15 +994,16 @@ static_assert(PAIR_FEW <= HALF, "one survivor per lane");
 template <bool UNITW>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *task_sub, const uint32_t *task_slot,
-                 const uint64_t *d_ntasks, uint8_t *pend) {
+                 RoundTot *tot, uint32_t *left, uint64_t *ts) {
   __shared__ __align__(16) uint32_t s_id[2][2 * HALF];  // survivors of the level (ranks, then ids)
   __shared__ uint32_t s_acc[2][2 * HALF];           // accepted ids, in id order
   __shared__ uint32_t s_set[2][HALF];               // the set at the level start
   __shared__ __align__(16) uint32_t s_r[2][HALF];   // chunk ranks
   const uint32_t lane = (uint32_t)lane_id(), h = lane >> 5, hl = lane & (HALF - 1);
   const uint32_t k = P.k;
-  const uint64_t total = *d_ntasks;
-  const bool flagged = P.plane && D >= P.flag_from;
+  const uint64_t total = tot->tasks;
+  const uint32_t Dm = D % P.NS, seen = *P.reach;
+  if (ts && blockIdx.x == 0 && lane == 0) *ts = wall_clock64();
   for (uint64_t pi = blockIdx.x; 2 * pi < total; pi += gridDim.x) {
     const uint64_t t = 2 * pi + h;
     const bool live = t < total;
@@ -1050,10 +1014,6 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
     }
     bool defer = live && slot != INF32;  // a slice of a split vertex
     bool act = live && !defer;           // half-uniform from here on
-    if (act && hl == 0) {
-      const uint32_t sD = D % P.NS;
-      atomicAnd(&P.flags[(size_t)u * P.FW + (sD >> 5)], ~(1u << (sD & 31)));
-    }
     // the task's row, set and count are loaded together: one wait
     const RankMap rm = rank_map(P.seg[seg_of(P.gid, u)]);
     const uint32_t cu = act ? P.cnt[u] : 0u;
@@ -1075,15 +1035,14 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
     // one candidate per lane: kept if below T0 and not in the start set
     auto offer = [&](bool valid, uint32_t r) {
       bool pass = act && valid && (!full0 || r < T0);
-      if (pass) {
-        uint32_t lo = 0, hi = nset0;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (s_set[h][mid] < r) lo = mid + 1;
-          else hi = mid;
-        }
-        if (lo < nset0 && s_set[h][lo] == r) pass = false;
-      }
+      if (!__ballot(pass)) return;
+      // already in the set?  A search of fixed length over the padded set,
+      // without branches (the lanes would leave a loop at different steps)
+      uint32_t lo = 0;
+#pragma unroll
+      for (uint32_t s = HALF / 2; s >= 1; s >>= 1)
+        if (s_set[h][lo + s - 1] < r) lo += s;
+      if (lo < nset0 && s_set[h][lo] == r) pass = false;
       const uint32_t m = half_ballot(pass);
       const uint32_t np = (uint32_t)__popc(m);
       if (ns + np > 2 * HALF) {
@@ -1103,7 +1062,8 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
         const uint32_t wv = UNITW ? 1u : P.w[a];
         if (wv <= D) {
           const uint32_t src = D - wv;
-          const uint4 rec = P.lvl[(size_t)(src % P.NS) * P.n + v];
+          const uint32_t sl = Dm >= wv ? Dm - wv : Dm + P.NS - wv;
+          const uint4 rec = P.lvl[(size_t)sl * P.n + v];
           if (rec.x == src && (!full0 || rec.y < T0)) {
             r0 = rec.y;
             r1 = rec.z;
@@ -1112,10 +1072,6 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
           }
         }
       }
-      const bool one = cn != 0 && cn <= 2, two = cn == 2;
-      examined += (uint32_t)__popc(half_ballot(one)) + (uint32_t)__popc(half_ballot(two));
-      offer(one, r0);
-      offer(two, r1);
       // long lists: one at a time per half, 32 entries per step; a level is
       // stored in increasing rank order, so once a rank reaches T0 the rest
       // of the list cannot enter
@@ -1140,7 +1096,10 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
           if (full0 && half_ballot(ok && r >= T0)) go = false;
         }
       }
-      const uint32_t cs = (act && cn > 2 && cn < LONG_LIST) ? cn : 0u;
+      // short lists: flattened over the half, the owner lane of an entry found
+      // by binary search; a level of one or two entries has its ranks in the
+      // record
+      const uint32_t cs = (act && cn < LONG_LIST) ? cn : 0u;
       const uint32_t incl = half_scan_incl(cs);
       const uint32_t tot = half_shfl(incl, HALF - 1);
       const uint32_t excl = incl - cs;
@@ -1156,9 +1115,11 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
           if (val <= idx) pos += s;
         }
         const bool ok = cm && idx < tot;
-        const uint32_t ov = half_shfl(v, pos), ost = half_shfl(st, pos), oex = half_shfl(excl, pos);
-        uint32_t r = INF32;
-        if (ok) r = P.sk_rank[(size_t)ov * P.cap + ost + (idx - oex)];
+        const uint32_t ov = half_shfl(v, pos), ost = half_shfl(st, pos), ocn = half_shfl(cs, pos);
+        const uint32_t i = idx - half_shfl(excl, pos);
+        const uint32_t o0 = half_shfl(r0, pos), o1 = half_shfl(r1, pos);
+        uint32_t r = i == 0 ? o0 : o1;
+        if (ok && ocn > 2) r = P.sk_rank[(size_t)ov * P.cap + ost + i];
         offer(ok, r);
       }
     };
@@ -1166,9 +1127,9 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
       defer = true;  // a long row: the one-wave kernel
       act = false;
     }
-    if (flagged) {
-      // only the arcs flagged in this round's plane
-      const uint32_t *plane = P.plane + (size_t)(D % P.NS) * P.pw;
+    if (P.by_arc) {
+      // only the arcs marked in this round's plane
+      const uint32_t *plane = P.plane + (size_t)Dm * P.pw;
       const uint64_t w0 = a0 >> 5, w1 = (a1 + 31) >> 5;
       for (uint64_t wb = w0;; wb += HALF) {
         const bool more = act && wb < w1;
@@ -1393,36 +1354,26 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
         }
       }
     }
-    // the heads of u's out-arcs are queued for round D + w
-    uint64_t b0 = 0, b1 = 0;
+    // u's out-arcs are marked for round D + w
     if (committed) {
-      b0 = P.out_ptr[u];
-      b1 = P.out_ptr[u + 1];
+      // (an undirected graph's out-arcs are its in-arcs)
+      const bool same = P.out_ptr == P.row_ptr;
+      const uint64_t b0 = same ? a0 : P.out_ptr[u], b1 = same ? a1 : P.out_ptr[u + 1];
+      for (uint64_t a = b0 + hl; a < b1; a += HALF) mark_arc<UNITW>(P, a, D, Dm, seen);
     }
-    for (uint64_t b = b0;; b += HALF) {
-      const bool more = committed && b < b1;
-      if (!__ballot(more)) break;
-      const uint64_t a = b + hl;
-      const bool want = more && a < b1;
-      uint32_t y = 0, s = 0;
-      if (want) {
-        y = P.out_col[a];
-        const uint32_t wv = UNITW ? 1u : P.out_w[a];
-        s = (D + wv) % P.NS;
-        if (P.plane && D >= P.plane_from) {
-          const uint32_t p = P.out_to_in[a];
-          atomicOr(&P.plane[(size_t)s * P.pw + (p >> 5)], 1u << (p & 31));
-        }
-      }
-      mark_targets<UNITW>(P, want, y, s);
+    // tasks left to the one-wave kernel
+    const bool lv = live && hl == 0 && defer;
+    const uint64_t lm = __ballot(lv);
+    if (lm) {
+      uint32_t p0 = 0;
+      if (lane == 0) p0 = (uint32_t)atomicAdd(&tot->left, (unsigned long long)__popcll(lm));
+      p0 = __shfl(p0, 0, WAVE);
+      if (lv) left[p0 + lanes_below(lm)] = (uint32_t)t;
     }
-    if (live && hl == 0) {
-      pend[t] = defer ? 1 : 0;
-      if (!defer) {
-        ctr_add(P, CF_EXAMINED, examined);
-        ctr_add(P, CF_SURVIVORS, ns);
-        if (committed) ctr_add(P, CF_COMMITS, 1);
-      }
+    if (live && hl == 0 && !defer) {
+      ctr_add(P, CF_EXAMINED, examined);
+      ctr_add(P, CF_SURVIVORS, ns);
+      if (committed) ctr_add(P, CF_COMMITS, 1);
     }
     wave_lds_sync();  // the half buffers are rewritten by the next pair
   }
@@ -1430,21 +1381,22 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
 
 // One wave per task.  task_slot == INF32: the task is the whole vertex and
 // commits; otherwise it leaves its kept set in scratch slot task_slot.  With
-// d_ntasks (device) the grid strides over that many tasks (the host does not
-// know the count); otherwise one wave per task.  With `only`, just the tasks
-// t with only[t] != 0 (those the two-task kernel left).
+// tot (device) the grid strides over its task count (the host does not know
+// it); otherwise one wave per task.  With `left`, just the tasks of that list
+// (those the two-task kernel left).
 template <bool UNITW, int KR, uint32_t SB>
 __global__ __launch_bounds__(TASK_WPB * WAVE) __attribute__((amdgpu_waves_per_eu(SB <= ADS_SB / 2 ? 5 : 4)))
 void k_ads_tasks(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *task_sub, const uint32_t *task_slot,
-                 uint32_t ntasks, const uint64_t *d_ntasks, uint32_t task_arcs, int sparse, int mark,
-                 const uint8_t *only) {
+                 uint32_t ntasks, const RoundTot *tot, uint32_t task_arcs, int sparse, int mark,
+                 const uint32_t *left, uint64_t *ts) {
   __shared__ uint32_t lds_id[TASK_WPB][SB];
   __shared__ uint32_t lds_tmp[TASK_WPB][SB];
   __shared__ __align__(16) uint32_t lds_cnt[TASK_WPB][(2 + KR) * WAVE];
   const int wv = threadIdx.x / WAVE;
-  const uint64_t total = d_ntasks ? *d_ntasks : ntasks;
-  for (uint64_t item = (uint64_t)blockIdx.x * TASK_WPB + wv; item < total; item += (uint64_t)gridDim.x * TASK_WPB) {
-    if (only && !only[item]) continue;  // done by the two-task kernel
+  const uint64_t total = tot ? (left ? tot->left : tot->tasks) : ntasks;
+  if (ts && blockIdx.x == 0 && threadIdx.x == 0) *ts = wall_clock64();
+  for (uint64_t i = (uint64_t)blockIdx.x * TASK_WPB + wv; i < total; i += (uint64_t)gridDim.x * TASK_WPB) {
+    const uint64_t item = left ? left[i] : i;
     ads_task<UNITW, KR, SB>(P, D, task_u[item], task_sub[item], task_slot[item], task_arcs, sparse, mark, lds_id[wv],
                             lds_tmp[wv], lds_cnt[wv]);
   }
@@ -1460,7 +1412,7 @@ template <bool UNITW, int KR, uint32_t SB>
 __global__ __launch_bounds__(MERGE_WPB * WAVE) void k_ads_merge(AdsArgs P, uint32_t D, const uint32_t *split_u,
                                                                 const uint32_t *split_first,
                                                                 const uint32_t *split_nt, uint32_t nsplit,
-                                                                const uint64_t *d_nsplit, int mark) {
+                                                                const RoundTot *tot, int mark, uint64_t *ts) {
   constexpr uint32_t NW = MERGE_WPB - 1;  // waves that build partial sets
   __shared__ uint32_t lds_id[MERGE_WPB][SB];
   __shared__ uint32_t lds_tmp[MERGE_WPB][SB];
@@ -1474,7 +1426,8 @@ __global__ __launch_bounds__(MERGE_WPB * WAVE) void k_ads_merge(AdsArgs P, uint3
   uint32_t *s_cnt = lds_cnt[wv];
   // the block's split vertices (uniform over the block): every wave reaches
   // both barriers of every item
-  const uint64_t total = d_nsplit ? *d_nsplit : nsplit;
+  const uint64_t total = tot ? tot->splits : nsplit;
+  if (ts && blockIdx.x == 0 && threadIdx.x == 0) *ts = wall_clock64();
   for (uint64_t item = blockIdx.x; item < total; item += gridDim.x) {
     const uint32_t u = split_u[item];
     const uint32_t first = split_first[item];
@@ -1502,12 +1455,8 @@ __global__ __launch_bounds__(MERGE_WPB * WAVE) void k_ads_merge(AdsArgs P, uint3
           const bool valid = idx < tot;
           const uint32_t oex = __shfl(excl, (int)pos, WAVE);
           const uint32_t otask = __shfl(task, (int)pos, WAVE);
-          uint32_t id = INF32, r = INF32;
-          if (valid) {
-            id = P.kept[(size_t)otask * SB + (idx - oex)];
-            r = rank_of(id, L.rm);
-          }
-          level_offer<KR, SB>(P, L, valid, r, true, id, s_id, s_tmp, s_cnt);
+          const uint32_t r = valid ? rank_of(P.kept[(size_t)otask * SB + (idx - oex)], L.rm) : INF32;
+          level_offer<KR, SB>(P, L, valid, r, s_id, s_tmp, s_cnt);
         }
       }
       uint32_t m = 0;
@@ -1529,9 +1478,8 @@ __global__ __launch_bounds__(MERGE_WPB * WAVE) void k_ads_merge(AdsArgs P, uint3
         const uint32_t *part = lds_tmp[w];
         for (uint32_t c0 = 0; c0 < pn && !L.overflow; c0 += WAVE) {
           const bool valid = c0 + lane < pn;
-          const uint32_t id = valid ? part[c0 + lane] : INF32;
-          const uint32_t r = valid ? rank_of(id, L.rm) : INF32;
-          level_offer<KR, SB>(P, L, valid, r, true, id, s_id, s_tmp, s_cnt);
+          const uint32_t r = valid ? rank_of(part[c0 + lane], L.rm) : INF32;
+          level_offer<KR, SB>(P, L, valid, r, s_id, s_tmp, s_cnt);
         }
       }
       bool committed = false;
@@ -1665,34 +1613,125 @@ struct TaskScratch {
   uint64_t *toff, *soff, *poff;
 };
 
-// The task list of a worklist whose length only the device knows: each
-// 256-thread block takes TB_ITEMS consecutive entries per thread and reserves
-// the tile's tasks, kept slots and split records with one atomic per counter
-// (the order of the tasks does not matter: the prune does not depend on it).
-// tot: [0] tasks, [1] kept slots, [2] split vertices, zero before the launch.
-constexpr uint32_t TB_ITEMS = 4;
-__global__ __launch_bounds__(256) void k_task_build(const uint32_t *list, const uint32_t *d_count,
-                                                    const uint64_t *row_ptr, uint32_t task_arcs, uint64_t *tot,
-                                                    uint32_t *task_u, uint32_t *task_sub, uint32_t *task_slot,
-                                                    uint32_t *split_u, uint32_t *split_first, uint32_t *split_nt) {
-  __shared__ uint32_t wsum[3][4];
+// Start of a round run from marks: the task list of the vertices with a mark
+// in plane D % NS.  A thread takes `ITEMS` vertices; rows of up to
+// SCAN_WORDS words of the plane are read by their thread, longer ones by the
+// wave, 512 words at a time up to the first mark.  Each block reserves the
+// tile's tasks, kept slots and split records with one atomic per counter (the
+// order of the tasks does not matter: the prune does not depend on it).
+// The launch also clears the plane of round D - 1, which the marks of this
+// round may reuse, and block 0 takes the reach of the earlier rounds.
+//
+// Reading every row pointer and one plane a round (8 B per vertex + 1 bit per
+// arc, tens of us at 2^21 vertices and 65M arcs) replaced worklists, which
+// every mark paid for: a read of the head's flag, and for a first mark two
+// dependent atomics, the second on the slot's one count.  On a grid with
+// weights 1..4 those counts bounded the round: 57 -> 17 us a round of the
+// two-task kernel; on R-MAT 2^21 (weights 1..100) 708 -> 608 us.
+// tot: this round's totals, zero before the launch.
+constexpr uint32_t SCAN_WORDS = 8;
+constexpr uint32_t BEGIN_T = 1024;  // threads of a block: few blocks, few reservations on the three counters
+template <uint32_t ITEMS>
+__global__ __launch_bounds__(BEGIN_T) void k_round_begin(AdsArgs P, uint32_t D, uint32_t task_arcs, RoundTot *tot,
+                                                     uint32_t *task_u, uint32_t *task_sub, uint32_t *task_slot,
+                                                     uint32_t *split_u, uint32_t *split_first, uint32_t *split_nt,
+                                                     uint64_t *ts) {
+  __shared__ uint32_t wsum[3][BEGIN_T / WAVE];
   __shared__ uint64_t base[3];
+  __shared__ uint32_t s_reach[4];
   const uint32_t lane = (uint32_t)lane_id(), wv = threadIdx.x / WAVE;
-  const uint32_t count = *d_count;
-  constexpr uint32_t TILE = 256 * TB_ITEMS;
-  for (uint64_t b = (uint64_t)blockIdx.x * TILE; b < count; b += (uint64_t)gridDim.x * TILE) {
-    uint32_t u[TB_ITEMS], nt[TB_ITEMS];
+  if (blockIdx.x == 0) {
+    if (ts && threadIdx.x == 0) *ts = wall_clock64();
+    static_assert(CTR_STRIPES == 4 * WAVE, "one stripe per thread of the first four waves");
+    if (wv < 4) {
+      const uint32_t r = wave_max_u32((uint32_t)P.ctr[(size_t)threadIdx.x * CTR_FIELDS + CF_REACH]);
+      if (lane == 0) s_reach[wv] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      *P.reach = max(max(s_reach[0], s_reach[1]), max(s_reach[2], s_reach[3]));
+  }
+  const uint32_t *plane = P.plane + (size_t)(D % P.NS) * P.pw;
+  {
+    uint4 *old = reinterpret_cast<uint4 *>(P.plane + (size_t)((D - 1) % P.NS) * P.pw);  // pw is a multiple of 4
+    const uint64_t nq = P.pw / 4, stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq; i += stride)
+      old[i] = make_uint4(0, 0, 0, 0);
+  }
+  constexpr uint32_t TILE = BEGIN_T * ITEMS;
+  for (uint64_t b = (uint64_t)blockIdx.x * TILE; b < P.n; b += (uint64_t)gridDim.x * TILE) {
+    uint64_t a0[ITEMS], a1[ITEMS];
+    uint32_t nt[ITEMS], any[ITEMS];
     uint32_t c[3] = {0, 0, 0};
 #pragma unroll
-    for (uint32_t j = 0; j < TB_ITEMS; ++j) {
-      const uint64_t i = b + (uint64_t)threadIdx.x * TB_ITEMS + j;
-      u[j] = 0;
-      nt[j] = 0;
-      if (i < count) {
-        u[j] = list[i];
-        const uint64_t d = row_ptr[u[j] + 1] - row_ptr[u[j]];
-        nt[j] = d <= task_arcs ? 1u : (uint32_t)((d + task_arcs - 1) / task_arcs);
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const uint64_t u = b + (uint64_t)j * BEGIN_T + threadIdx.x;
+      a0[j] = u < P.n ? P.row_ptr[u] : 0;
+      a1[j] = u < P.n ? P.row_ptr[u + 1] : 0;
+    }
+    // bits of the row [r0, r1) in its i-th word
+    auto row_bits = [&](uint32_t i, uint64_t r0, uint64_t r1) -> uint32_t {
+      const uint64_t p = ((r0 >> 5) + i) << 5;
+      uint32_t x = plane[(r0 >> 5) + i];
+      if (p < r0) x &= ~0u << (uint32_t)(r0 - p);
+      if (r1 - p < 32) x &= (1u << (uint32_t)(r1 - p)) - 1u;
+      return x;
+    };
+    auto row_words = [&](uint64_t r0, uint64_t r1) -> uint32_t {
+      return r1 > r0 ? (uint32_t)(((r1 - 1) >> 5) - (r0 >> 5)) + 1u : 0u;
+    };
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      any[j] = 0;
+      if (!P.by_arc) {
+        const uint64_t u = b + (uint64_t)j * BEGIN_T + threadIdx.x;
+        any[j] = a1[j] > a0[j] ? (plane[u >> 5] >> (u & 31)) & 1u : 0u;
+      } else {
+        // every lane loads SCAN_WORDS words, its row's last one again past the
+        // row's end: without branches the loads are in flight together
+        const uint32_t nw = row_words(a0[j], a1[j]);
+        const uint32_t last = nw ? nw - 1 : 0u;
+        uint32_t x[SCAN_WORDS];
+#pragma unroll
+        for (uint32_t i = 0; i < SCAN_WORDS; ++i) x[i] = plane[(a0[j] >> 5) + (i < last ? i : last)];
+        const uint32_t mf = ~0u << (uint32_t)(a0[j] & 31), ml = ~0u >> (uint32_t)((32 - (a1[j] & 31)) & 31);
+#pragma unroll
+        for (uint32_t i = 0; i < SCAN_WORDS; ++i) {
+          if (i == 0) x[i] &= mf;
+          if (i == last) x[i] &= ml;
+          if (i <= last) any[j] |= x[i];
+        }
+        if (nw == 0) any[j] = 0;
       }
+    }
+    if (P.by_arc) {
+#pragma unroll
+      for (uint32_t j = 0; j < ITEMS; ++j) {
+        uint64_t lm = __ballot(row_words(a0[j], a1[j]) > SCAN_WORDS);
+        while (lm) {
+          const int o = __ffsll((long long)lm) - 1;
+          lm &= lm - 1;
+          const uint64_t r0 = shfl_u64(a0[j], o), r1 = shfl_u64(a1[j], o);
+          const uint32_t rw = row_words(r0, r1);
+          uint64_t hit = 0;
+          // 8 words per lane and step: an unmarked hub's row is read to its end
+          for (uint32_t i0 = 0; i0 < rw && !hit; i0 += 8 * WAVE) {
+            uint32_t x = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < 8; ++q) {
+              const uint32_t i = i0 + q * WAVE + lane;
+              if (i < rw) x |= row_bits(i, r0, r1);
+            }
+            hit = __ballot(x != 0);
+          }
+          if ((int)lane == o) any[j] = hit != 0;
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const uint64_t d = a1[j] - a0[j];
+      nt[j] = !any[j] ? 0u : d <= task_arcs ? 1u : (uint32_t)((d + task_arcs - 1) / task_arcs);
       c[0] += nt[j];
       c[1] += nt[j] > 1 ? nt[j] : 0u;
       c[2] += nt[j] > 1 ? 1u : 0u;
@@ -1706,8 +1745,10 @@ __global__ __launch_bounds__(256) void k_task_build(const uint32_t *list, const 
     __syncthreads();
     if (threadIdx.x < 3) {
       const uint32_t q = threadIdx.x;
-      const uint32_t t = wsum[q][0] + wsum[q][1] + wsum[q][2] + wsum[q][3];
-      base[q] = t ? atomicAdd((unsigned long long *)&tot[q], (unsigned long long)t) : 0ull;
+      uint32_t t = 0;
+      for (uint32_t w = 0; w < BEGIN_T / WAVE; ++w) t += wsum[q][w];
+      unsigned long long *dst = q == 0 ? &tot->tasks : (q == 1 ? &tot->slots : &tot->splits);
+      base[q] = t ? atomicAdd(dst, (unsigned long long)t) : 0ull;
     }
     __syncthreads();
     uint64_t off[3];
@@ -1719,14 +1760,15 @@ __global__ __launch_bounds__(256) void k_task_build(const uint32_t *list, const 
     }
     __syncthreads();  // wsum and base are rewritten by the next tile
 #pragma unroll
-    for (uint32_t j = 0; j < TB_ITEMS; ++j) {
+    for (uint32_t j = 0; j < ITEMS; ++j) {
+      const uint32_t u = (uint32_t)(b + (uint64_t)j * BEGIN_T + threadIdx.x);
       for (uint32_t t = 0; t < nt[j]; ++t) {
-        task_u[off[0] + t] = u[j];
+        task_u[off[0] + t] = u;
         task_sub[off[0] + t] = t;
         task_slot[off[0] + t] = nt[j] > 1 ? (uint32_t)(off[1] + t) : INF32;
       }
       if (nt[j] > 1) {
-        split_u[off[2]] = u[j];
+        split_u[off[2]] = u;
         split_first[off[2]] = (uint32_t)off[1];
         split_nt[off[2]] = nt[j];
         off[1] += nt[j];
@@ -1734,6 +1776,49 @@ __global__ __launch_bounds__(256) void k_task_build(const uint32_t *list, const 
       }
       off[0] += nt[j];
     }
+  }
+}
+
+// After a round, or a chunk of them: what the host reads back.
+struct RoundInfo {
+  uint64_t examined, commits, reach;  // cumulative counters
+  uint64_t ts;                        // clock at the end
+  uint32_t cap_over, buf_over;        // status bits
+};
+__global__ __launch_bounds__(256) void k_round_end(AdsArgs P, RoundInfo *out) {
+  __shared__ uint64_t s_e[4], s_c[4];
+  __shared__ uint32_t s_r[4];
+  const uint64_t *f = P.ctr + (size_t)threadIdx.x * CTR_FIELDS;
+  const uint64_t e = wave_sum_u64(f[CF_EXAMINED]), c = wave_sum_u64(f[CF_COMMITS]);
+  const uint32_t r = wave_max_u32((uint32_t)f[CF_REACH]);
+  const uint32_t wv = threadIdx.x / WAVE;
+  if (lane_id() == 0) {
+    s_e[wv] = e;
+    s_c[wv] = c;
+    s_r[wv] = r;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *out = RoundInfo{s_e[0] + s_e[1] + s_e[2] + s_e[3], s_c[0] + s_c[1] + s_c[2] + s_c[3],
+                     max(max(s_r[0], s_r[1]), max(s_r[2], s_r[3])), (uint64_t)wall_clock64(), P.status[0],
+                     P.status[1]};
+}
+
+// in-degrees: out[0] scratch slots of the vertices a dense round splits,
+// out[1] the largest (both zero before the launch)
+__global__ __launch_bounds__(256) void k_degrees(uint32_t n, const uint64_t *row_ptr, unsigned long long *out) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  uint64_t slots = 0, mx = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const uint64_t d = row_ptr[i + 1] - row_ptr[i];
+    if (d > TASK_ARCS) slots += (d + TASK_ARCS - 1) / TASK_ARCS;
+    mx = d > mx ? d : mx;
+  }
+  slots = wave_sum_u64(slots);
+  mx = wave_max_u32((uint32_t)mx);  // a simple graph's degree is below n
+  if (lane_id() == 0) {
+    if (slots) atomicAdd(&out[0], (unsigned long long)slots);
+    if (mx) atomicMax(&out[1], (unsigned long long)mx);
   }
 }
 
@@ -1785,19 +1870,6 @@ __global__ void k_reverse_arcs(uint32_t n, uint64_t m, const uint64_t *row_ptr, 
   }
 }
 
-// Work still pending after a round of a chunk (every worklist slot) and the
-// round's task count, for the host's readback at the end of the chunk.
-__global__ void k_round_pending(const uint32_t *wl_cnt, uint32_t NS, const uint64_t *d_ntasks, uint64_t *pend,
-                                uint64_t *tasks) {
-  uint64_t sum = 0;
-  for (uint32_t s = threadIdx.x; s < NS; s += WAVE) sum += wl_cnt[s * CNT_PAD];
-  sum = wave_sum_u64(sum);
-  if (threadIdx.x == 0) {
-    *pend = sum;
-    *tasks = *d_ntasks;
-  }
-}
-
 // list of vertices with at least one in-arc
 __global__ void k_nonisolated_flags(uint32_t n, const uint64_t *row_ptr, uint32_t *flag) {
   uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1807,15 +1879,6 @@ __global__ void k_compact(uint32_t n, const uint32_t *flag, const uint64_t *pos,
   uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n && flag[i]) out[pos[i]] = (uint32_t)i;
 }
-// number of scratch slots a vertex needs when split
-__global__ void k_slot_need(uint32_t n, const uint64_t *row_ptr, uint32_t *need) {
-  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const uint64_t d = row_ptr[i + 1] - row_ptr[i];
-    need[i] = d > TASK_ARCS ? (uint32_t)((d + TASK_ARCS - 1) / TASK_ARCS) : 0u;
-  }
-}
-
 // Compact the per-vertex sketches into CSR (one wave per vertex).
 __global__ __launch_bounds__(256) void k_ads_export(uint32_t n, uint32_t cap, const uint32_t *cnt,
                                                     const uint64_t *off, const uint32_t *sk_rank,
@@ -1845,19 +1908,16 @@ uint32_t ads_capacity(uint32_t n, uint32_t k) {
 }
 
 size_t ads_scratch_bytes(uint32_t n, uint64_t m, uint32_t k, uint32_t NS) {
-  const size_t FW = (NS + 31) / 32;
   const uint64_t slots = 2 * (m / TASK_ARCS) + 2;  // >= sum of ceil(deg/TASK_ARCS) over vertices with deg > TASK_ARCS
   const uint64_t tasks = (uint64_t)n + m / TASK_ARCS + 64;
   size_t b = 0;
   b += (size_t)n * k * 4;                  // bottom-k sets
-  b += (size_t)NS * n * (16 + 4);          // per-slot level records + worklists
-  b += (size_t)m * 4 + (size_t)NS * (m / 32 + 2) * 4;  // reverse-arc positions, arc bit planes
-  b += (size_t)n * FW * 4;                 // worklist flags
-  b += (size_t)NS * CNT_PAD * 4;           // worklist lengths, one per line
+  b += (size_t)NS * n * 16;                // per-slot level records
+  b += (size_t)m * 4 + (size_t)NS * (m / 32 + n / 32 + 8) * 4;  // reverse-arc positions, planes (arcs or vertices)
   b += (size_t)slots * (ADS_SB * (k > 64 ? 2 : 1) + 1) * 4;   // kept sets of split tasks
   b += (size_t)tasks * 4 * 3 * 2 + (size_t)n * 4 * 3 * 2;  // two task lists
   b += (size_t)n * (4 * 3 + 8 * 3) + (size_t)n * 24;       // task scratch, dense list
-  b += (size_t)tasks;                      // tasks left by the two-task kernel
+  b += (size_t)tasks * 4;                  // tasks left by the two-task kernel
   b += (size_t)8 << 20;
   return b;
 }
@@ -1868,11 +1928,11 @@ size_t ads_scratch_bytes(uint32_t n, uint64_t m, uint32_t k, uint32_t NS) {
 // set registers of k and the survivor buffer of the build.
 static void launch_tasks(hipStream_t s, uint32_t grid, bool unit, uint32_t k, uint32_t sb, const AdsArgs &P,
                          uint32_t D, const uint32_t *tu, const uint32_t *tsub, const uint32_t *tslot, uint32_t nt,
-                         const uint64_t *dnt, uint32_t task_arcs, int sparse, int mark,
-                         const uint8_t *only = nullptr) {
+                         const RoundTot *tot, uint32_t task_arcs, int sparse, int mark, const uint32_t *left,
+                         uint64_t *ts) {
 #define FL_TASKS(U, K, S)                                                                                          \
-  k_ads_tasks<U, K, S><<<grid, TASK_WPB * WAVE, 0, s>>>(P, D, tu, tsub, tslot, nt, dnt, task_arcs, sparse, mark, \
-                                                        only)
+  k_ads_tasks<U, K, S><<<grid, TASK_WPB * WAVE, 0, s>>>(P, D, tu, tsub, tslot, nt, tot, task_arcs, sparse, mark, \
+                                                        left, ts)
   if (k > 64) {
     if (unit) FL_TASKS(true, 2, 2 * ADS_SB);
     else FL_TASKS(false, 2, 2 * ADS_SB);
@@ -1887,9 +1947,9 @@ static void launch_tasks(hipStream_t s, uint32_t grid, bool unit, uint32_t k, ui
 }
 static void launch_merge(hipStream_t s, uint32_t grid, bool unit, uint32_t k, uint32_t sb, const AdsArgs &P,
                          uint32_t D, const uint32_t *su, const uint32_t *sfirst, const uint32_t *snt, uint32_t ns,
-                         const uint64_t *dns, int mark) {
+                         const RoundTot *tot, int mark, uint64_t *ts) {
 #define FL_MERGE(U, K, S) \
-  k_ads_merge<U, K, S><<<grid, MERGE_WPB * WAVE, 0, s>>>(P, D, su, sfirst, snt, ns, dns, mark)
+  k_ads_merge<U, K, S><<<grid, MERGE_WPB * WAVE, 0, s>>>(P, D, su, sfirst, snt, ns, tot, mark, ts)
   if (k > 64) {
     if (unit) FL_MERGE(true, 2, 2 * ADS_SB);
     else FL_MERGE(false, 2, 2 * ADS_SB);
@@ -1910,7 +1970,6 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
   const uint32_t n = g.n, k = cfg.k, cap = o.cap;
   const uint32_t W = g.w ? g.max_w : 1u;
   const uint32_t NS = W + 1;
-  const uint32_t FW = (NS + 31) / 32;
   const bool unit = g.w == nullptr;
   *need_more = false;
   *buf_over = false;
@@ -1922,7 +1981,6 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
   P.cap = cap;
   P.W = W;
   P.NS = NS;
-  P.FW = FW;
   P.gid = cfg.gid;
   P.seg = cfg.seg;
   P.row_ptr = g.in_ptr;
@@ -1936,24 +1994,17 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
   P.bk = c.arena->get<uint32_t>((size_t)n * k);
   P.cnt = o.cnt;
   P.lvl = c.arena->get<uint4>((size_t)NS * n);
-  P.flags = c.arena->get<uint32_t>((size_t)n * FW);
-  P.wl = c.arena->get<uint32_t>((size_t)NS * n);
-  P.wl_cnt = c.arena->get<uint32_t>((size_t)NS * CNT_PAD);
   P.ctr = c.arena->get<uint64_t>((size_t)CTR_STRIPES * CTR_FIELDS);
   P.dbg = std::getenv("FL_DEBUG") ? 1u : 0u;
-  P.status = c.arena->get<uint32_t>(4);
   P.thr = o.thr;
   P.thr_idx = o.thr ? cfg.thr_idx : nullptr;
-  // arc bit planes for the rounds run from worklists (arc positions must fit 32 bits)
-  const bool planes = g.m > 0 && g.m < 0xFFFFFFFFull;
-  P.plane = nullptr;
-  P.pw = g.m / 32 + 2;
+  // marks by arc where arc positions fit 32 bits, by vertex otherwise
+  P.by_arc = g.m < 0xFFFFFFFFull ? 1u : 0u;
+  P.pw = (((P.by_arc ? g.m : (uint64_t)n) / 32 + 2) + 3) & ~3ull;
+  P.plane = c.arena->get<uint32_t>((size_t)NS * P.pw);
+  fill_u32(c, P.plane, (size_t)NS * P.pw, 0);
   P.out_to_in = nullptr;
-  P.flag_from = FLAG_FROM_RINGS * NS;
-  P.plane_from = P.flag_from > W ? P.flag_from - W : 0;
-  if (planes) {
-    P.plane = c.arena->get<uint32_t>((size_t)NS * P.pw);
-    fill_u32(c, P.plane, (size_t)NS * P.pw, 0);
+  if (P.by_arc && g.m) {
     if (g.out_to_in) {
       P.out_to_in = g.out_to_in;
     } else {
@@ -1965,21 +2016,39 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     }
   }
   fill_u64(c, reinterpret_cast<uint64_t *>(P.lvl), (size_t)NS * n * 2, INF64);  // no level anywhere
-  fill_u32(c, P.flags, (size_t)n * FW, 0);
-  fill_u32(c, P.wl_cnt, (size_t)NS * CNT_PAD, 0);
+  // small device state of the rounds, zeroed together: counters, status, the
+  // totals of a chunk's rounds, clocks, what the host reads back
+  constexpr uint32_t RCHUNK = 16;
+  struct RoundState {
+    RoundTot tot[RCHUNK];
+    uint64_t ts[RCHUNK][3];  // clocks at the start of a round, of its kernels, of its merge
+    RoundInfo info;
+    uint64_t deg[2];
+    uint32_t status[2], reach, pad;
+  };
+  RoundState *rs = c.arena->get<RoundState>(1);
   fill_u64(c, P.ctr, (size_t)CTR_STRIPES * CTR_FIELDS, 0);
-  fill_u32(c, P.status, 4, 0);
+  fill_u32(c, reinterpret_cast<uint32_t *>(rs), sizeof(RoundState) / 4, 0);
+  P.status = rs->status;
+  P.reach = &rs->reach;
+  // Round 0 marks every arc: the farthest mark is the largest weight.  With
+  // the dense list the rounds end when nothing changed; the reach is not kept
+  // (no mark exceeds INF32).
+  const bool dense_ok = unit && !(cfg.flags & FL_FLAG_NO_DENSE);
+  if (g.m) {
+    fill_u64(c, P.ctr + CF_REACH, 1, dense_ok ? INF32 : W);
+    fill_u32(c, P.reach, 1, dense_ok ? INF32 : W);
+  }
 
   // scratch slots: enough for every vertex split at once
+  uint64_t max_deg = 0;
   {
-    uint32_t *need = c.arena->get<uint32_t>(n);
-    uint64_t *noff = c.arena->get<uint64_t>((size_t)n + 1);
-    k_slot_need<<<(uint32_t)ceil_div(n, 256), 256, 0, c.s>>>(n, g.in_ptr, need);
+    k_degrees<<<(uint32_t)std::min<uint64_t>(ceil_div(n, 256), 1024), 256, 0, c.s>>>(
+        n, g.in_ptr, reinterpret_cast<unsigned long long *>(rs->deg));
     FL_LAUNCH_CHECK();
-    scan_u32_to_u64(c, need, noff, n);
-    FL_HIP(hipMemcpyAsync(c.h_status, noff + n, 8, hipMemcpyDeviceToHost, c.s));
-    c.sync();
+    c.fetch(rs->deg, sizeof(rs->deg));
     const uint64_t slots = c.h_status[0] + 1;
+    max_deg = c.h_status[1];
     P.kept = c.arena->get<uint32_t>(slots * sb);
     P.kept_cnt = c.arena->get<uint32_t>(slots);
   }
@@ -2005,7 +2074,6 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
 
   // dense list: vertices with at least one arc, and its static task list
   uint32_t n_dense = 0;
-  const bool dense_ok = unit && !(cfg.flags & FL_FLAG_NO_DENSE);
   if (dense_ok) {
     uint32_t *fl = c.arena->get<uint32_t>(n);
     uint64_t *pos = c.arena->get<uint64_t>((size_t)n + 1);
@@ -2021,7 +2089,7 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     alloc_list(tl_dense);
     build_tasks(c, g, dense, n_dense, TASK_ARCS, ts, tl_dense);
   }
-  // a round marks (so that the next one runs on worklists) once the previous
+  // a round marks (so that the next one runs from marks) once the previous
   // round changed at most a quarter of the dense list
   const uint64_t dense_threshold = (uint64_t)n_dense / 4;
 
@@ -2034,226 +2102,156 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     FL_LAUNCH_CHECK();
   }
   bool sparse = mark;  // mode of round 1
-  hipEvent_t e0 = nullptr, em = nullptr, e1 = nullptr;
-  if (c.timing) {
-    FL_HIP(hipEventCreate(&e0));
-    FL_HIP(hipEventCreate(&em));
-    FL_HIP(hipEventCreate(&e1));
-  }
-  struct EvDel {
-    hipEvent_t a, b, c;
-    ~EvDel() {
-      if (a) (void)hipEventDestroy(a);
-      if (b) (void)hipEventDestroy(b);
-      if (c) (void)hipEventDestroy(c);
-    }
-  } evdel{e0, em, e1};
   o.kernel_ms = 0.0;
   o.merge_ms = 0.0;
   o.launches = 0;
-  uint64_t active_prev = n;
-  uint64_t commits_prev = 0;  // commits counted before this round
-  std::vector<uint64_t> hctr((size_t)CTR_STRIPES * CTR_FIELDS);
+  double ms_per_tick = 0.0;  // of the clock the kernels read
+  if (c.timing) {
+    int dev = 0, khz = 0;
+    FL_HIP(hipGetDevice(&dev));
+    FL_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+    ms_per_tick = khz > 0 ? 1.0 / khz : 0.0;
+  }
+  const bool pairs = k <= HALF && !dense_ok;  // the set of a level fits one half of a wave
+  const uint32_t sparse_arcs = P.by_arc ? TASK_ARCS_FLAGGED : TASK_ARCS_SPARSE;
+  const bool splits = max_deg > sparse_arcs;  // some row is split in rounds run from marks
+  const uint32_t GT = (uint32_t)std::min<uint64_t>(max_tasks, 65536);  // one-wave blocks striding over tasks
+  const uint32_t GL = (uint32_t)std::min<uint64_t>(max_tasks, 8192);   // the same over the tasks left
+  const uint32_t GM = (uint32_t)std::min<uint64_t>(n, 2048);           // merge blocks striding over hubs
+  const uint32_t GP = (uint32_t)std::min<uint64_t>(ceil_div(max_tasks, 2), 65536);  // two-task waves
+  uint32_t *left = pairs ? c.arena->get<uint32_t>(max_tasks) : nullptr;
+  // one round run from marks; r: its place in the chunk
+  auto sparse_round = [&](uint32_t D, uint32_t r, int marks) {
+    RoundTot *tot = &rs->tot[r];
+    uint64_t *ts = c.timing ? rs->ts[r] : nullptr;
+    auto tsp = [&](int i) { return ts ? ts + i : nullptr; };
+#define FL_BEGIN(ITEMS)                                                                                       \
+  k_round_begin<ITEMS><<<(uint32_t)std::min<uint64_t>(ceil_div(n, BEGIN_T * ITEMS), 512), BEGIN_T, 0, c.s>>>( \
+      P, D, sparse_arcs, tot, tl.task_u, tl.task_sub, tl.task_slot, tl.split_u, tl.split_first, tl.split_nt, \
+      tsp(0))
+    if (n >= (1u << 18)) FL_BEGIN(4);
+    else FL_BEGIN(1);
+#undef FL_BEGIN
+    FL_LAUNCH_CHECK();
+    if (pairs) {
+      // k <= 32: two small tasks per wave first, then the one-wave kernel on the rest
+      if (unit)
+        k_ads_pairs<true><<<GP, WAVE, 0, c.s>>>(P, D, tl.task_u, tl.task_sub, tl.task_slot, tot, left, tsp(1));
+      else
+        k_ads_pairs<false><<<GP, WAVE, 0, c.s>>>(P, D, tl.task_u, tl.task_sub, tl.task_slot, tot, left, tsp(1));
+      FL_LAUNCH_CHECK();
+    }
+    launch_tasks(c.s, pairs ? GL : GT, unit, k, sb, P, D, tl.task_u, tl.task_sub, tl.task_slot, 0, tot, sparse_arcs, 1,
+                 marks, left, pairs ? nullptr : tsp(1));
+    FL_LAUNCH_CHECK();
+    if (splits) {
+      launch_merge(c.s, GM, unit, k, sb, P, D, tl.split_u, tl.split_first, tl.split_nt, 0, tot, marks, tsp(2));
+      FL_LAUNCH_CHECK();
+    }
+  };
+  // host copy of the rounds' state (waits)
+  std::vector<uint64_t> hbuf(sizeof(RoundState) / 8);
+  const RoundState &h = *reinterpret_cast<const RoundState *>(hbuf.data());
+  auto round_end = [&]() {
+    k_round_end<<<1, CTR_STRIPES, 0, c.s>>>(P, &rs->info);
+    FL_LAUNCH_CHECK();
+    c.fetch(rs, sizeof(RoundState));
+    std::memcpy(hbuf.data(), c.h_status, sizeof(RoundState));
+  };
+  // device time of round r's kernels and merge (next: clock at the next start)
+  auto add_times = [&](uint32_t r, uint64_t next, bool merged) {
+    o.launches += 1;
+    if (!c.timing) return;
+    const uint64_t kend = merged ? h.ts[r][2] : next;
+    o.kernel_ms += (double)(kend - h.ts[r][1]) * ms_per_tick;
+    if (merged) o.merge_ms += (double)(next - kend) * ms_per_tick;
+  };
+  static_assert(sizeof(RoundState) <= 4096 * 8, "fits the host status words");
   uint32_t rounds = 0;
-  std::vector<uint32_t> hwl(NS);
-  bool hwl_valid = false;  // hwl holds the slot counts read back after the previous round
   if (!dense_ok) {
-    // Every round runs from worklists.  Rounds are launched RCHUNK at a time
-    // with their task lists built on the device (no count goes to the host
-    // in between); the round kernels stride over the device-side totals.
-    // The host reads back, once per chunk, the work pending after each of
-    // its rounds; rounds after the first with nothing pending find empty
-    // worklists and change nothing.
-    constexpr uint32_t RCHUNK = 16;
-    uint64_t *pend = c.arena->get<uint64_t>(2 * RCHUNK);  // [r] pending after round r, [RCHUNK + r] its tasks
-    std::vector<hipEvent_t> ev(c.timing ? 3 * RCHUNK : 0, nullptr);
-    struct EvVecDel {
-      std::vector<hipEvent_t> &v;
-      ~EvVecDel() {
-        for (hipEvent_t e : v)
-          if (e) (void)hipEventDestroy(e);
-      }
-    } evvd{ev};
-    for (auto &e : ev) FL_HIP(hipEventCreate(&e));
-    const uint32_t GT = (uint32_t)std::min<uint64_t>(max_tasks, 65536);  // one-wave blocks striding over tasks
-    const uint32_t GM = (uint32_t)std::min<uint64_t>(n, 2048);           // merge blocks striding over hubs
-    const uint32_t TB = (uint32_t)std::min<uint64_t>(ceil_div(n, 256 * TB_ITEMS), 1024);  // task-list blocks
-    const bool pairs = k <= HALF;  // the set of a level fits one half of a wave
-    const uint32_t GP = (uint32_t)std::min<uint64_t>(ceil_div(max_tasks, 2), 65536);  // two-task waves
-    uint8_t *pend_task = pairs ? c.arena->get<uint8_t>(max_tasks) : nullptr;
-    uint64_t *tot = c.arena->get<uint64_t>(3);
-    const uint64_t *d_ntasks = tot, *d_nsplit = tot + 2;
+    // Every round runs from marks.  Rounds are launched RCHUNK at a time
+    // with their task lists built on the device (nothing goes to the host in
+    // between); the round kernels stride over the device-side totals.  Rounds
+    // after the last one with a mark find no task and change nothing.
     for (uint32_t D0 = 1;; D0 += RCHUNK) {
-      for (uint32_t r = 0; r < RCHUNK; ++r) {
-        const uint32_t D = D0 + r;
-        const uint32_t slot = D % NS;
-        const uint32_t task_arcs = (P.plane && D >= P.flag_from) ? TASK_ARCS_FLAGGED : TASK_ARCS_SPARSE;
-        fill_u64(c, tot, 3, 0);
-        k_task_build<<<TB, 256, 0, c.s>>>(P.wl + (size_t)slot * n, P.wl_cnt + (size_t)slot * CNT_PAD, g.in_ptr, task_arcs, tot,
-                                          tl.task_u, tl.task_sub, tl.task_slot, tl.split_u, tl.split_first,
-                                          tl.split_nt);
-        FL_LAUNCH_CHECK();
-        if (c.timing) FL_HIP(hipEventRecord(ev[3 * r], c.s));
-        if (pairs) {
-          // k <= 32: two small tasks per wave first, then the one-wave kernel on the rest
-          if (unit)
-            k_ads_pairs<true><<<GP, WAVE, 0, c.s>>>(P, D, tl.task_u, tl.task_sub, tl.task_slot, d_ntasks, pend_task);
-          else
-            k_ads_pairs<false><<<GP, WAVE, 0, c.s>>>(P, D, tl.task_u, tl.task_sub, tl.task_slot, d_ntasks, pend_task);
-          FL_LAUNCH_CHECK();
-        }
-        launch_tasks(c.s, GT, unit, k, sb, P, D, tl.task_u, tl.task_sub, tl.task_slot, 0, d_ntasks, task_arcs, 1,
-                     1, pairs ? pend_task : nullptr);
-        FL_LAUNCH_CHECK();
-        if (c.timing) FL_HIP(hipEventRecord(ev[3 * r + 1], c.s));
-        launch_merge(c.s, GM, unit, k, sb, P, D, tl.split_u, tl.split_first, tl.split_nt, 0, d_nsplit, 1);
-        FL_LAUNCH_CHECK();
-        if (c.timing) FL_HIP(hipEventRecord(ev[3 * r + 2], c.s));
-        fill_u32(c, P.wl_cnt + (size_t)slot * CNT_PAD, 1, 0);
-        if (P.plane) fill_u32(c, P.plane + (size_t)slot * P.pw, P.pw, 0);
-        k_round_pending<<<1, WAVE, 0, c.s>>>(P.wl_cnt, NS, d_ntasks, pend + r, pend + RCHUNK + r);
-        FL_LAUNCH_CHECK();
-      }
-      std::vector<uint64_t> hp(2 * RCHUNK);
-      FL_HIP(hipMemcpyAsync(c.h_status, P.status, 8, hipMemcpyDeviceToHost, c.s));
-      FL_HIP(hipMemcpyAsync(hp.data(), pend, 2 * RCHUNK * 8, hipMemcpyDeviceToHost, c.s));
-      c.sync();
-      const uint32_t st0 = (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-      const uint32_t st1 = (uint32_t)(c.h_status[0] >> 32);
-      if (st0) {
+      if (D0 > 1) fill_u32(c, reinterpret_cast<uint32_t *>(rs->tot), sizeof(rs->tot) / 4, 0);
+      for (uint32_t r = 0; r < RCHUNK; ++r) sparse_round(D0 + r, r, 1);
+      round_end();
+      if (h.info.cap_over) {
         *need_more = true;
         return FL_OK;
       }
-      if (st1) {
+      if (h.info.buf_over) {
         *buf_over = true;
         return FL_OK;
       }
-      uint32_t used = RCHUNK;
-      bool done = false;
-      for (uint32_t r = 0; r < RCHUNK; ++r)
-        if (hp[r] == 0) {
-          used = r + 1;
-          done = true;
-          break;
-        }
       // every round of the chunk launched the round kernel (those past the
       // last one with work exit at once): all are counted and timed, as a
       // kernel trace sees them
       for (uint32_t r = 0; r < RCHUNK; ++r) {
-        o.launches += 1;
-        if (c.timing) {
-          float ms = 0.f, ms2 = 0.f;
-          FL_HIP(hipEventElapsedTime(&ms, ev[3 * r], ev[3 * r + 1]));
-          FL_HIP(hipEventElapsedTime(&ms2, ev[3 * r + 1], ev[3 * r + 2]));
-          o.kernel_ms += ms;
-          o.merge_ms += ms2;
-        }
+        add_times(r, r + 1 < RCHUNK ? h.ts[r + 1][0] : h.info.ts, splits);
+        if (h.tot[r].tasks) rounds = D0 + r;  // every vertex with a mark makes a task
       }
-      rounds = D0 + used - 1;
+      if (rounds == 0) rounds = 1;
       if (std::getenv("FL_DEBUG"))
-        std::fprintf(stderr, "[fl] rounds %u-%u: tasks of the first %llu, pending after the last %llu\n", D0,
-                     D0 + used - 1, (unsigned long long)hp[RCHUNK], (unsigned long long)hp[used - 1]);
-      if (done) break;
+        std::fprintf(stderr, "[fl] rounds %u-%u: tasks of the first %llu, left to the one-wave kernel %llu, reach %llu\n",
+                     D0, D0 + RCHUNK - 1, h.tot[0].tasks, h.tot[0].left, (unsigned long long)h.info.reach);
+      if (h.info.reach < (uint64_t)D0 + RCHUNK) break;  // no mark beyond this chunk
       // a settled entry is at most (n-1) max_w away: more rounds mean a bug
       if ((uint64_t)D0 + RCHUNK > (uint64_t)(n - 1) * W + 2 + RCHUNK) return FL_EHIP;
     }
   }
+  uint64_t active_prev = n;
+  uint64_t commits_prev = 0;  // commits counted before this round
+  bool was_sparse = false;
   for (uint32_t D = 1; dense_ok; ++D) {
-    const uint32_t slot = D % NS;
-    const TaskList *T = &tl_dense;
-    if (sparse) {
-      // slot D is filled by rounds before D, so the previous readback is exact
-      uint32_t count = hwl[slot];
-      if (!hwl_valid) {
-        FL_HIP(hipMemcpyAsync(c.h_status, P.wl_cnt + (size_t)slot * CNT_PAD, 4, hipMemcpyDeviceToHost, c.s));
-        c.sync();
-        count = (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-      }
-      build_tasks(c, g, P.wl + (size_t)slot * n, count,
-                  (P.plane && D >= P.flag_from) ? TASK_ARCS_FLAGGED : TASK_ARCS_SPARSE, ts, tl);
-      T = &tl;
-    }
     // marking decision for this round (decides the mode of the next one)
-    mark = !dense_ok || active_prev <= dense_threshold;
-    if (T->ntasks) {
-      if (c.timing) FL_HIP(hipEventRecord(e0, c.s));
-      const uint32_t tb = (uint32_t)ceil_div(T->ntasks, TASK_WPB);
-      launch_tasks(c.s, tb, unit, k, sb, P, D, T->task_u, T->task_sub, T->task_slot, T->ntasks, nullptr,
-                   T->task_arcs, sparse ? 1 : 0, mark ? 1 : 0);
+    mark = active_prev <= dense_threshold;
+    bool merged = sparse && splits;
+    if (sparse) {
+      fill_u32(c, reinterpret_cast<uint32_t *>(rs->tot), sizeof(RoundTot) / 4, 0);
+      sparse_round(D, 0, mark ? 1 : 0);
+    } else if (tl_dense.ntasks) {
+      const TaskList &T = tl_dense;
+      // the marks of a round run from them, which this round's may join
+      if (was_sparse) fill_u32(c, P.plane + (size_t)((D - 1) % NS) * P.pw, P.pw, 0);
+      launch_tasks(c.s, (uint32_t)ceil_div(T.ntasks, TASK_WPB), unit, k, sb, P, D, T.task_u, T.task_sub, T.task_slot,
+                   T.ntasks, nullptr, T.task_arcs, 0, mark ? 1 : 0, nullptr, c.timing ? &rs->ts[0][1] : nullptr);
       FL_LAUNCH_CHECK();
-      if (c.timing) FL_HIP(hipEventRecord(em, c.s));
-      if (T->nsplit) {
-        const uint32_t mb = T->nsplit;  // one block of MERGE_WPB waves per split vertex
-        launch_merge(c.s, mb, unit, k, sb, P, D, T->split_u, T->split_first, T->split_nt, T->nsplit, nullptr,
-                     mark ? 1 : 0);
+      if (T.nsplit) {
+        merged = true;
+        // one block of MERGE_WPB waves per split vertex
+        launch_merge(c.s, T.nsplit, unit, k, sb, P, D, T.split_u, T.split_first, T.split_nt, T.nsplit, nullptr,
+                     mark ? 1 : 0, c.timing ? &rs->ts[0][2] : nullptr);
         FL_LAUNCH_CHECK();
       }
-      if (c.timing) FL_HIP(hipEventRecord(e1, c.s));
     }
-    if (sparse) fill_u32(c, P.wl_cnt + (size_t)slot * CNT_PAD, 1, 0);
-    // the plane of this round is read; commits of later rounds refill it
-    if (P.plane) fill_u32(c, P.plane + (size_t)slot * P.pw, P.pw, 0);
     ++rounds;
-    FL_HIP(hipMemcpyAsync(c.h_status, P.status, 8, hipMemcpyDeviceToHost, c.s));
-    FL_HIP(hipMemcpyAsync(hctr.data(), P.ctr, hctr.size() * 8, hipMemcpyDeviceToHost, c.s));
-    fetch_padded(c, hwl.data(), P.wl_cnt, NS);  // waits for both
-    hwl_valid = true;
-    if (T->ntasks) {
-      float ms = 0.f, ms2 = 0.f;
-      if (c.timing) {
-        FL_HIP(hipEventElapsedTime(&ms, e0, em));
-        FL_HIP(hipEventElapsedTime(&ms2, em, e1));
-      }
-      o.kernel_ms += ms;
-      o.merge_ms += ms2;
-      o.launches += 1;
-      if (std::getenv("FL_DEBUG")) {
-        std::vector<uint64_t> hs((size_t)CTR_STRIPES * CTR_FIELDS), f(CF_COUNT, 0);
-        FL_HIP(hipMemcpy(hs.data(), P.ctr, hs.size() * 8, hipMemcpyDeviceToHost));
-        for (uint32_t i = 0; i < CTR_STRIPES; ++i)
-          for (uint32_t q = 0; q < CF_COUNT; ++q) f[q] += hs[(size_t)i * CTR_FIELDS + q];
-        const uint64_t ex = f[CF_EXAMINED], sv = f[CF_SURVIVORS], pr = f[CF_PRUNES], sc = f[CF_SCANNED],
-                       mt = f[CF_MATCHED], ma = f[CF_MARK_ARCS], mp = f[CF_MARKED];
-        const uint64_t act = f[CF_COMMITS] - commits_prev;
-        std::fprintf(stderr, "[fl] round %u: %s, %u tasks, %u split, %llu changed, %.2f ms, merge %.2f ms, "
-                     "examined(cum) %.3fG survivors(cum) %.3fG prunes(cum) %.3fM scanned(cum) %.3fG "
-                     "matched(cum) %.3fG markarcs(cum) %.3fG marked(cum) %.3fG\n",
-                     D, sparse ? "sparse" : "dense", T->ntasks, T->nsplit, (unsigned long long)act, ms, ms2,
-                     ex / 1e9, sv / 1e9, pr / 1e6, sc / 1e9, mt / 1e9, ma / 1e9, mp / 1e9);
-      }
-    }
-    const uint32_t st0 = (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-    const uint32_t st1 = (uint32_t)(c.h_status[0] >> 32);
-    if (st0) {
+    round_end();
+    if (h.info.cap_over) {
       *need_more = true;
       return FL_OK;
     }
-    if (st1) {
+    if (h.info.buf_over) {
       *buf_over = true;
       return FL_OK;
     }
-    uint64_t commits = 0;
-    for (uint32_t i = 0; i < CTR_STRIPES; ++i) commits += hctr[(size_t)i * CTR_FIELDS + CF_COMMITS];
-    const uint64_t active = commits - commits_prev;  // vertices that changed this round
-    commits_prev = commits;
-    uint64_t pending = 0;
-    for (uint32_t s = 0; s < NS; ++s) pending += hwl[s];
-    if (unit) {
-      if (active == 0) break;
-    } else {
-      if (pending == 0) break;
-    }
+    if (sparse ? h.tot[0].tasks != 0 : tl_dense.ntasks != 0) add_times(0, h.info.ts, merged);
+    const uint64_t active = h.info.commits - commits_prev;  // vertices that changed this round
+    commits_prev = h.info.commits;
+    if (std::getenv("FL_DEBUG"))
+      std::fprintf(stderr, "[fl] round %u: %s, %llu tasks, %llu changed, examined(cum) %.3fG\n", D,
+                   sparse ? "sparse" : "dense", sparse ? h.tot[0].tasks : (unsigned long long)tl_dense.ntasks,
+                   (unsigned long long)active, h.info.examined / 1e9);
+    if (active == 0) break;
     active_prev = active;
+    was_sparse = sparse;
     sparse = mark;
     // a settled entry is at most (n-1) max_w away: more rounds mean a bug
     if ((uint64_t)D > (uint64_t)(n - 1) * W + 2) return FL_EHIP;
   }
   o.rounds = rounds;
-  std::vector<uint64_t> hc((size_t)CTR_STRIPES * CTR_FIELDS);
-  FL_HIP(hipMemcpyAsync(hc.data(), P.ctr, hc.size() * 8, hipMemcpyDeviceToHost, c.s));
-  c.sync();
-  o.relax_exec = 0;
-  for (uint32_t i = 0; i < CTR_STRIPES; ++i) o.relax_exec += hc[(size_t)i * CTR_FIELDS + CF_EXAMINED];
+  o.relax_exec = h.info.examined;
   return FL_OK;
 }
 
