@@ -384,6 +384,11 @@ __device__ inline uint32_t kset_below(const KSet<KR> &s, uint32_t r) {
   return q == 64u ? 64u + q2 : q;
 }
 
+// Chunks with more candidates than this left are compared bit by bit: some
+// 140 instructions, and the accepted ranks come out in order; comparing all
+// pairs takes 13 per 4 candidates and a sort of the accepted ones after it.
+constexpr int CHUNK_SLICED = 24;
+
 // One chunk of candidates, one id per lane in ascending lane order (INF32 =
 // empty slot at the end); duplicates are adjacent; `prev` is the last id of
 // the previous chunk of this level.  Candidate i is accepted iff
@@ -403,36 +408,78 @@ __device__ inline uint64_t chunk_accept(uint32_t id, uint32_t k, const RankMap &
   // not new; one that dropped out of the set is rejected by the count
   const uint32_t atq = kset_at(set, q < 64u * KR - 1u ? q : 64u * KR - 1u);
   if (q < nset && atq == r) valid = false;
+  // one with k set elements below it is rejected, and so is any it could count
+  // for: only those below the set's k-th rank remain
+  if (q >= k) valid = false;
   const uint64_t vm = __ballot(valid);
-  // earlier candidates of the chunk with a smaller rank: ranks staged in LDS,
-  // read four at a time by every lane from the same address (broadcast)
-  s_r[lane] = valid ? r : INF32;
-  wave_lds_sync();
-  const int top = vm ? 64 - __clzll(vm) : 0;  // lanes above the last valid one are empty
-  uint32_t cp = 0;
-  for (int j4 = 0; j4 < top; j4 += 4) {
-    const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[j4]);
-    cp += (j4 + 0 < lane && v.x < r) ? 1u : 0u;
-    cp += (j4 + 1 < lane && v.y < r) ? 1u : 0u;
-    cp += (j4 + 2 < lane && v.z < r) ? 1u : 0u;
-    cp += (j4 + 3 < lane && v.w < r) ? 1u : 0u;
-  }
-  wave_lds_sync();
-  const bool acc = valid && q + cp < k;
-  const uint64_t am = __ballot(acc);
-  // the running set becomes the k smallest of (set, accepted ranks); rejected
-  // candidates have k smaller ranks before them and never enter it
-  const uint32_t na = (uint32_t)__popcll(am);
-  if (na <= 8) {
-    uint64_t it2 = am;
-    while (it2) {
-      const int j = __ffsll((long long)it2) - 1;
-      it2 &= it2 - 1;
-      const uint32_t rj = __shfl(r, j, WAVE);
-      kset_insert(set, rj, kset_ballot_below(set, rj), k);
+  bool acc;
+  uint64_t am;
+  uint32_t na;
+  if (__popcll(vm) > CHUNK_SLICED) {
+    // lt: the lanes with a smaller rank, found by comparing bit by bit from
+    // the highest that can differ.  eq holds the lanes equal so far; a ballot
+    // of each bit splits it.  Ranks are distinct, so it ends when every eq is
+    // a single lane, after some 13 bits for 64 random ranks.
+    const uint32_t kth = nset < k ? INF32 : __builtin_amdgcn_readfirstlane(kset_at(set, k - 1));
+    uint32_t el = valid ? (uint32_t)vm : 0u, eh = valid ? (uint32_t)(vm >> 32) : 0u, ll = 0, lh = 0;
+    for (int b = 31 - (kth ? __clz(kth) : 31); b >= 0; b -= 4) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        if (b < d) break;
+        const uint32_t bm = (uint32_t)__builtin_amdgcn_sbfe((int)r, (uint32_t)(b - d), 1u);
+        const uint64_t B = __ballot(bm != 0);
+        const uint32_t bl = (uint32_t)B, bh = (uint32_t)(B >> 32);
+        ll |= el & ~bl & bm;
+        lh |= eh & ~bh & bm;
+        el &= ~(bl ^ bm);
+        eh &= ~(bh ^ bm);
+      }
+      if (!__ballot((el & (el - 1)) | (eh & (eh - 1)) | (el && eh ? 1u : 0u))) break;
+    }
+    const uint64_t lt = ((uint64_t)lh << 32) | ll;
+    const uint32_t cp = lanes_below(lt);
+    acc = valid && q + cp < k;
+    am = __ballot(acc);
+    na = (uint32_t)__popcll(am);
+    if (na) {
+      // the accepted ranks ascending: each lane knows its place
+      if (acc) s_r[__popcll(lt & am)] = r;
+      wave_lds_sync();
+      const uint32_t x = (uint32_t)lane < na ? s_r[lane] : INF32;
+      wave_lds_sync();
+      kset_merge(set, x, k);
     }
   } else {
-    kset_merge(set, wave_sort_reg(acc ? r : INF32), k);
+    // few: the ranks staged in LDS, read four at a time by every lane from the
+    // same address (broadcast)
+    s_r[lane] = valid ? r : INF32;
+    wave_lds_sync();
+    const int top = vm ? 64 - __clzll(vm) : 0;  // lanes above the last valid one are empty
+    uint32_t cp = 0;
+    for (int j4 = 0; j4 < top; j4 += 4) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[j4]);
+      cp += (j4 + 0 < lane && v.x < r) ? 1u : 0u;
+      cp += (j4 + 1 < lane && v.y < r) ? 1u : 0u;
+      cp += (j4 + 2 < lane && v.z < r) ? 1u : 0u;
+      cp += (j4 + 3 < lane && v.w < r) ? 1u : 0u;
+    }
+    wave_lds_sync();
+    acc = valid && q + cp < k;
+    am = __ballot(acc);
+    // the running set becomes the k smallest of (set, accepted ranks); rejected
+    // candidates have k smaller ranks before them and never enter it
+    na = (uint32_t)__popcll(am);
+    if (na <= 8) {
+      uint64_t it2 = am;
+      while (it2) {
+        const int j = __ffsll((long long)it2) - 1;
+        it2 &= it2 - 1;
+        const uint32_t rj = __shfl(r, j, WAVE);
+        kset_insert(set, rj, kset_ballot_below(set, rj), k);
+      }
+    } else {
+      kset_merge(set, wave_sort_reg(acc ? r : INF32), k);
+    }
   }
   const uint32_t tot = nset + na;
   nset = tot < k ? tot : k;
