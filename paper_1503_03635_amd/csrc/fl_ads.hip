@@ -528,81 +528,100 @@ __device__ inline uint32_t prune_level(uint32_t *s_id, uint32_t *s_tmp, uint32_t
     s_tmp[atomicAdd(&s_cnt[bucket_of(id, rm)], 1u)] = id;
   }
   wave_lds_sync();
-  // Buckets are walked in id order.  The survivors of consecutive buckets are
-  // gathered in one pending chunk of at most WAVE ids and decided together;
-  // accepted ids are written back to s_tmp[m..), which never reaches a bucket
-  // not yet read (accepted ones are a subset of the buckets already read).
+  // Buckets are walked in id order, in windows: the whole buckets among the
+  // next WAVE ids, one id per lane.  A window's ids are filtered against the
+  // running threshold and gathered in one pending chunk of at most WAVE ids,
+  // which is decided when the next window does not fit; accepted ids are
+  // written back to s_tmp[m..), which never reaches a bucket not yet read
+  // (accepted ones are a subset of the buckets already read).  A bucket of
+  // more than WAVE ids is filtered in place first, and if it is still larger,
+  // sorted into s_id (free now) and taken from there.
+  // With one bucket per step (some 15 ids each, and a rank, a threshold and a
+  // compaction for every one) the walk was a quarter of the prune.
+  const uint32_t bend = bstart + bc;
   uint64_t nonempty = __ballot(bc != 0);
   uint32_t tb = INF32;
   int done_b = -1;
   uint32_t npend = 0;
-  auto flush = [&]() {
-    uint32_t x = (uint32_t)lane < npend ? s_pend[lane] : INF32;
-    x = npend <= COUNT_SORT_MAX ? wave_sort_few(x, npend, s_r) : wave_sort_reg(x);
-    const uint64_t am = chunk_accept(x, k, rm, set, nset, prev, s_r);
-    if ((am >> lane) & 1) s_tmp[m + lanes_below(am)] = x;
-    m += (uint32_t)__popcll(am);
-    npend = 0;
-    wave_lds_sync();
-  };
-  // keep the ids of bucket [sb, sb + cb) whose rank beats the running
-  // threshold, compacted in place; returns their number
-  auto filter = [&](uint32_t sb, uint32_t cb) -> uint32_t {
-    const bool open = nset < k;
-    const uint32_t Trun = open ? INF32 : kset_at(set, k - 1);
-    uint32_t np = 0;
-    for (uint32_t j0 = 0; j0 < cb; j0 += WAVE) {
-      const uint32_t j = j0 + lane;
-      uint32_t id = INF32;
-      bool pass = false;
-      if (j < cb) {
-        id = s_tmp[sb + j];
-        pass = open || rank_of(id, rm) < Trun;
-      }
-      const uint64_t pm = __ballot(pass);
-      if (pass) s_tmp[sb + np + lanes_below(pm)] = id;
-      np += (uint32_t)__popcll(pm);
-    }
-    wave_lds_sync();
-    return np;
-  };
-  while (nonempty) {
-    const int b = __ffsll((long long)nonempty) - 1;
-    nonempty &= nonempty - 1;
-    const uint32_t cb = __shfl(bc, b, WAVE);
-    const uint32_t sb = __shfl(bstart, b, WAVE);
-    // the running threshold now bounds every bucket up to b
-    const uint32_t Tnow = nset < k ? INF32 : kset_at(set, k - 1);
-    if (lane > done_b && lane <= b) tb = Tnow;
-    done_b = b;
-    uint32_t np = filter(sb, cb);
-    if (np == 0) continue;
-    if (npend + np > (uint32_t)WAVE) {
-      flush();
-      // every earlier candidate is decided: the threshold is exact for bucket b
-      const uint32_t T2 = nset < k ? INF32 : kset_at(set, k - 1);
-      if (lane == b) tb = T2;
-      np = filter(sb, np);
-      if (np == 0) continue;
-    }
-    if (np > (uint32_t)WAVE) {
-      // many survivors in one bucket: sort them in s_id (free now), then chunks in order
-      for (uint32_t i = lane; i < np; i += WAVE) s_id[i] = s_tmp[sb + i];
-      wave_sort_lds(s_id, np);
-      for (uint32_t c0 = 0; c0 < np; c0 += WAVE) {
-        const uint32_t x = c0 + lane < np ? s_id[c0 + lane] : INF32;
-        const uint64_t am = chunk_accept(x, k, rm, set, nset, prev, s_r);
-        if ((am >> lane) & 1) s_tmp[m + lanes_below(am)] = x;
-        m += (uint32_t)__popcll(am);
+  uint32_t w0 = 0, wn = 0;  // the rest of a large bucket, sorted, in s_id
+  auto threshold = [&]() -> uint32_t { return nset < k ? INF32 : kset_at(set, k - 1); };
+  for (;;) {
+    const bool end = !wn && !nonempty;
+    bool fresh = false, wait = false;  // the window starts at a new bucket; it waits for the pending chunk
+    int b = 0, last = 0;
+    uint32_t cnt = 0;
+    const uint32_t *win = s_tmp;
+    bool open = nset < k;
+    uint32_t T = threshold();
+    if (wn) {
+      cnt = wn < (uint32_t)WAVE ? wn : (uint32_t)WAVE;
+      win = s_id + w0;
+      w0 += cnt;
+      wn -= cnt;
+    } else if (nonempty) {
+      b = __ffsll((long long)nonempty) - 1;
+      const uint32_t sb = __builtin_amdgcn_readlane(bstart, b);
+      const uint64_t fit = __ballot(bend - sb <= (uint32_t)WAVE) & nonempty;
+      win = s_tmp + sb;
+      if (fit) {
+        last = 63 - __clzll(fit);
+        cnt = __builtin_amdgcn_readlane(bend, last) - sb;
+        nonempty &= ~fit;
+        fresh = true;
+      } else if (npend) {
+        wait = true;
+      } else {
+        // the running threshold bounds every bucket up to b
+        if (lane > done_b && lane <= b) tb = T;
+        done_b = b;
+        nonempty &= nonempty - 1;
+        const uint32_t cb = __builtin_amdgcn_readlane(bc, b);
+        for (uint32_t j0 = 0; j0 < cb; j0 += WAVE) {
+          const uint32_t id = j0 + lane < cb ? s_tmp[sb + j0 + lane] : INF32;
+          const bool pass = j0 + lane < cb && (open || rank_of(id, rm) < T);
+          const uint64_t pm = __ballot(pass);
+          if (pass) s_tmp[sb + cnt + lanes_below(pm)] = id;
+          cnt += (uint32_t)__popcll(pm);
+        }
         wave_lds_sync();
+        if (cnt > (uint32_t)WAVE) {
+          for (uint32_t i = lane; i < cnt; i += WAVE) s_id[i] = s_tmp[sb + i];
+          wave_sort_lds(s_id, cnt);
+          w0 = 0;
+          wn = cnt;
+          continue;
+        }
       }
-      continue;
     }
-    if ((uint32_t)lane < np) s_pend[npend + lane] = s_tmp[sb + lane];
+    const uint32_t id = (uint32_t)lane < cnt ? win[lane] : INF32;
+    const uint32_t r = rank_of(id, rm);
+    bool pass = (uint32_t)lane < cnt && (open || r < T);
+    uint64_t pm = __ballot(pass);
+    uint32_t np = (uint32_t)__popcll(pm);
+    if (npend && (end || wait || npend + np > (uint32_t)WAVE)) {
+      uint32_t x = (uint32_t)lane < npend ? s_pend[lane] : INF32;
+      x = npend <= COUNT_SORT_MAX ? wave_sort_few(x, npend, s_r) : wave_sort_reg(x);
+      const uint64_t am = chunk_accept(x, k, rm, set, nset, prev, s_r);
+      if ((am >> lane) & 1) s_tmp[m + lanes_below(am)] = x;
+      m += (uint32_t)__popcll(am);
+      npend = 0;
+      wave_lds_sync();
+      // every earlier candidate is decided: the threshold is exact for the window
+      open = nset < k;
+      T = threshold();
+      pass = pass && (open || r < T);
+      pm = __ballot(pass);
+      np = (uint32_t)__popcll(pm);
+    }
+    if (end) break;
+    if (fresh) {
+      if (lane > done_b && lane <= last) tb = T;
+      done_b = last;
+    }
+    if (pass) s_pend[npend + lanes_below(pm)] = id;
     npend += np;
     wave_lds_sync();
   }
-  if (npend) flush();
   if (tbk) {
     const uint32_t Tend = nset < k ? INF32 : kset_at(set, k - 1);
     if (lane > done_b) tb = Tend;
