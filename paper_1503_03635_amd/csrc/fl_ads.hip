@@ -315,31 +315,6 @@ __device__ inline uint32_t kset_at(const KSet<KR> &s, uint32_t i) {
   return i < 64u ? a : b;
 }
 
-// number of set elements below the wave-uniform rank rj
-template <int KR>
-__device__ inline uint32_t kset_ballot_below(const KSet<KR> &s, uint32_t rj) {
-  uint32_t c = (uint32_t)__popcll(__ballot(s.v[0] < rj));
-  if (KR == 2) c += (uint32_t)__popcll(__ballot(s.v[KR - 1] < rj));
-  return c;
-}
-
-// insert the wave-uniform rank rj at position below, keeping k elements
-template <int KR>
-__device__ inline void kset_insert(KSet<KR> &s, uint32_t rj, uint32_t below, uint32_t k) {
-  const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t up0 = __shfl_up(s.v[0], 1, WAVE);
-  if (KR == 2) {
-    const uint32_t last0 = __shfl(s.v[0], WAVE - 1, WAVE);
-    uint32_t up1 = __shfl_up(s.v[KR - 1], 1, WAVE);
-    if (lane == 0) up1 = last0;
-    const uint32_t e1 = 64u + lane;
-    if (e1 > below && e1 < k) s.v[KR - 1] = up1;
-    if (e1 == below) s.v[KR - 1] = rj;
-  }
-  if (lane > below && lane < k) s.v[0] = up0;
-  if (lane == below) s.v[0] = rj;
-}
-
 // the set becomes the k smallest of itself and the ascending chunk x
 // (INF32-padded)
 template <int KR>
@@ -384,10 +359,33 @@ __device__ inline uint32_t kset_below(const KSet<KR> &s, uint32_t r) {
   return q == 64u ? 64u + q2 : q;
 }
 
-// Chunks with more candidates than this left are compared bit by bit: some
-// 140 instructions, and the accepted ranks come out in order; comparing all
-// pairs takes 13 per 4 candidates and a sort of the accepted ones after it.
-constexpr int CHUNK_SLICED = 24;
+// The lanes (of vm, those with valid set) with a smaller rank than this one.
+// The ranks of the valid lanes are distinct and at most `most`.  They are
+// compared bit by bit from the highest that can differ: eq holds the lanes
+// equal so far, and a ballot of each bit splits it, until every eq is a single
+// lane (after some 13 bits for 64 random ranks, 10 instructions each).
+// Comparing all pairs out of LDS took 13 instructions per 4 candidates and
+// then a sort of the accepted ranks, which here have their places: round
+// kernels of R-MAT 2^22 (unit, k = 64) 576 -> 544 ms with it for every chunk,
+// also small ones (700 -> 668 ms when first used, for more than 24).
+__device__ inline uint64_t wave_smaller(uint32_t r, bool valid, uint64_t vm, uint32_t most) {
+  uint32_t el = valid ? (uint32_t)vm : 0u, eh = valid ? (uint32_t)(vm >> 32) : 0u, ll = 0, lh = 0;
+  for (int b = most ? 31 - __clz(most) : 0; b >= 0; b -= 4) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      if (b < d) break;
+      const uint32_t bm = (uint32_t)__builtin_amdgcn_sbfe((int)r, (uint32_t)(b - d), 1u);
+      const uint64_t B = __ballot(bm != 0);
+      const uint32_t bl = (uint32_t)B, bh = (uint32_t)(B >> 32);
+      ll |= el & ~bl & bm;
+      lh |= eh & ~bh & bm;
+      el &= ~(bl ^ bm);
+      eh &= ~(bh ^ bm);
+    }
+    if (!__ballot((el & (el - 1)) | (eh & (eh - 1)) | (el && eh ? 1u : 0u))) break;
+  }
+  return ((uint64_t)lh << 32) | ll;
+}
 
 // One chunk of candidates, one id per lane in ascending lane order (INF32 =
 // empty slot at the end); duplicates are adjacent; `prev` is the last id of
@@ -412,74 +410,20 @@ __device__ inline uint64_t chunk_accept(uint32_t id, uint32_t k, const RankMap &
   // for: only those below the set's k-th rank remain
   if (q >= k) valid = false;
   const uint64_t vm = __ballot(valid);
-  bool acc;
-  uint64_t am;
-  uint32_t na;
-  if (__popcll(vm) > CHUNK_SLICED) {
-    // lt: the lanes with a smaller rank, found by comparing bit by bit from
-    // the highest that can differ.  eq holds the lanes equal so far; a ballot
-    // of each bit splits it.  Ranks are distinct, so it ends when every eq is
-    // a single lane, after some 13 bits for 64 random ranks.
-    const uint32_t kth = nset < k ? INF32 : __builtin_amdgcn_readfirstlane(kset_at(set, k - 1));
-    uint32_t el = valid ? (uint32_t)vm : 0u, eh = valid ? (uint32_t)(vm >> 32) : 0u, ll = 0, lh = 0;
-    for (int b = 31 - (kth ? __clz(kth) : 31); b >= 0; b -= 4) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        if (b < d) break;
-        const uint32_t bm = (uint32_t)__builtin_amdgcn_sbfe((int)r, (uint32_t)(b - d), 1u);
-        const uint64_t B = __ballot(bm != 0);
-        const uint32_t bl = (uint32_t)B, bh = (uint32_t)(B >> 32);
-        ll |= el & ~bl & bm;
-        lh |= eh & ~bh & bm;
-        el &= ~(bl ^ bm);
-        eh &= ~(bh ^ bm);
-      }
-      if (!__ballot((el & (el - 1)) | (eh & (eh - 1)) | (el && eh ? 1u : 0u))) break;
-    }
-    const uint64_t lt = ((uint64_t)lh << 32) | ll;
-    const uint32_t cp = lanes_below(lt);
-    acc = valid && q + cp < k;
-    am = __ballot(acc);
-    na = (uint32_t)__popcll(am);
-    if (na) {
-      // the accepted ranks ascending: each lane knows its place
-      if (acc) s_r[__popcll(lt & am)] = r;
-      wave_lds_sync();
-      const uint32_t x = (uint32_t)lane < na ? s_r[lane] : INF32;
-      wave_lds_sync();
-      kset_merge(set, x, k);
-    }
-  } else {
-    // few: the ranks staged in LDS, read four at a time by every lane from the
-    // same address (broadcast)
-    s_r[lane] = valid ? r : INF32;
+  const uint32_t kth = nset < k ? INF32 : __builtin_amdgcn_readfirstlane(kset_at(set, k - 1));
+  const uint64_t lt = wave_smaller(r, valid, vm, kth);
+  const bool acc = valid && q + lanes_below(lt) < k;
+  const uint64_t am = __ballot(acc);
+  const uint32_t na = (uint32_t)__popcll(am);
+  if (na) {
+    // the running set becomes the k smallest of (set, accepted ranks), which
+    // each lane puts in its place (rejected candidates have k smaller ranks
+    // before them and never enter it)
+    if (acc) s_r[__popcll(lt & am)] = r;
     wave_lds_sync();
-    const int top = vm ? 64 - __clzll(vm) : 0;  // lanes above the last valid one are empty
-    uint32_t cp = 0;
-    for (int j4 = 0; j4 < top; j4 += 4) {
-      const uint4 v = *reinterpret_cast<const uint4 *>(&s_r[j4]);
-      cp += (j4 + 0 < lane && v.x < r) ? 1u : 0u;
-      cp += (j4 + 1 < lane && v.y < r) ? 1u : 0u;
-      cp += (j4 + 2 < lane && v.z < r) ? 1u : 0u;
-      cp += (j4 + 3 < lane && v.w < r) ? 1u : 0u;
-    }
+    const uint32_t x = (uint32_t)lane < na ? s_r[lane] : INF32;
     wave_lds_sync();
-    acc = valid && q + cp < k;
-    am = __ballot(acc);
-    // the running set becomes the k smallest of (set, accepted ranks); rejected
-    // candidates have k smaller ranks before them and never enter it
-    na = (uint32_t)__popcll(am);
-    if (na <= 8) {
-      uint64_t it2 = am;
-      while (it2) {
-        const int j = __ffsll((long long)it2) - 1;
-        it2 &= it2 - 1;
-        const uint32_t rj = __shfl(r, j, WAVE);
-        kset_insert(set, rj, kset_ballot_below(set, rj), k);
-      }
-    } else {
-      kset_merge(set, wave_sort_reg(acc ? r : INF32), k);
-    }
+    kset_merge(set, x, k);
   }
   const uint32_t tot = nset + na;
   nset = tot < k ? tot : k;
@@ -901,8 +845,14 @@ __device__ inline bool level_commit(const AdsArgs &P, uint32_t u, uint32_t D, Le
   const size_t base = (size_t)u * P.cap + cu;
   uint32_t x0, x1;  // the two smallest ranks of the level, for its record
   if (m <= (uint32_t)WAVE) {
-    uint32_t x = (uint32_t)lane < m ? rank_of(s_tmp[lane], L.rm) : INF32;
-    x = m <= COUNT_SORT_MAX ? wave_sort_few(x, m, s_cnt + (1 + KR) * WAVE) : wave_sort_reg(x);
+    uint32_t *s_r = s_cnt + (1 + KR) * WAVE;
+    const bool in = (uint32_t)lane < m;
+    uint32_t x = in ? rank_of(s_tmp[lane], L.rm) : INF32;
+    const uint64_t lt = wave_smaller(x, in, m < (uint32_t)WAVE ? (1ull << m) - 1 : ~0ull, L.T0);
+    if (in) s_r[__popcll(lt)] = x;
+    wave_lds_sync();
+    x = in ? s_r[lane] : INF32;
+    wave_lds_sync();
     if ((uint32_t)lane < m) {
       P.sk_rank[base + lane] = x;
       P.sk_dist[base + lane] = D;
