@@ -37,10 +37,34 @@
 
 namespace fl {
 
-struct SweepState {
-  uint32_t j;     // distance to settle next
-  uint32_t done;  // no label is pending: the sweep has ended
-  uint32_t cnt;   // vertices with a label pending at distance j
+// The phase's work on one step (the i-th non-empty rung of every graph) in
+// order; rounds repeat from MP_ROUND until no facility is active.
+enum MisPhase : uint32_t {
+  MP_STEP = 0,  // the step's facilities (act) and clients (ct), the clients' bitmap
+  MP_ROUND,     // priorities of the active facilities, their bitmap
+  MP_SWEEP1,    // from act: smallest priority at the clients
+  MP_TAKE,      // the clients' minima become their labels (src)
+  MP_SWEEP2,    // from src: smallest of them at the facilities
+  MP_JOIN,      // facilities that join, the rest (act2), covered clients (cov)
+  MP_SWEEP3,    // from cov: facilities that retire
+  MP_COLLECT,   // the facilities still active (act)
+  MP_END        // the clients' bitmap is cleared
+};
+// Why the one-block kernel stopped.
+enum MisGo : uint32_t {
+  MG_DONE = 1,  // every step is done
+  MG_WIDE,      // the sweep's next distance is too large for one block
+  MG_LIST,      // the phase's lists are
+  MG_ERROR      // more rounds than facilities
+};
+struct MisState {
+  uint32_t go, phase;
+  uint32_t j;       // the sweep's distance to settle next
+  uint32_t start;   // it starts from the sources (distance 0)
+  uint32_t cnt;     // vertices to settle there
+  uint32_t step, round, stamp;             // round within the step; rounds in all
+  uint32_t na, ncl, ns2, nr, ncov, nnew;   // lengths of act, ct, src, act2, cov, the new act
+  uint32_t ntouched, nheavy;
 };
 struct SweepArgs {
   uint32_t n, NS;
@@ -57,9 +81,59 @@ struct SweepArgs {
   uint32_t *touched_cnt;
   uint64_t *heavy;    // pieces of the long rows queued in the current distance
   uint32_t *heavy_cnt;
-  SweepState *st;     // device
-  const uint32_t *tbits;  // bitmap of the vertices whose result is read (nullptr: all)
+  const uint32_t *tbits;  // bitmap of the vertices whose result is read
 };
+
+// One step's ranges, and one range: a graph's facilities and clients of the
+// step's rung.
+struct MisStep {
+  uint32_t r0, r1;       // its ranges
+  uint32_t nf, nc;       // facilities and clients in all
+  uint32_t nf_max;       // most facilities of a range
+};
+struct MisRange {
+  uint64_t f0, c0;       // in flist and clist
+  uint32_t nf, nc, fdst, cdst;  // lengths, places in act and ct
+  uint32_t q, R;         // graph and radius
+};
+
+// Device view of the whole phase.  Direction 0: from facilities over the
+// in-arcs, to the clients of cbits; 1: from clients over the out-arcs, to the
+// facilities of fbits.
+struct MisArgs {
+  SweepArgs S;  // row_ptr, col, w and tbits are set per direction
+  const uint64_t *rp[2];
+  const uint32_t *col[2], *w[2];
+  uint32_t *bits[2];  // cbits, fbits
+  MisState *st;
+  const MisStep *steps;
+  const MisRange *ranges;
+  uint32_t nsteps, G, luby;
+  const uint32_t *flist, *clist;  // facilities and clients by (graph, rung)
+  uint32_t *act, *act2, *ct, *src, *cov;
+  uint32_t *lab;     // [n] source labels
+  uint32_t *Rg;      // [G] radius of each graph in the current step
+  uint32_t *gstamp;  // [G] last round with an active facility
+  uint32_t *rcount;  // [G] rounds
+  const SegInfo *seg;
+  uint8_t *open;
+};
+__device__ inline SweepArgs sweep_args(const MisArgs &A, uint32_t phase) {
+  // both sides of each choice are loaded: an index that the compiler cannot
+  // see would put the arrays in scratch memory
+  const bool in = phase == MP_SWEEP1;
+  SweepArgs S = A.S;
+  S.row_ptr = in ? A.rp[0] : A.rp[1];
+  S.col = in ? A.col[0] : A.col[1];
+  S.w = in ? A.w[0] : A.w[1];
+  S.tbits = in ? A.bits[0] : A.bits[1];
+  return S;
+}
+// the sources of a sweep
+__device__ inline const uint32_t *sweep_sources(const MisArgs &A, const MisState &st, uint32_t phase, uint32_t *n) {
+  *n = phase == MP_SWEEP1 ? st.na : phase == MP_SWEEP2 ? st.ns2 : st.ncov;
+  return phase == MP_SWEEP1 ? A.act : phase == MP_SWEEP2 ? A.src : A.cov;
+}
 
 // Queue appends (vertex y to the list of slot s), staged per wave in LDS
 // (2 WAVE entries) and written WAVE at a time with one atomic per distinct
@@ -161,8 +235,8 @@ __device__ inline void sweep_arcs2(const SweepArgs &S, SlotQ &q, uint32_t j, boo
   const uint32_t y0 = v0 ? S.col[i0] : 0u, y1 = v1 ? S.col[i1] : 0u;
   const uint32_t w0 = v0 ? (S.w ? S.w[i0] : 1u) : 0u, w1 = v1 ? (S.w ? S.w[i1] : 1u) : 0u;
   const uint64_t d0 = (uint64_t)j + w0, d1 = (uint64_t)j + w1;
-  const bool k0 = v0 && (d0 < R0 || (d0 == R0 && (!S.tbits || ((S.tbits[y0 >> 5] >> (y0 & 31)) & 1u))));
-  const bool k1 = v1 && (d1 < R1 || (d1 == R1 && (!S.tbits || ((S.tbits[y1 >> 5] >> (y1 & 31)) & 1u))));
+  const bool k0 = v0 && (d0 < R0 || (d0 == R0 && ((S.tbits[y0 >> 5] >> (y0 & 31)) & 1u)));
+  const bool k1 = v1 && (d1 < R1 || (d1 == R1 && ((S.tbits[y1 >> 5] >> (y1 & 31)) & 1u)));
   const uint32_t m0 = k0 ? __hip_atomic_load(&S.ml[y0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
   const uint32_t m1 = k1 ? __hip_atomic_load(&S.ml[y1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
   bool add0 = false, add1 = false;
@@ -247,33 +321,21 @@ __device__ inline void touch(const SweepArgs &S, bool first, uint32_t x) {
   wave_push(S.touched, S.touched_cnt, first, x);
 }
 
-// Wide step at distance 0: the sources set ml and push (one lane per source).
-__global__ __launch_bounds__(256) void k_sweep_init(SweepArgs S, const uint32_t *src, uint32_t nsrc,
-                                                    const uint32_t *lab) {
+// Wide step, first launch: settle the labels pending at distance st->j, or the
+// sources' (a lane per vertex).  Nothing to do unless a wide step is due.
+__global__ __launch_bounds__(256) void k_sweep_wide(MisArgs A) {
+  if (A.st->go != MG_WIDE) return;
+  const uint32_t phase = A.st->phase, j = A.st->j;
+  const SweepArgs S = sweep_args(A, phase);
   SLOTQ_DECL(q);
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *S.st = SweepState{0u, 0u, nsrc};
-  bool want = false;
-  uint32_t x = 0, l = INF32;
-  if (i < nsrc) {
-    x = src[i];
-    l = lab[x];
-    want = l != INF32;
-    if (want) S.ml[x] = l;
-  }
-  touch(S, want, x);
-  sweep_push_lanes(S, q, want, x, l, 0);
-  slotq_flush(S, q);
-}
-
-// Wide step, first launch: settle the labels pending at distance st->j (one
-// lane per vertex).
-__global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
-  if (S.st->done) return;
-  SLOTQ_DECL(q);
-  const uint32_t j = S.st->j;
   const uint32_t slot = j % S.NS;
-  const uint32_t cnt = S.tl_cnt[slot * CNT_PAD];
+  const bool start = A.st->start != 0;
+  uint32_t cnt = 0;
+  const uint32_t *list = sweep_sources(A, *A.st, phase, &cnt);
+  if (!start) {
+    list = S.tl + (size_t)slot * S.n;
+    cnt = S.tl_cnt[slot * CNT_PAD];
+  }
   const uint32_t vw = wave_share(cnt), lane = (uint32_t)lane_id();
   const uint64_t stride = (uint64_t)gridDim.x * (blockDim.x / WAVE) * vw;
   for (uint64_t b = ((uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE) * vw; b < cnt; b += stride) {
@@ -281,10 +343,15 @@ __global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
     bool want = false, first = false;
     uint32_t y = 0, v = INF32;
     if (lane < vw && i < cnt) {
-      y = S.tl[(size_t)slot * S.n + i];
-      v = S.pend[(size_t)slot * S.n + y];
-      const uint32_t cur = S.ml[y];
-      S.pend[(size_t)slot * S.n + y] = INF32;
+      y = list[i];
+      uint32_t cur = INF32;
+      if (start) {
+        v = A.lab[y];
+      } else {
+        v = S.pend[(size_t)slot * S.n + y];
+        cur = S.ml[y];
+        S.pend[(size_t)slot * S.n + y] = INF32;
+      }
       if (v < cur) {
         S.ml[y] = v;
         want = true;
@@ -300,9 +367,11 @@ __global__ __launch_bounds__(256) void k_sweep_round(SweepArgs S) {
 // Wide step, second launch: the pieces of long rows queued at distance st->j,
 // one wave per piece; the label is the vertex's own (settled at this
 // distance, unchanged until the next).
-__global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S) {
-  const uint32_t cnt = *S.heavy_cnt, j = S.st->j;
+__global__ __launch_bounds__(256) void k_sweep_heavy(MisArgs A) {
+  if (A.st->go != MG_WIDE) return;
+  const uint32_t cnt = A.st->nheavy, j = A.st->j;
   if (blockIdx.x * (blockDim.x / WAVE) >= cnt) return;
+  const SweepArgs S = sweep_args(A, A.st->phase);
   SLOTQ_DECL(q);
   const int lane = lane_id();
   const uint64_t nw = ((uint64_t)gridDim.x * blockDim.x) / WAVE;
@@ -319,224 +388,11 @@ __global__ __launch_bounds__(256) void k_sweep_heavy(SweepArgs S) {
   slotq_flush(S, q);
 }
 
-// Narrow steps of a sweep (see fl_frontier.h), by one block: the distances
-// with pending labels in increasing order, until none is pending or one is
-// too large for the block.  The slot counts live in LDS meanwhile, so empty
-// distances cost nothing and appends take LDS atomics.  after_wide: first
-// close the wide step at distance st->j; otherwise start a sweep from the
-// nsrc <= NARROW_V vertices of src with labels lab (distance 0).  Pending
-// labels and minima are read and lowered at the device's L2 (agent scope);
-// the vertex lists are written and read by this block only, a barrier apart.
-// On return every wide counter is zero and st says where the sweep stands.
-// Against bursts of 8 wide distances per host check (with the fourth sweep of
-// a round gone as well): MIS of R-MAT 2^18 (unit weights, eps 0.01) 120 -> 64
-// ms, of a Chung-Lu graph of 50,000 vertices (weights 1..50) 81 -> 43 ms, of
-// R-MAT 2^21 (weights 1..100) 204 -> 152 ms.
-__global__ __launch_bounds__(NARROW_T) void k_sweep_narrow(SweepArgs S, const uint32_t *src, uint32_t nsrc,
-                                                           const uint32_t *lab, int after_wide) {
-  __shared__ uint64_t s_a0[NARROW_V];
-  __shared__ uint32_t s_excl[NARROW_V], s_lab[NARROW_V], s_R[NARROW_V], s_cnt[MAX_W + 1], s_tmp[NARROW_WAVES];
-  __shared__ uint32_t s_next, s_touched;
-  const uint32_t tid = threadIdx.x, NS = S.NS;
-  bool start = !after_wide;  // the next step settles the sources
-  uint32_t j = 0;
-  if (after_wide) {
-    if (S.st->done) return;  // the sweep had ended before the wide launches
-    j = S.st->j;
-  }
-  if (tid < NS) s_cnt[tid] = (start || tid == j % NS) ? 0u : S.tl_cnt[tid * CNT_PAD];
-  if (tid == 0) {
-    s_touched = start ? 0u : *S.touched_cnt;
-    s_next = INF32;
-  }
-  __syncthreads();
-  bool done = false;
-  uint32_t cnt = 0;
-  for (;;) {
-    if (start) {
-      cnt = nsrc;
-    } else {
-      // the next distance with a pending label (slots j + 1 .. j + NS - 1)
-      if (tid + 1 < NS && s_cnt[(j + 1 + tid) % NS]) atomicMin(&s_next, tid);
-      __syncthreads();
-      const uint32_t d = s_next;
-      __syncthreads();
-      if (d == INF32) {
-        done = true;
-        break;
-      }
-      j += 1 + d;
-      cnt = s_cnt[j % NS];
-      if (tid == 0) s_next = INF32;
-    }
-    if (cnt > NARROW_V) break;
-    const uint32_t slot = j % NS;
-    uint32_t x[2] = {0, 0}, lv[2] = {INF32, INF32}, cur[2] = {INF32, INF32}, R[2] = {0, 0}, deg[2] = {0, 0}, ex[2];
-    uint64_t a0[2] = {0, 0};
-    bool set[2] = {false, false};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t p = tid + h * NARROW_T;
-      if (p < cnt) {
-        x[h] = start ? src[p] : S.tl[(size_t)slot * S.n + p];
-        if (start) {
-          lv[h] = lab[x[h]];
-        } else {
-          lv[h] = __hip_atomic_load(&S.pend[(size_t)slot * S.n + x[h]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          cur[h] = __hip_atomic_load(&S.ml[x[h]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        R[h] = S.Rg[seg_of(S.gid, x[h])];
-        a0[h] = S.row_ptr[x[h]];
-        const uint64_t d = S.row_ptr[x[h] + 1] - a0[h];
-        set[h] = lv[h] < cur[h];
-        // arcs weigh at least 1: a label settled at distance R goes no further
-        if (set[h] && j < R[h]) deg[h] = d > NARROW_ARCS ? NARROW_ARCS + 1 : (uint32_t)d;
-      }
-    }
-    uint32_t t0, t1 = 0;
-    ex[0] = narrow_scan_excl(deg[0], s_tmp, &t0);
-    ex[1] = t0;
-    if (cnt > NARROW_T) ex[1] = t0 + narrow_scan_excl(deg[1], s_tmp, &t1);
-    const uint32_t total = t0 + t1;
-    if (total > NARROW_ARCS) break;  // a wide step takes this distance (nothing is settled yet)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t p = tid + h * NARROW_T;
-      if (!start && p < cnt) S.pend[(size_t)slot * S.n + x[h]] = INF32;
-      if (set[h]) S.ml[x[h]] = lv[h];
-      wave_push(S.touched, &s_touched, set[h] && cur[h] == INF32, x[h]);
-      s_excl[p] = p < cnt ? ex[h] : total;
-      s_a0[p] = a0[h];
-      s_lab[p] = lv[h];
-      s_R[p] = R[h];
-    }
-    if (tid == 0 && !start) s_cnt[slot] = 0;
-    __syncthreads();
-    const uint32_t half = narrow_half(cnt);
-    for (uint32_t b = 0; b < total; b += NARROW_T) {
-      const uint32_t idx = b + tid;
-      bool add = false;
-      uint32_t y = 0, s = 0;
-      if (idx < total) {
-        const uint32_t p = narrow_owner(s_excl, idx, half);
-        const uint64_t a = s_a0[p] + (idx - s_excl[p]);
-        const uint32_t l = s_lab[p], Rp = s_R[p];
-        y = S.col[a];
-        const uint32_t w = S.w ? S.w[a] : 1u;
-        const uint64_t d = (uint64_t)j + w;
-        // the conditions of sweep_arcs2
-        const bool keep = d < Rp || (d == Rp && (!S.tbits || ((S.tbits[y >> 5] >> (y & 31)) & 1u)));
-        if (keep && l < __hip_atomic_load(&S.ml[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-          s = (j + w) % NS;
-          add = atomicMin(&S.pend[(size_t)s * S.n + y], l) == INF32;
-        }
-      }
-      if (NS == 2) {
-        wave_push(S.tl + (size_t)((j + 1) & 1) * S.n, &s_cnt[(j + 1) & 1], add, y);  // one slot: one atomic per wave
-      } else if (add) {
-        S.tl[(size_t)s * S.n + atomicAdd(&s_cnt[s], 1u)] = y;
-      }
-    }
-    __syncthreads();
-    start = false;
-  }
-  if (tid < NS) S.tl_cnt[tid * CNT_PAD] = s_cnt[tid];
-  if (tid == 0) {
-    *S.touched_cnt = s_touched;
-    *S.heavy_cnt = 0;
-    *S.st = SweepState{j, done ? 1u : 0u, cnt};
-  }
-}
-
 __global__ void k_sweep_reset(SweepArgs S) {
   const uint32_t cnt = *S.touched_cnt;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt;
        i += (uint64_t)gridDim.x * blockDim.x)
     S.ml[S.touched[i]] = INF32;
-}
-
-struct MisWork {
-  SweepArgs S;
-  const Graph *g;
-  uint32_t *cbits;   // [n / 32] clients of the current step
-  uint32_t *fbits;   // [n / 32] active facilities of the current round
-  uint32_t *lab;     // [n] source labels
-  uint32_t *act;     // [n] list of active facilities
-  uint32_t *act2;    // [n]
-  uint32_t *cov;     // [n]
-  uint32_t *src;     // [n] sweep sources
-  uint32_t *cnts;    // [8] device counters
-};
-
-enum class Toward { clients, facilities };
-
-// blocks of a long-row sweep launch: twice the other frontier kernels'
-// HEAVY_BLOCKS, 32 waves per CU on 256 CUs.  A hub piece keeps two groups of
-// reads in flight per wave, and the extra waves add more: MIS 1.080 -> 0.954 s
-// on the large weighted workload, timed on one box, identical results (four
-// times gave the same)
-constexpr uint32_t SWEEP_HEAVY_BLOCKS = 2 * HEAVY_BLOCKS;
-
-// run one sweep to completion; results in S.ml (caller resets afterwards).
-// Toward::clients: from facilities f to every x with d(x, f) <= R (in-arcs);
-// Toward::facilities: from clients c to every x with d(c, x) <= R (out-arcs).
-// S.ml is exact at the vertices of the bitmap targets and at every vertex
-// closer than R; a vertex at distance exactly R outside targets may keep no
-// label.
-static void sweep(Ctx &c, MisWork &M, const uint32_t *src, uint32_t nsrc, uint32_t R, Toward dir,
-                  const uint32_t *targets) {
-  SweepArgs &S = M.S;
-  if (nsrc == 0) return;
-  S.tbits = targets;
-  const bool in = dir == Toward::clients;
-  S.row_ptr = in ? M.g->in_ptr : M.g->row_ptr;
-  S.col = in ? M.g->in_col : M.g->col;
-  S.w = in ? M.g->in_w : M.g->w;
-  auto narrow = [&](uint32_t ns, int after_wide) {
-    k_sweep_narrow<<<1, NARROW_T, 0, c.s>>>(S, src, ns, M.lab, after_wide);
-    FL_LAUNCH_CHECK();
-  };
-  auto heavy = [&]() {
-    k_sweep_heavy<<<SWEEP_HEAVY_BLOCKS, 256, 0, c.s>>>(S);
-    FL_LAUNCH_CHECK();
-  };
-  SweepState st{0u, 0u, nsrc};
-  auto check = [&]() {
-    c.fetch(S.st, sizeof(SweepState));
-    std::memcpy(&st, c.h_status, sizeof(SweepState));
-  };
-  if (nsrc <= NARROW_V) {
-    narrow(nsrc, 0);
-    check();
-  } else {
-    fill_u32(c, S.touched_cnt, 1, 0);
-  }
-  // Wide steps: two launches and the narrow one that closes the step and goes
-  // on with the narrow distances after it.  WIDE_CHAIN of them are launched
-  // per host check; those that find the sweep ended exit at once.  A frontier
-  // can grow from a handful of vertices to most of the graph within a chain,
-  // so every launch gets a grid for any frontier (the kernel strides over the
-  // count).
-  constexpr int WIDE_CHAIN = 2;
-  while (!st.done) {
-    const uint32_t blocks = wide_blocks(S.n, (uint64_t)st.cnt * 2);
-    for (int b = 0; b < WIDE_CHAIN; ++b) {
-      if (b == 0 && st.j == 0) {
-        k_sweep_init<<<(uint32_t)ceil_div((uint64_t)nsrc, 256), 256, 0, c.s>>>(S, src, nsrc, M.lab);
-      } else {
-        k_sweep_round<<<blocks, 256, 0, c.s>>>(S);
-      }
-      FL_LAUNCH_CHECK();
-      heavy();
-      narrow(0, 1);
-    }
-    check();
-  }
-}
-
-static void sweep_reset(Ctx &c, MisWork &M) {
-  k_sweep_reset<<<1024, 256, 0, c.s>>>(M.S);
-  FL_LAUNCH_CHECK();
 }
 
 // ---- small per-round kernels -------------------------------------------------
@@ -579,7 +435,20 @@ __global__ void k_take_pmin(const uint32_t *cl, uint32_t ncl, const uint32_t *ml
     if (want) src[base + lanes_below(m)] = c;
   }
 }
-// join test: m(f) = ml[f]; join iff no client (INF) or m(f) == pi(f)
+// Facility f joins iff it has no client (its minimum m is INF32) or m == pi(f).
+__device__ inline bool joins(uint32_t m, uint32_t f, const uint32_t *gid, const SegInfo *seg, uint32_t luby_round) {
+  return m == INF32 || m >= priority_of(f, gid, seg, luby_round);
+}
+// A client with label pi_min is covered iff the facility with that priority
+// joined: a facility joins when its priority is the smallest pi_min around it,
+// so it is pi_min at every client it has.  (An active facility is open only if
+// it joined this round.)
+__device__ inline bool covered(uint32_t c, const uint32_t *gid, const SegInfo *seg, uint32_t luby_round,
+                               const uint8_t *open, const uint32_t *lab) {
+  const SegInfo &sg = seg[seg_of(gid, c)];
+  const uint32_t f = perm_inv(lab[c], priority_key(sg, luby_round)) + sg.base;
+  return __hip_atomic_load(&open[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
 __global__ void k_join(const uint32_t *act, uint32_t na, const uint32_t *ml, const uint32_t *gid,
                        const SegInfo *seg, uint32_t luby_round, uint8_t *open, uint32_t *rest, uint32_t *nr) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -587,17 +456,12 @@ __global__ void k_join(const uint32_t *act, uint32_t na, const uint32_t *ml, con
   uint32_t f = 0;
   if (i < na) {
     f = act[i];
-    const uint32_t m = ml[f];
-    r = !(m == INF32 || m >= priority_of(f, gid, seg, luby_round));
+    r = !joins(ml[f], f, gid, seg, luby_round);
     if (!r) open[f] = 1;
   }
   wave_push(rest, nr, r, f);
 }
-// The clients covered by a facility that joined this round, of the clients in
-// src (label pi_min).  A facility joins when its priority is the smallest
-// pi_min around it, so it is pi_min at every client it has: a client is
-// covered iff the facility whose priority it holds joined (an active facility
-// is open only if it joined this round).  Their labels become 0, for sweep 3.
+// the covered clients of src; their labels become 0, for sweep 3
 __global__ void k_covered(const uint32_t *src, uint32_t cnt, const uint32_t *gid, const SegInfo *seg,
                           uint32_t luby_round, const uint8_t *open, uint32_t *lab, uint32_t *cov, uint32_t *ncov) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -605,8 +469,7 @@ __global__ void k_covered(const uint32_t *src, uint32_t cnt, const uint32_t *gid
   uint32_t x = 0;
   if (i < cnt) {
     x = src[i];
-    const SegInfo &sg = seg[seg_of(gid, x)];
-    hit = open[perm_inv(lab[x], priority_key(sg, luby_round)) + sg.base] != 0;
+    hit = covered(x, gid, seg, luby_round, open, lab);
     if (hit) lab[x] = 0;
   }
   wave_push(cov, ncov, hit, x);
@@ -617,6 +480,339 @@ __global__ void k_collect_alive(const uint32_t *list, uint32_t cnt, const uint32
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t x = i < cnt ? list[i] : 0u;
   wave_push(out, nout, i < cnt && ml[x] != 0, x);
+}
+
+// ---- the phase in one block --------------------------------------------------
+// Lists of up to LIST_MAX entries, and up to TOUCH_MAX minima to clear, are
+// handled by the block; 1,024 threads take some 1-2 us per 1,024 entries, a
+// separate launch with the host's round trip 30 us or more.
+constexpr uint32_t LIST_MAX = 16384, TOUCH_MAX = 65536;
+enum MisEntry : int { ME_START = 0, ME_CLOSE, ME_LISTED };
+
+// Runs the phase (every step, round and sweep) until a sweep's distance or a
+// list is too large for one block, which then stops with the reason in
+// st->go; the host launches the wide form of that piece and this kernel again:
+// ME_CLOSE after a wide step (a no-op if none was due), ME_LISTED after the
+// wide form of the phase's lists.
+//
+// Narrow steps of a sweep (see fl_frontier.h): the distances with pending
+// labels in increasing order, empty ones skipped.  The slot counts live in LDS
+// meanwhile, so appends take LDS atomics.  Pending labels, minima and bitmaps
+// are read and changed at the device's L2 (agent scope); lists and source
+// labels are written and read by this block only, a barrier apart.  While the
+// block runs, every wide counter is zero.
+//
+// Bound by latency: a step is the chain list -> row, label and minimum ->
+// column -> minimum -> atomic minimum -> list, some 5 us.  Against two
+// launches per distance, empty ones included, 8 distances per host check, and
+// a fourth sweep per round (MIS of R-MAT 2^18, unit weights, eps 0.01: 120 ms;
+// of a Chung-Lu graph of 50,000 vertices, weights 1..50: 81 ms; of R-MAT 2^21,
+// weights 1..100: 204 ms): one block per sweep 64, 33 and 144 ms; one block
+// for the whole phase 14, 24 and 137.
+__global__ __launch_bounds__(NARROW_T) void k_mis_narrow(MisArgs A, int entry) {
+  __shared__ uint64_t s_a0[NARROW_V];
+  __shared__ uint32_t s_excl[NARROW_V], s_lab[NARROW_V], s_R[NARROW_V], s_cnt[MAX_W + 1], s_tmp[NARROW_WAVES];
+  __shared__ uint32_t s_next;
+  __shared__ MisState s;
+  const uint32_t tid = threadIdx.x, NS = A.S.NS;
+  if (entry == ME_CLOSE && A.st->go != MG_WIDE) return;  // no wide step was due
+  if (tid == 0) {
+    s = *A.st;
+    s_next = INF32;
+  }
+  __syncthreads();
+  uint32_t phase = s.phase, go = 0;
+  bool closing = entry == ME_CLOSE, listed = entry == ME_LISTED;
+  if (tid < NS) s_cnt[tid] = closing && tid != s.j % NS ? A.S.tl_cnt[tid * CNT_PAD] : 0u;
+  __syncthreads();
+  // f(i, valid) for every entry of a list, by all threads, whole waves at a time
+  auto for_list = [&](uint32_t cnt, auto &&f) {
+    for (uint32_t b = 0; b < cnt; b += NARROW_T) f(b + tid, b + tid < cnt);
+  };
+  auto clear_minima = [&]() { for_list(s.ntouched, [&](uint32_t i, bool v) { if (v) A.S.ml[A.S.touched[i]] = INF32; }); };
+  auto minimum = [&](uint32_t x) -> uint32_t {
+    return __hip_atomic_load(&A.S.ml[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto set_bit = [&](uint32_t *bits, uint32_t x) { atomicOr(&bits[x >> 5], 1u << (x & 31)); };
+  auto clear_bit = [&](uint32_t *bits, uint32_t x) { atomicAnd(&bits[x >> 5], ~(1u << (x & 31))); };
+  // one phase per turn; every condition is the same in all threads, and the
+  // state is changed between two barriers
+  for (;;) {
+    __syncthreads();
+    const uint32_t luby_round = A.luby ? s.round : 0u;
+    if (phase == MP_STEP) {
+      if (s.step == A.nsteps) {
+        go = MG_DONE;
+        break;
+      }
+      const MisStep st = A.steps[s.step];
+      if (!listed) {
+        for (uint32_t r = st.r0 + tid; r < st.r1; r += NARROW_T) A.Rg[A.ranges[r].q] = A.ranges[r].R;
+        if (st.nf > LIST_MAX || st.nc > LIST_MAX) {
+          go = MG_LIST;
+          break;
+        }
+        for (uint32_t r = st.r0; r < st.r1; ++r) {
+          const MisRange x = A.ranges[r];
+          for (uint32_t i = tid; i < x.nf; i += NARROW_T) A.act[x.fdst + i] = A.flist[x.f0 + i];
+          for (uint32_t i = tid; i < x.nc; i += NARROW_T) {
+            const uint32_t c = A.clist[x.c0 + i];
+            A.ct[x.cdst + i] = c;
+            set_bit(A.bits[0], c);
+          }
+        }
+      }
+      listed = false;
+      if (tid == 0) {
+        s.na = st.nf;
+        s.ncl = st.nc;
+        s.round = 0;
+      }
+      phase = MP_ROUND;
+    } else if (phase == MP_ROUND) {
+      if (s.na == 0) {
+        phase = MP_END;
+        continue;
+      }
+      if (!listed) {
+        // the active facility of smallest priority of each graph joins every round
+        const bool over = s.round > A.steps[s.step].nf_max;
+        __syncthreads();
+        if (tid == 0) {
+          ++s.round;
+          ++s.stamp;
+        }
+        __syncthreads();
+        if (over || s.na > LIST_MAX) {
+          go = over ? MG_ERROR : MG_LIST;
+          break;
+        }
+        for_list(s.na, [&](uint32_t i, bool v) {
+          if (!v) return;
+          const uint32_t f = A.act[i];
+          A.lab[f] = priority_of(f, A.S.gid, A.seg, A.luby ? s.round : 0u);
+          set_bit(A.bits[1], f);
+          if (A.G > 1) A.gstamp[A.S.gid[f]] = s.stamp;
+        });
+        __syncthreads();
+      }
+      listed = false;
+      for (uint32_t g = tid; g < A.G; g += NARROW_T)
+        if (A.G == 1 || A.gstamp[g] == s.stamp) A.rcount[g] += 1;
+      if (tid == 0) {
+        s.j = 0;
+        s.start = 1;
+      }
+      phase = MP_SWEEP1;
+    } else if (phase == MP_SWEEP1 || phase == MP_SWEEP2 || phase == MP_SWEEP3) {
+      const SweepArgs S = sweep_args(A, phase);
+      uint32_t nsrc = 0;
+      const uint32_t *src = sweep_sources(A, s, phase, &nsrc);
+      uint32_t j = s.j, cnt = 0;
+      bool start = s.start && !closing, done = false;
+      closing = false;
+      __syncthreads();
+      if (start && tid == 0) s.ntouched = 0;
+      for (;;) {
+        if (start) {
+          cnt = nsrc;
+        } else {
+          // the next distance with a pending label (slots j + 1 .. j + NS - 1)
+          if (tid + 1 < NS && s_cnt[(j + 1 + tid) % NS]) atomicMin(&s_next, tid);
+          __syncthreads();
+          const uint32_t d = s_next;
+          __syncthreads();
+          if (d == INF32) {
+            done = true;
+            break;
+          }
+          j += 1 + d;
+          cnt = s_cnt[j % NS];
+          if (tid == 0) s_next = INF32;
+        }
+        if (cnt > NARROW_V) break;
+        const uint32_t slot = j % NS;
+        uint32_t x[2] = {0, 0}, lv[2] = {INF32, INF32}, cur[2] = {INF32, INF32}, R[2] = {0, 0}, deg[2] = {0, 0}, ex[2];
+        uint64_t a0[2] = {0, 0};
+        bool set[2] = {false, false};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t p = tid + h * NARROW_T;
+          if (p < cnt) {
+            x[h] = start ? src[p] : S.tl[(size_t)slot * S.n + p];
+            if (start) {
+              lv[h] = A.lab[x[h]];
+            } else {
+              lv[h] =
+                  __hip_atomic_load(&S.pend[(size_t)slot * S.n + x[h]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              cur[h] = minimum(x[h]);
+            }
+            R[h] = S.Rg[seg_of(S.gid, x[h])];
+            a0[h] = S.row_ptr[x[h]];
+            const uint64_t d = S.row_ptr[x[h] + 1] - a0[h];
+            set[h] = lv[h] < cur[h];
+            // arcs weigh at least 1: a label settled at distance R goes no further
+            if (set[h] && j < R[h]) deg[h] = d > NARROW_ARCS ? NARROW_ARCS + 1 : (uint32_t)d;
+          }
+        }
+        uint32_t t0, t1 = 0;
+        ex[0] = narrow_scan_excl(deg[0], s_tmp, &t0);
+        ex[1] = t0;
+        if (cnt > NARROW_T) ex[1] = t0 + narrow_scan_excl(deg[1], s_tmp, &t1);
+        const uint32_t total = t0 + t1;
+        if (total > NARROW_ARCS) break;  // a wide step takes this distance (nothing is settled yet)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t p = tid + h * NARROW_T;
+          if (!start && p < cnt) S.pend[(size_t)slot * S.n + x[h]] = INF32;
+          if (set[h]) S.ml[x[h]] = lv[h];
+          wave_push(S.touched, &s.ntouched, set[h] && cur[h] == INF32, x[h]);
+          s_excl[p] = p < cnt ? ex[h] : total;
+          s_a0[p] = a0[h];
+          s_lab[p] = lv[h];
+          s_R[p] = R[h];
+        }
+        if (tid == 0 && !start) s_cnt[slot] = 0;
+        __syncthreads();
+        const uint32_t half = narrow_half(cnt);
+        for (uint32_t b = 0; b < total; b += NARROW_T) {
+          const uint32_t idx = b + tid;
+          bool add = false;
+          uint32_t y = 0, sl = 0;
+          if (idx < total) {
+            const uint32_t p = narrow_owner(s_excl, idx, half);
+            const uint64_t a = s_a0[p] + (idx - s_excl[p]);
+            const uint32_t l = s_lab[p], Rp = s_R[p];
+            y = S.col[a];
+            const uint32_t w = S.w ? S.w[a] : 1u;
+            const uint64_t d = (uint64_t)j + w;
+            // the conditions of sweep_arcs2
+            bool keep = d < Rp;
+            if (d == Rp)
+              keep = (__hip_atomic_load(&S.tbits[y >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (y & 31)) & 1u;
+            if (keep && l < minimum(y)) {
+              sl = (j + w) % NS;
+              add = atomicMin(&S.pend[(size_t)sl * S.n + y], l) == INF32;
+            }
+          }
+          if (NS == 2) {
+            wave_push(S.tl + (size_t)((j + 1) & 1) * S.n, &s_cnt[(j + 1) & 1], add, y);  // one slot: one atomic per wave
+          } else if (add) {
+            S.tl[(size_t)sl * S.n + atomicAdd(&s_cnt[sl], 1u)] = y;
+          }
+        }
+        __syncthreads();
+        start = false;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        s.j = j;
+        s.start = start ? 1u : 0u;
+        s.cnt = cnt;
+      }
+      if (!done) {
+        go = MG_WIDE;
+        break;
+      }
+      phase += 1;
+    } else if (phase == MP_TAKE) {
+      if (!listed) {
+        if (tid == 0) s.ns2 = 0;
+        __syncthreads();
+        if (s.ncl > LIST_MAX || s.ntouched > TOUCH_MAX) {
+          go = MG_LIST;
+          break;
+        }
+        for_list(s.ncl, [&](uint32_t i, bool v) {
+          const uint32_t c = v ? A.ct[i] : 0u;
+          const uint32_t m = v ? minimum(c) : INF32;
+          if (m != INF32) A.lab[c] = m;
+          wave_push(A.src, &s.ns2, m != INF32, c);
+        });
+        __syncthreads();
+        clear_minima();
+      }
+      listed = false;
+      if (tid == 0) {
+        s.j = 0;
+        s.start = 1;
+      }
+      phase = MP_SWEEP2;
+    } else if (phase == MP_JOIN) {
+      if (!listed) {
+        if (tid == 0) s.nr = s.ncov = 0;
+        __syncthreads();
+        if (s.na > LIST_MAX || s.ns2 > LIST_MAX || s.ntouched > TOUCH_MAX) {
+          go = MG_LIST;
+          break;
+        }
+        for_list(s.na, [&](uint32_t i, bool v) {
+          const uint32_t f = v ? A.act[i] : 0u;
+          const bool rest = v && !joins(minimum(f), f, A.S.gid, A.seg, luby_round);
+          if (v && !rest) A.open[f] = 1;
+          wave_push(A.act2, &s.nr, rest, f);
+        });
+        __syncthreads();
+        clear_minima();
+        for_list(s.ns2, [&](uint32_t i, bool v) {
+          const uint32_t c = v ? A.src[i] : 0u;
+          const bool hit = v && covered(c, A.S.gid, A.seg, luby_round, A.open, A.lab);
+          if (hit) A.lab[c] = 0;
+          wave_push(A.cov, &s.ncov, hit, c);
+        });
+        __syncthreads();
+      }
+      listed = false;
+      phase = s.nr ? MP_SWEEP3 : MP_COLLECT;
+      __syncthreads();
+      if (tid == 0) {
+        s.j = 0;
+        s.start = 1;
+        s.ntouched = 0;
+      }
+    } else if (phase == MP_COLLECT) {
+      if (!listed) {
+        if (tid == 0) s.nnew = 0;
+        __syncthreads();
+        if (s.na > LIST_MAX || s.ntouched > TOUCH_MAX) {
+          go = MG_LIST;
+          break;
+        }
+        for_list(s.na, [&](uint32_t i, bool v) { if (v) clear_bit(A.bits[1], A.act[i]); });
+        __syncthreads();
+        for_list(s.nr, [&](uint32_t i, bool v) {
+          const uint32_t f = v ? A.act2[i] : 0u;
+          wave_push(A.act, &s.nnew, v && minimum(f) != 0, f);
+        });
+        __syncthreads();
+        clear_minima();
+      }
+      listed = false;
+      __syncthreads();
+      if (tid == 0) s.na = s.nnew;
+      phase = MP_ROUND;
+    } else {  // MP_END
+      if (!listed) {
+        if (s.ncl > LIST_MAX) {
+          go = MG_LIST;
+          break;
+        }
+        for_list(s.ncl, [&](uint32_t i, bool v) { if (v) clear_bit(A.bits[0], A.ct[i]); });
+      }
+      listed = false;
+      __syncthreads();
+      if (tid == 0) ++s.step;
+      phase = MP_STEP;
+    }
+  }
+  __syncthreads();
+  if (tid < NS) A.S.tl_cnt[tid * CNT_PAD] = s_cnt[tid];
+  if (tid == 0) {
+    s.go = go;
+    s.phase = phase;
+    s.nheavy = 0;
+    *A.st = s;
+  }
 }
 
 // per-(graph, rung) lists: counting sort by key koff[g] + t - 1 (t in 1..T[g])
@@ -687,20 +883,19 @@ __global__ __launch_bounds__(256) void k_rung_scatter(uint32_t n, const uint32_t
     if (keys[it] != INF32) out[off[keys[it]] + lc[keys[it]] + lpos[it]] = (uint32_t)v;
   }
 }
-// concatenate ranges [src + start, src + start + len) of a list; blockIdx.x
-// picks the range, the blocks along y split it
-__global__ void k_gather_ranges(const uint32_t *src, const uint64_t *rstart, const uint32_t *rlen,
-                                const uint64_t *rdst, uint32_t *dst) {
-  const uint32_t r = blockIdx.x;
-  const uint64_t s0 = rstart[r], d0 = rdst[r];
-  const uint32_t len = rlen[r];
-  const uint64_t stride = (uint64_t)gridDim.y * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.y * blockDim.x + threadIdx.x; i < len; i += stride) dst[d0 + i] = src[s0 + i];
+// a step's facilities and clients; blockIdx.x picks the range, the blocks
+// along y split it
+__global__ void k_gather_step(MisArgs A, uint32_t r0) {
+  const MisRange x = A.ranges[r0 + blockIdx.x];
+  const uint32_t i0 = blockIdx.y * blockDim.x + threadIdx.x, stride = gridDim.y * blockDim.x;
+  for (uint64_t i = i0; i < x.nf; i += stride) A.act[x.fdst + i] = A.flist[x.f0 + i];
+  for (uint64_t i = i0; i < x.nc; i += stride) A.ct[x.cdst + i] = A.clist[x.c0 + i];
 }
 // graphs whose facility of list[i] is active this round
-__global__ void k_mark_graphs(const uint32_t *list, uint32_t cnt, const uint32_t *gid, uint32_t *flag) {
+__global__ void k_mark_graphs(const uint32_t *list, uint32_t cnt, const uint32_t *gid, uint32_t *gstamp,
+                              uint32_t stamp) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < cnt) flag[seg_of(gid, list[i])] = 1u;
+  if (i < cnt) gstamp[gid[list[i]]] = stamp;
 }
 __global__ void k_guard_open(uint32_t n, const uint32_t *orung, uint8_t *open) {
   const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -719,9 +914,10 @@ static void mark_bits(Ctx &c, const uint32_t *list, uint32_t cnt, uint32_t *bits
   k_mark_bits<<<(uint32_t)ceil_div(cnt, 256), 256, 0, c.s>>>(list, cnt, bits, set);
   FL_LAUNCH_CHECK();
 }
-__global__ void k_open_list(const uint32_t *list, uint32_t cnt, uint8_t *open) {
+// facilities alone in their graph's rung join at once: at[i] are their places
+__global__ void k_open_singles(const uint32_t *flist, const uint32_t *at, uint32_t cnt, uint8_t *open) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < cnt) open[list[i]] = 1;
+  if (i < cnt) open[flist[at[i]]] = 1;
 }
 
 static void by_rung(Ctx &c, uint32_t n, const uint32_t *rung, const uint32_t *gid, const uint32_t *koff,
@@ -742,42 +938,12 @@ static void by_rung(Ctx &c, uint32_t n, const uint32_t *rung, const uint32_t *gi
   c.sync();
 }
 
-static uint32_t read_u32(Ctx &c, const uint32_t *d) {
-  FL_HIP(hipMemcpyAsync(c.h_status, d, 4, hipMemcpyDeviceToHost, c.s));
-  c.sync();
-  return (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-}
-
-// Concatenates host-described ranges of `src` into `dst` on the device;
-// returns the total length.
-struct RangeBuf {
-  uint64_t *start, *dst;
-  uint32_t *len;
-};
-static uint32_t gather(Ctx &c, const uint32_t *src, const std::vector<std::pair<uint64_t, uint32_t>> &rs,
-                       RangeBuf &rb, uint32_t *dst) {
-  if (rs.empty()) return 0;
-  const size_t R = rs.size();
-  std::vector<uint64_t> hs(R), hd(R);
-  std::vector<uint32_t> hl(R);
-  uint64_t tot = 0;
-  for (size_t i = 0; i < R; ++i) {
-    hs[i] = rs[i].first;
-    hl[i] = rs[i].second;
-    hd[i] = tot;
-    tot += rs[i].second;
-  }
-  FL_HIP(hipMemcpyAsync(rb.start, hs.data(), R * 8, hipMemcpyHostToDevice, c.s));
-  FL_HIP(hipMemcpyAsync(rb.dst, hd.data(), R * 8, hipMemcpyHostToDevice, c.s));
-  FL_HIP(hipMemcpyAsync(rb.len, hl.data(), R * 4, hipMemcpyHostToDevice, c.s));
-  uint32_t maxlen = 1;
-  for (size_t i = 0; i < R; ++i) maxlen = std::max(maxlen, hl[i]);
-  const uint32_t cy = (uint32_t)std::min<uint64_t>(ceil_div(maxlen, 1024), 1024);
-  k_gather_ranges<<<dim3((uint32_t)R, cy), 256, 0, c.s>>>(src, rb.start, rb.len, rb.dst, dst);
-  FL_LAUNCH_CHECK();
-  c.sync();  // the host vectors are released on return
-  return (uint32_t)tot;
-}
+// blocks of a long-row sweep launch: twice the other frontier kernels'
+// HEAVY_BLOCKS, 32 waves per CU on 256 CUs.  A hub piece keeps two groups of
+// reads in flight per wave, and the extra waves add more: MIS 1.080 -> 0.954 s
+// on the large weighted workload, timed on one box, identical results (four
+// times gave the same)
+constexpr uint32_t SWEEP_HEAVY_BLOCKS = 2 * HEAVY_BLOCKS;
 
 int mis_phase(Ctx &c, const MisIn &in, uint8_t *open, std::vector<uint32_t> &rounds_out) {
   const Graph &g = *in.g;
@@ -807,152 +973,194 @@ int mis_phase(Ctx &c, const MisIn &in, uint8_t *open, std::vector<uint32_t> &rou
   by_rung(c, n, in.orung, in.gid, koff, Tg, K, flist, foff);
   by_rung(c, n, in.frz, in.gid, koff, Tg, K, clist, coff);
 
-  MisWork M;
-  M.S.n = n;
-  M.S.NS = NS;
-  M.S.gid = in.gid;
-  uint32_t *d_R = c.arena->get<uint32_t>(G);
-  M.S.Rg = d_R;
-  M.g = &g;
-  M.S.ml = c.arena->get<uint32_t>(n);
-  M.S.pend = c.arena->get<uint32_t>((size_t)NS * n);
-  M.S.tl = c.arena->get<uint32_t>((size_t)NS * n);
-  M.S.tl_cnt = c.arena->get<uint32_t>((size_t)NS * CNT_PAD);
-  M.S.touched = c.arena->get<uint32_t>(n);
-  M.S.touched_cnt = c.arena->get<uint32_t>(1);
-  M.S.heavy = c.arena->get<uint64_t>(piece_capacity(n, g.m));
-  M.S.heavy_cnt = c.arena->get<uint32_t>(1);
-  M.S.st = c.arena->get<SweepState>(1);
-  M.lab = c.arena->get<uint32_t>(n);
-  M.act = c.arena->get<uint32_t>(n);
-  M.act2 = c.arena->get<uint32_t>(n);
-  M.cov = c.arena->get<uint32_t>(n);
-  M.src = c.arena->get<uint32_t>(n);
-  M.cnts = c.arena->get<uint32_t>(8);
+  MisArgs A{};
+  A.S.n = n;
+  A.S.NS = NS;
+  A.S.gid = in.gid;
+  A.Rg = c.arena->get<uint32_t>(G);
+  A.S.Rg = A.Rg;
+  A.S.ml = c.arena->get<uint32_t>(n);
+  A.S.pend = c.arena->get<uint32_t>((size_t)NS * n);
+  A.S.tl = c.arena->get<uint32_t>((size_t)NS * n);
+  A.S.tl_cnt = c.arena->get<uint32_t>((size_t)NS * CNT_PAD);
+  A.S.touched = c.arena->get<uint32_t>(n);
+  A.S.heavy = c.arena->get<uint64_t>(piece_capacity(n, g.m));
+  A.st = c.arena->get<MisState>(1);
+  A.S.touched_cnt = &A.st->ntouched;
+  A.S.heavy_cnt = &A.st->nheavy;
+  A.rp[0] = g.in_ptr;
+  A.col[0] = g.in_col;
+  A.w[0] = g.in_w;
+  A.rp[1] = g.row_ptr;
+  A.col[1] = g.col;
+  A.w[1] = g.w;
   const size_t nwords = ((size_t)n + 31) / 32;
-  M.cbits = c.arena->get<uint32_t>(nwords);
-  M.fbits = c.arena->get<uint32_t>(nwords);
-  M.S.tbits = nullptr;
-  uint32_t *ct_list = c.arena->get<uint32_t>(n);  // clients of the current step
-  uint32_t *gact = c.arena->get<uint32_t>(G);     // graphs active in a round
-  RangeBuf rb;
-  rb.start = c.arena->get<uint64_t>(G);
-  rb.dst = c.arena->get<uint64_t>(G);
-  rb.len = c.arena->get<uint32_t>(G);
-  fill_u32(c, M.S.ml, n, INF32);
-  fill_u32(c, M.S.pend, (size_t)NS * n, INF32);
-  fill_u32(c, M.S.tl_cnt, (size_t)NS * CNT_PAD, 0);
-  fill_u32(c, M.S.heavy_cnt, 1, 0);
-  fill_u32(c, M.cbits, nwords, 0);
-  fill_u32(c, M.fbits, nwords, 0);
+  A.bits[0] = c.arena->get<uint32_t>(nwords);
+  A.bits[1] = c.arena->get<uint32_t>(nwords);
+  A.G = G;
+  A.luby = in.luby ? 1u : 0u;
+  A.flist = flist;
+  A.clist = clist;
+  A.act = c.arena->get<uint32_t>(n);
+  A.act2 = c.arena->get<uint32_t>(n);
+  A.ct = c.arena->get<uint32_t>(n);
+  A.src = c.arena->get<uint32_t>(n);
+  A.cov = c.arena->get<uint32_t>(n);
+  A.lab = c.arena->get<uint32_t>(n);
+  A.gstamp = c.arena->get<uint32_t>(G);
+  A.rcount = c.arena->get<uint32_t>(G);
+  A.seg = in.seg;
+  A.open = open;
 
-  // each graph's non-empty rungs, in order
+  // Each graph's non-empty rungs, in order; step i takes the i-th of every
+  // graph.  A facility alone in its rung conflicts with nothing: it joins.
+  const double one_eps = 1.0 + in.eps;
   std::vector<std::vector<uint32_t>> lists(G);
-  size_t steps = 0;
+  size_t nlists = 0;
   for (uint32_t q = 0; q < G; ++q) {
     for (uint32_t t = 1; t <= hT[q]; ++t) {
       const uint32_t key = hkoff[q] + t - 1;
       if (foff[key + 1] > foff[key]) lists[q].push_back(t);
     }
-    steps = std::max(steps, lists[q].size());
+    nlists = std::max(nlists, lists[q].size());
   }
-  const double one_eps = 1.0 + in.eps;
-  std::vector<uint32_t> hR(G, 0), hact(G);
-  std::vector<std::pair<uint64_t, uint32_t>> fr, cr, single;
-  for (size_t i = 0; i < steps; ++i) {
-    fr.clear();
-    cr.clear();
-    single.clear();
-    uint32_t Rmax = 0;
-    std::fill(hR.begin(), hR.end(), 0u);
+  std::vector<MisStep> steps;
+  std::vector<MisRange> ranges;
+  std::vector<uint32_t> singles;
+  for (size_t i = 0; i < nlists; ++i) {
+    MisStep st{(uint32_t)ranges.size(), 0, 0, 0, 0};
     for (uint32_t q = 0; q < G; ++q) {
       if (i >= lists[q].size()) continue;
       const uint32_t t = lists[q][i];
       const uint32_t key = hkoff[q] + t - 1;
       const uint32_t nf = (uint32_t)(foff[key + 1] - foff[key]);
       if (nf == 1) {
-        single.push_back({foff[key], 1u});
+        singles.push_back((uint32_t)foff[key]);
         rounds_out[q] += 1;
         continue;
       }
-      fr.push_back({foff[key], nf});
-      const uint32_t ncl = (uint32_t)(coff[key + 1] - coff[key]);
-      if (ncl) cr.push_back({coff[key], ncl});
+      const uint32_t nc = (uint32_t)(coff[key + 1] - coff[key]);
       const double rho = one_eps * (*in.lad)[q][t];
       // integer radius: d <= rho  <=>  d <= floor(rho)
-      hR[q] = rho >= 4294967295.0 ? 0xFFFFFFFEu : (uint32_t)std::floor(rho);
-      Rmax = std::max(Rmax, hR[q]);
+      const uint32_t R = rho >= 4294967295.0 ? 0xFFFFFFFEu : (uint32_t)std::floor(rho);
+      ranges.push_back(MisRange{foff[key], coff[key], nf, nc, st.nf, st.nc, q, R});
+      st.nf += nf;
+      st.nc += nc;
+      st.nf_max = std::max(st.nf_max, nf);
     }
-    if (!single.empty()) {
-      const uint32_t ns1 = gather(c, flist, single, rb, M.act);
-      k_open_list<<<(uint32_t)ceil_div(ns1, 256), 256, 0, c.s>>>(M.act, ns1, open);
-      FL_LAUNCH_CHECK();
-    }
-    if (fr.empty()) continue;
-    FL_HIP(hipMemcpyAsync(d_R, hR.data(), G * 4, hipMemcpyHostToDevice, c.s));
-    uint32_t na = gather(c, flist, fr, rb, M.act);
-    const uint32_t ncl = gather(c, clist, cr, rb, ct_list);
-    const uint32_t *Ct = ct_list;
-    mark_bits(c, Ct, ncl, M.cbits, 1);
-    uint32_t guard_rounds = 0, step_round = 0;
-    uint32_t nf_max = 0;
-    for (auto &r : fr) nf_max = std::max(nf_max, r.second);
-    while (na) {
-      // the active facility of smallest priority of each graph joins every round
-      if (++guard_rounds > nf_max + 1) return FL_EHIP;
-      const uint32_t luby_round = in.luby ? ++step_round : 0u;
-      if (G > 1) {
-        fill_u32(c, gact, G, 0);
-        k_mark_graphs<<<(uint32_t)ceil_div(na, 256), 256, 0, c.s>>>(M.act, na, in.gid, gact);
-        FL_LAUNCH_CHECK();
-        FL_HIP(hipMemcpyAsync(hact.data(), gact, G * 4, hipMemcpyDeviceToHost, c.s));
-      }
-      mark_bits(c, M.act, na, M.fbits, 1);
-      // 1. pi_min at the clients of the rung
-      k_set_key_labels<<<(uint32_t)ceil_div(na, 256), 256, 0, c.s>>>(M.act, na, M.lab, in.gid, in.seg,
-                                                                     luby_round);
-      FL_LAUNCH_CHECK();
-      sweep(c, M, M.act, na, Rmax, Toward::clients, M.cbits);
-      if (G > 1) {
-        for (uint32_t q = 0; q < G; ++q) rounds_out[q] += hact[q];
-      } else {
-        rounds_out[0] += 1;
-      }
-      fill_u32(c, M.cnts, 8, 0);
-      if (ncl) {
-        k_take_pmin<<<(uint32_t)ceil_div(ncl, 256), 256, 0, c.s>>>(Ct, ncl, M.S.ml, M.lab, M.src, M.cnts);
-        FL_LAUNCH_CHECK();
-      }
-      sweep_reset(c, M);
-      const uint32_t ns2 = read_u32(c, M.cnts);
-      // 2. smallest pi_min around each active facility; joins
-      sweep(c, M, M.src, ns2, Rmax, Toward::facilities, M.fbits);
-      k_join<<<(uint32_t)ceil_div(na, 256), 256, 0, c.s>>>(M.act, na, M.S.ml, in.gid, in.seg, luby_round, open,
-                                                           M.act2, M.cnts + 1);
-      FL_LAUNCH_CHECK();
-      sweep_reset(c, M);
-      if (ns2) {
-        k_covered<<<(uint32_t)ceil_div(ns2, 256), 256, 0, c.s>>>(M.src, ns2, in.gid, in.seg, luby_round, open, M.lab,
-                                                                 M.cov, M.cnts + 2);
-        FL_LAUNCH_CHECK();
-      }
-      c.fetch(M.cnts, 16);
-      const uint32_t nr = (uint32_t)(c.h_status[0] >> 32);
-      const uint32_t ncov = (uint32_t)(c.h_status[1] & 0xFFFFFFFFu);
-      if (nr == 0) {
-        mark_bits(c, M.act, na, M.fbits, 0);
-        break;
-      }
-      // 3. facilities next to a covered client retire
-      sweep(c, M, M.cov, ncov, Rmax, Toward::facilities, M.fbits);  // read at the rest, a subset of act
-      mark_bits(c, M.act, na, M.fbits, 0);  // before act is rewritten
-      k_collect_alive<<<(uint32_t)ceil_div(nr, 256), 256, 0, c.s>>>(M.act2, nr, M.S.ml, M.act, M.cnts + 3);
-      FL_LAUNCH_CHECK();
-      sweep_reset(c, M);
-      na = read_u32(c, M.cnts + 3);
-    }
-    mark_bits(c, Ct, ncl, M.cbits, 0);
+    st.r1 = (uint32_t)ranges.size();
+    if (st.r1 > st.r0) steps.push_back(st);
   }
+  if (!singles.empty()) {
+    uint32_t *d = c.arena->get<uint32_t>(singles.size());
+    FL_HIP(hipMemcpyAsync(d, singles.data(), singles.size() * 4, hipMemcpyHostToDevice, c.s));
+    const uint32_t ns1 = (uint32_t)singles.size();
+    k_open_singles<<<(uint32_t)ceil_div(ns1, 256), 256, 0, c.s>>>(flist, d, ns1, open);
+    FL_LAUNCH_CHECK();
+  }
+  if (steps.empty()) {
+    c.sync();  // singles is read by the copy above
+    return FL_OK;
+  }
+  MisStep *d_steps = c.arena->get<MisStep>(steps.size());
+  MisRange *d_ranges = c.arena->get<MisRange>(ranges.size());
+  FL_HIP(hipMemcpyAsync(d_steps, steps.data(), steps.size() * sizeof(MisStep), hipMemcpyHostToDevice, c.s));
+  FL_HIP(hipMemcpyAsync(d_ranges, ranges.data(), ranges.size() * sizeof(MisRange), hipMemcpyHostToDevice, c.s));
+  A.steps = d_steps;
+  A.ranges = d_ranges;
+  A.nsteps = (uint32_t)steps.size();
+  fill_u32(c, A.S.ml, n, INF32);
+  fill_u32(c, A.S.pend, (size_t)NS * n, INF32);
+  fill_u32(c, A.S.tl_cnt, (size_t)NS * CNT_PAD, 0);
+  fill_u32(c, reinterpret_cast<uint32_t *>(A.st), sizeof(MisState) / 4, 0);
+  fill_u32(c, A.bits[0], nwords, 0);
+  fill_u32(c, A.bits[1], nwords, 0);
+  fill_u32(c, A.gstamp, G, 0);
+  fill_u32(c, A.rcount, G, 0);
+
+  MisState st{};
+  auto narrow = [&](MisEntry e) {
+    k_mis_narrow<<<1, NARROW_T, 0, c.s>>>(A, e);
+    FL_LAUNCH_CHECK();
+  };
+  // A wide step is two launches and the one-block kernel, which closes it and
+  // goes on.  One that finds no wide step due exits at once.  A frontier can
+  // grow from a handful of vertices to most of the graph, so every launch
+  // gets a grid for any frontier (the kernel strides over the count).
+  auto wide = [&](uint64_t want) {
+    k_sweep_wide<<<wide_blocks(n, want), 256, 0, c.s>>>(A);
+    FL_LAUNCH_CHECK();
+    k_sweep_heavy<<<SWEEP_HEAVY_BLOCKS, 256, 0, c.s>>>(A);
+    FL_LAUNCH_CHECK();
+    narrow(ME_CLOSE);
+  };
+  auto check = [&]() {
+    c.fetch(A.st, sizeof(MisState));
+    std::memcpy(&st, c.h_status, sizeof(MisState));
+  };
+  auto blocks = [](uint32_t cnt) { return (uint32_t)ceil_div(cnt ? cnt : 1, 256); };
+  auto clear_minima = [&]() {
+    k_sweep_reset<<<1024, 256, 0, c.s>>>(A.S);
+    FL_LAUNCH_CHECK();
+  };
+  // the wide form of a phase's lists
+  auto lists_of = [&](uint32_t phase) {
+    const uint32_t luby_round = in.luby ? st.round : 0u;
+    if (phase == MP_STEP) {
+      const MisStep &ms = steps[st.step];
+      const uint32_t cy = (uint32_t)std::min<uint64_t>(ceil_div(std::max(ms.nf, ms.nc), 1024), 1024);
+      k_gather_step<<<dim3(ms.r1 - ms.r0, cy), 256, 0, c.s>>>(A, ms.r0);
+      FL_LAUNCH_CHECK();
+      mark_bits(c, A.ct, ms.nc, A.bits[0], 1);
+    } else if (phase == MP_ROUND) {
+      k_set_key_labels<<<blocks(st.na), 256, 0, c.s>>>(A.act, st.na, A.lab, in.gid, in.seg, luby_round);
+      FL_LAUNCH_CHECK();
+      mark_bits(c, A.act, st.na, A.bits[1], 1);
+      if (G > 1) {
+        k_mark_graphs<<<blocks(st.na), 256, 0, c.s>>>(A.act, st.na, in.gid, A.gstamp, st.stamp);
+        FL_LAUNCH_CHECK();
+      }
+    } else if (phase == MP_TAKE) {
+      k_take_pmin<<<blocks(st.ncl), 256, 0, c.s>>>(A.ct, st.ncl, A.S.ml, A.lab, A.src, &A.st->ns2);
+      FL_LAUNCH_CHECK();
+      clear_minima();
+    } else if (phase == MP_JOIN) {
+      k_join<<<blocks(st.na), 256, 0, c.s>>>(A.act, st.na, A.S.ml, in.gid, in.seg, luby_round, open, A.act2,
+                                             &A.st->nr);
+      FL_LAUNCH_CHECK();
+      clear_minima();
+      k_covered<<<blocks(st.ns2), 256, 0, c.s>>>(A.src, st.ns2, in.gid, in.seg, luby_round, open, A.lab, A.cov,
+                                                 &A.st->ncov);
+      FL_LAUNCH_CHECK();
+    } else if (phase == MP_COLLECT) {
+      mark_bits(c, A.act, st.na, A.bits[1], 0);  // before act is rewritten
+      k_collect_alive<<<blocks(st.nr), 256, 0, c.s>>>(A.act2, st.nr, A.S.ml, A.act, &A.st->nnew);
+      FL_LAUNCH_CHECK();
+      clear_minima();
+    } else {
+      mark_bits(c, A.ct, st.ncl, A.bits[0], 0);
+    }
+  };
+  narrow(ME_START);
+  check();
+  while (st.go != MG_DONE) {
+    if (st.go == MG_WIDE) {
+      wide((uint64_t)st.cnt * 2);
+      wide(0);
+    } else if (st.go == MG_LIST) {
+      // large lists are mostly a large sweep's sources
+      lists_of(st.phase);
+      narrow(ME_LISTED);
+      wide(0);
+    } else {
+      return FL_EHIP;  // more rounds than facilities: a bug
+    }
+    check();
+  }
+  std::vector<uint32_t> hr(G);
+  FL_HIP(hipMemcpyAsync(hr.data(), A.rcount, G * 4, hipMemcpyDeviceToHost, c.s));
+  c.sync();
+  for (uint32_t q = 0; q < G; ++q) rounds_out[q] += hr[q];
   return FL_OK;
 }
 
