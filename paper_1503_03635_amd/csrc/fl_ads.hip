@@ -1646,7 +1646,7 @@ struct TaskScratch {
 // two-task kernel; on R-MAT 2^21 (weights 1..100) 708 -> 608 us.
 // tot: this round's totals, zero before the launch.
 constexpr uint32_t SCAN_WORDS = 8;
-constexpr uint32_t BEGIN_T = 1024;  // threads of a block: few blocks, few reservations on the three counters
+constexpr uint32_t BEGIN_T = 256;  // threads of a block: small blocks start sooner beside other streams' kernels
 template <uint32_t ITEMS>
 __global__ __launch_bounds__(BEGIN_T) void k_round_begin(AdsArgs P, uint32_t D, uint32_t task_arcs, RoundTot *tot,
                                                      uint32_t *task_u, uint32_t *task_sub, uint32_t *task_slot,
@@ -2142,7 +2142,7 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     uint64_t *ts = c.timing ? rs->ts[r] : nullptr;
     auto tsp = [&](int i) { return ts ? ts + i : nullptr; };
 #define FL_BEGIN(ITEMS)                                                                                       \
-  k_round_begin<ITEMS><<<(uint32_t)std::min<uint64_t>(ceil_div(n, BEGIN_T * ITEMS), 512), BEGIN_T, 0, c.s>>>( \
+  k_round_begin<ITEMS><<<(uint32_t)std::min<uint64_t>(ceil_div(n, BEGIN_T * ITEMS), 2048), BEGIN_T, 0, c.s>>>( \
       P, D, sparse_arcs, tot, tl.task_u, tl.task_sub, tl.task_slot, tl.split_u, tl.split_first, tl.split_nt, \
       tsp(0))
     if (n >= (1u << 18)) FL_BEGIN(4);

@@ -462,6 +462,7 @@ struct SsspState {
   uint32_t iter;    // iterations done on this workspace (stamps grow across searches)
   uint32_t nnext;   // wide iterations: vertices appended to the other list
   uint32_t nheavy;  // wide iterations: queued pieces of long rows
+  uint32_t wide;    // wide iterations done on this workspace
 };
 struct SsspWork {
   uint32_t *front[2];
@@ -471,5 +472,14 @@ struct SsspWork {
 };
 void sssp_alloc(Ctx &c, SsspWork &wk, uint32_t n, uint64_t m);
 void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, uint32_t nseeds, SsspWork &wk);
+// Without a host check, for the opening loop (all device pointers): a search
+// from the *d_nseeds vertices of seeds, which also get their labels (their own
+// id at distance 0), as far as one block goes; nothing if *stop is set.  A
+// search that needs wide iterations is left with wk.st->nf != 0; if the seeds
+// themselves are too many, unlabelled.
+void sssp_opened(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, const uint32_t *d_nseeds,
+                 const uint32_t *stop, SsspWork &wk);
+// the search that wk.st describes: narrow iterations and up to `wide` wide ones
+void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, SsspWork &wk, int wide);
 
 }  // namespace fl

@@ -572,28 +572,40 @@ __global__ __launch_bounds__(256) void k_sssp_heavy(SsspArgs S) {
 }
 
 // Narrow iterations (see fl_frontier.h), by one block, until the frontier is
-// empty or too large.  after_wide: first close the wide iteration that ran
-// before (its frontier is the list it appended to); otherwise start from the
-// nseeds <= NARROW_V vertices of seeds.  Labels are read and lowered at the
+// empty or too large.  SE_SEEDS: start from the nseeds <= NARROW_V vertices of
+// seeds; SE_WIDE: first close the wide iteration that ran before (its frontier
+// is the list it appended to); SE_STATE: go on from the state; SE_OPENED: start
+// from the *d_nseeds vertices of seeds and label them, unless *stop is set
+// (more than NARROW_V are left to the host).  Labels are read and lowered at the
 // device's L2 (agent scope); the frontier lists are written and read by this
 // block only, a barrier apart.
 // Bound by latency: an iteration is the chain list -> row and label ->
 // column -> label -> atomic minimum -> stamp -> list.  Opening loop of R-MAT
 // 2^18 (unit weights, eps 0.01, 476 searches): 86 -> 60 ms, of a Chung-Lu
 // graph of 50,000 vertices 20 -> 13 ms, against 8 wide iterations per check.
+enum SsspEntry : int { SE_SEEDS = 0, SE_WIDE, SE_STATE, SE_OPENED };
 __global__ __launch_bounds__(NARROW_T) void k_sssp_narrow(SsspArgs S, const uint32_t *seeds, uint32_t nseeds,
-                                                          int after_wide) {
+                                                          int entry, const uint32_t *d_nseeds, const uint32_t *stop) {
   __shared__ uint64_t s_a0[NARROW_V], s_L[NARROW_V];
   __shared__ uint32_t s_excl[NARROW_V], s_tmp[NARROW_WAVES], s_nn;
   const uint32_t tid = threadIdx.x;
-  uint32_t nf = nseeds, cur = S.st->cur, iter = S.st->iter;
+  uint32_t nf = nseeds, cur = S.st->cur, iter = S.st->iter, wide = S.st->wide;
   const uint32_t *list = seeds;
-  if (after_wide) {
-    if (S.st->nf == 0) return;  // the search had ended before the wide launches
-    nf = S.st->nnext;
-    cur ^= 1;
-    ++iter;
+  if (entry == SE_WIDE || entry == SE_STATE) {
+    nf = S.st->nf;
+    if (nf == 0) return;  // the search had ended before the wide launches
+    if (entry == SE_WIDE) {
+      nf = S.st->nnext;
+      cur ^= 1;
+      ++iter;
+      ++wide;
+    }
     list = S.front[cur];
+  } else if (entry == SE_OPENED) {
+    if (*stop) return;
+    nf = *d_nseeds;
+    if (nf <= NARROW_V)
+      for (uint32_t p = tid; p < nf; p += NARROW_T) S.labels[seeds[p]] = (uint64_t)seeds[p];
   }
   __syncthreads();  // every thread has read the state before it is rewritten
   while (nf && nf <= NARROW_V) {
@@ -650,15 +662,15 @@ __global__ __launch_bounds__(NARROW_T) void k_sssp_narrow(SsspArgs S, const uint
     list = S.front[cur];
     __syncthreads();  // s_nn is cleared and the LDS arrays are rewritten by the next iteration
   }
-  if (nf && list == seeds) {
+  if (nf && nf <= NARROW_V && list == seeds) {
     // the first iteration is a wide one: it reads the frontier list
     for (uint32_t p = tid; p < nf; p += NARROW_T) S.front[cur][p] = seeds[p];
   }
-  if (tid == 0) *S.st = SsspState{nf, cur, iter, 0u, 0u};
+  if (tid == 0) *S.st = SsspState{nf, cur, iter, 0u, 0u, wide};
 }
 
 // a search that starts with a wide iteration over front[0]
-__global__ void k_sssp_start(SsspState *st, uint32_t nf) { *st = SsspState{nf, 0u, st->iter, 0u, 0u}; }
+__global__ void k_sssp_start(SsspState *st, uint32_t nf) { *st = SsspState{nf, 0u, st->iter, 0u, 0u, st->wide}; }
 
 void sssp_alloc(Ctx &c, SsspWork &wk, uint32_t n, uint64_t m) {
   wk.front[0] = c.arena->get<uint32_t>(n + 1);
@@ -679,40 +691,59 @@ void sssp_alloc(Ctx &c, SsspWork &wk, uint32_t n, uint64_t m) {
 // large; a wide iteration is two launches and the narrow one that closes it
 // (and goes on if what is left is narrow).  WIDE_CHAIN wide iterations are
 // launched per host check; those that find the search ended exit at once.
+constexpr int WIDE_CHAIN = 2;
+static SsspArgs sssp_args(const Graph &g, uint64_t *labels, const SsspWork &wk) {
+  return SsspArgs{g.in_ptr, g.in_col, g.in_w, labels, {wk.front[0], wk.front[1]}, wk.flag, wk.heavy, wk.st};
+}
+static void sssp_narrow(Ctx &c, const SsspArgs &S, const uint32_t *seeds, uint32_t nseeds, SsspEntry e,
+                        const uint32_t *d_nseeds = nullptr, const uint32_t *stop = nullptr) {
+  k_sssp_narrow<<<1, NARROW_T, 0, c.s>>>(S, seeds, nseeds, e, d_nseeds, stop);
+  FL_LAUNCH_CHECK();
+}
+// a frontier can grow by orders of magnitude within a chain: every launch gets
+// a grid for any frontier (blocks past the count exit)
+static void sssp_wide(Ctx &c, const Graph &g, const SsspArgs &S, uint32_t nf) {
+  k_sssp_push<<<wide_blocks(g.n, nf), 256, 0, c.s>>>(S);
+  FL_LAUNCH_CHECK();
+  k_sssp_heavy<<<HEAVY_BLOCKS, 256, 0, c.s>>>(S);
+  FL_LAUNCH_CHECK();
+  sssp_narrow(c, S, nullptr, 0, SE_WIDE);
+}
+static uint32_t sssp_check(Ctx &c, const SsspWork &wk) {
+  c.fetch(wk.st, sizeof(uint32_t));
+  return (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
+}
+static void sssp_loop(Ctx &c, const Graph &g, const SsspArgs &S, const SsspWork &wk, uint32_t nf) {
+  while (nf) {
+    for (int b = 0; b < WIDE_CHAIN; ++b) sssp_wide(c, g, S, b == 0 ? nf : 0u);
+    nf = sssp_check(c, wk);
+  }
+}
+
 void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, uint32_t nseeds, SsspWork &wk) {
   if (nseeds == 0) return;
-  SsspArgs S{g.in_ptr, g.in_col, g.in_w, labels, {wk.front[0], wk.front[1]}, wk.flag, wk.heavy, wk.st};
-  auto narrow = [&](const uint32_t *s, uint32_t ns, int after_wide) {
-    k_sssp_narrow<<<1, NARROW_T, 0, c.s>>>(S, s, ns, after_wide);
-    FL_LAUNCH_CHECK();
-  };
+  const SsspArgs S = sssp_args(g, labels, wk);
   uint32_t nf = nseeds;
-  auto check = [&]() {
-    c.fetch(wk.st, sizeof(uint32_t));
-    nf = (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-  };
   if (nseeds <= NARROW_V) {
-    narrow(seeds, nseeds, 0);
-    check();
+    sssp_narrow(c, S, seeds, nseeds, SE_SEEDS);
+    nf = sssp_check(c, wk);
   } else {
     FL_HIP(hipMemcpyAsync(wk.front[0], seeds, (size_t)nseeds * 4, hipMemcpyDeviceToDevice, c.s));
     k_sssp_start<<<1, 1, 0, c.s>>>(wk.st, nseeds);
     FL_LAUNCH_CHECK();
   }
-  while (nf) {
-    // a frontier can grow by orders of magnitude within a chain: every launch
-    // gets a grid for any frontier (blocks past the count exit)
-    constexpr int WIDE_CHAIN = 2;
-    const uint32_t blocks = wide_blocks(g.n, nf);
-    for (int b = 0; b < WIDE_CHAIN; ++b) {
-      k_sssp_push<<<blocks, 256, 0, c.s>>>(S);
-      FL_LAUNCH_CHECK();
-      k_sssp_heavy<<<HEAVY_BLOCKS, 256, 0, c.s>>>(S);
-      FL_LAUNCH_CHECK();
-      narrow(nullptr, 0, 1);
-    }
-    check();
-  }
+  sssp_loop(c, g, S, wk, nf);
+}
+
+void sssp_opened(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, const uint32_t *d_nseeds,
+                 const uint32_t *stop, SsspWork &wk) {
+  sssp_narrow(c, sssp_args(g, labels, wk), seeds, 0, SE_OPENED, d_nseeds, stop);
+}
+
+void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, SsspWork &wk, int wide) {
+  const SsspArgs S = sssp_args(g, labels, wk);
+  sssp_narrow(c, S, nullptr, 0, SE_STATE);
+  for (int b = 0; b < wide; ++b) sssp_wide(c, g, S, 0);
 }
 
 }  // namespace fl

@@ -23,11 +23,19 @@
 // Several graphs (a disjoint union) run the loop together: rung t is the same
 // for every graph still running, alpha and the counters are per graph, and a
 // graph leaves the loop when its own stopping rule holds.
+//
+// The loop's control is on the device (k_open_ctl): each graph's counts and
+// flags, the rung, a window of the ladder, whether a look-ahead is due.  The
+// host launches the kernels of several rungs at a time and reads back why they
+// stopped; kernels of rungs after a stop exit at once.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "fl_common.h"
+#include "fl_frontier.h"
 #include "fl_open.h"
 
 namespace fl {
@@ -38,13 +46,35 @@ namespace fl {
 // atomics do not queue on one line
 enum { OC_HEAVY = 0, OC_OPENED, OC_FROZEN, OC_FINITE, OC_NUF_DEC, OC_LIVE, OC_NFIELD };
 
-// per-graph parameters of the current rung
-struct RungParam {
-  double alpha, eps_alpha, ae, a0, a1, rho;
-  uint32_t run;      // the graph evaluates this rung
-  uint32_t frz_prev; // some client of the graph froze in the previous rung
-  uint32_t freeze;   // the freeze kernel runs for the graph (it has open facilities)
-  uint32_t stuck;    // the stall check runs for the graph
+constexpr uint32_t FF_WIN = 256;   // rungs of a look-ahead
+constexpr uint32_t LAD_WIN = 2048; // ladder entries held on the device per graph
+static_assert(LAD_WIN > 2 * FF_WIN, "a window covers several look-aheads");
+
+// a graph in the loop
+struct OpenG {
+  uint32_t nF, nO;           // facilities, opened
+  uint32_t nU, nUF;          // unfrozen served clients, unopened facilities among them
+  uint32_t finite;           // unfrozen clients with a finite distance to the open set
+  uint32_t frz_prev;         // some client froze in the previous rung
+  uint32_t run, done;        // evaluates the current rung; has left the loop
+  uint32_t stuck, gflag;     // the stall check runs; 1: stall guard
+  uint32_t rungs;            // last rung evaluated
+  int32_t rc;
+  double a0, a1;             // first two ladder values
+};
+enum OpenStop : uint32_t {
+  OS_RUN = 0,
+  OS_DONE,   // no graph is left in the loop
+  OS_STUCK,  // a stall check is due
+  OS_SSSP    // the search of the current rung has not ended: the next rung's launches go on with it
+};
+struct OpenCtl {
+  uint32_t stop;
+  uint32_t pending;  // a rung was evaluated and is not closed yet
+  uint32_t ff, t0;   // a look-ahead is due; its first rung
+  uint32_t tev;      // the rung to evaluate (the first with an event)
+  uint32_t base;     // rung of the ladder window's first entry
+  uint32_t heavy_cnt, opened_cnt;
 };
 
 struct OpenArgs {
@@ -52,7 +82,11 @@ struct OpenArgs {
   uint32_t stripes, sstride;
   const uint32_t *gid;        // graph of each vertex (nullptr: one graph)
   const SegInfo *seg;
-  const RungParam *rp;        // [G]
+  uint32_t G;
+  double eps, one_eps;
+  OpenG *og;                  // [G]
+  OpenCtl *ctl;
+  double *win;                // [G * LAD_WIN] ladder values from rung ctl->base on
   const uint32_t *fac_list;
   const uint32_t *fac_cost;   // vertex-indexed
   uint32_t *sk_rank;          // live region holds client ids
@@ -68,11 +102,14 @@ struct OpenArgs {
   double *nhat;
   uint8_t *state;
   uint32_t *heavy;            // [nF]
-  uint32_t *heavy_cnt;        // [1]
   uint32_t *opened;           // [nF] vertex ids opened this rung
-  uint32_t *opened_cnt;       // [1]
   uint32_t *ctr;              // [G * OC_NFIELD * stripes * sstride]
 };
+
+// ladder value of rung t
+__device__ inline double lad_at(const OpenArgs &A, uint32_t g, uint32_t t) {
+  return A.win[(size_t)g * LAD_WIN + (t - A.ctl->base)];
+}
 
 __device__ inline void ctr_add(const OpenArgs &A, uint32_t g, int field, uint32_t v) {
   if (v) atomicAdd(&A.ctr[(((size_t)g * OC_NFIELD + field) * A.stripes + (blockIdx.x % A.stripes)) * A.sstride], v);
@@ -102,17 +139,6 @@ __device__ inline void block_ctr(const OpenArgs &A, int f0, bool v0, int f1, boo
     if (f >= 0) ctr_add(A, 0, f, tot);
   }
   __syncthreads();  // s_c may be reused
-}
-
-// wave-aggregated append of x to list (lanes with want)
-__device__ inline void wave_append(uint32_t *list, uint32_t *count, bool want, uint32_t x) {
-  const uint64_t m = __ballot(want);
-  if (!m) return;
-  const int lead = __ffsll((long long)m) - 1;
-  uint32_t base = 0;
-  if (lane_id() == lead) base = atomicAdd(count, (uint32_t)__popcll(m));
-  base = __shfl(base, lead, WAVE);
-  if (want) list[base + lanes_below(m)] = x;
 }
 
 // Block-aggregated append (every thread of a 256-thread block calls it, in
@@ -153,6 +179,128 @@ __global__ void k_fac_init(OpenArgs A) {
   A.state[i] = 0;
 }
 
+// the ladder window from its first two entries (a[t] = a[t-1] (1 + eps), one
+// rounding each, as the host computes it)
+__global__ void k_ladder_init(OpenArgs A) {
+  const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= A.G) return;
+  double a = A.og[g].a0;
+  for (uint32_t i = 0; i < LAD_WIN; ++i) {
+    A.win[(size_t)g * LAD_WIN + i] = a;
+    a = a * A.one_eps;
+  }
+}
+
+// Between two rungs, by one block: closes the rung that was evaluated (counts
+// and stopping rule of each graph), then opens the next one.  stuck_done: the
+// stall check this kernel asked for has run.
+// With the control on the host a rung was three round trips and some ten small
+// copies and fills, whatever its size (R-MAT 2^18, unit weights, eps 0.01: 118
+// us a rung; opening loop 57 ms, now 27; ER 2,000: 2.3 -> 1.2 ms; a batch of
+// 64 power-law graphs 114 -> 99 ms).
+constexpr uint32_t CTL_T = 256;
+__global__ __launch_bounds__(CTL_T) void k_open_ctl(OpenArgs A, int stuck_done) {
+  __shared__ OpenCtl s;
+  __shared__ uint32_t any_stuck, any_run, any_frz, any_inf, s_f[OC_NFIELD];
+  const uint32_t tid = threadIdx.x;
+  if (tid == 0) {
+    s = *A.ctl;
+    if (stuck_done) s.stop = OS_RUN;
+    any_stuck = any_run = any_frz = any_inf = 0;
+  }
+  __syncthreads();
+  if (s.stop != OS_RUN) return;
+  const uint32_t t0 = s.tev + 1;
+  if (A.stripes > 1) {
+    // one graph: a wave per field sums its stripes, a lane each
+    for (int f = (int)(tid / WAVE); f < OC_NFIELD; f += CTL_T / WAVE) {
+      const uint32_t i = (uint32_t)lane_id();
+      const uint64_t v = wave_sum_u64(i < A.stripes ? A.ctr[((size_t)f * A.stripes + i) * A.sstride] : 0u);
+      if (i == 0) s_f[f] = (uint32_t)v;
+    }
+    __syncthreads();
+  }
+  auto field = [&](uint32_t g, int f) -> uint32_t {
+    return A.stripes > 1 ? s_f[f] : A.ctr[((size_t)g * OC_NFIELD + f) * A.sstride];
+  };
+  for (uint32_t g = tid; g < A.G; g += CTL_T) {
+    OpenG &x = A.og[g];
+    if (s.pending && x.run) {
+      x.nO += field(g, OC_OPENED);
+      x.nU -= field(g, OC_FROZEN);
+      x.nUF -= field(g, OC_NUF_DEC);
+      x.finite = field(g, OC_FINITE);
+      x.frz_prev = field(g, OC_FROZEN) > 0;
+      x.rungs = s.tev;
+      x.run = 0;
+      if (!(x.nO < x.nF && x.nU > 0)) x.done = 1;
+    }
+    if (stuck_done) {
+      // stall guard: no unopened facility sees an unfrozen client
+      if (x.stuck && field(g, OC_LIVE) == 0) {
+        x.gflag |= 1;
+        x.nU = 0;
+        x.done = 1;
+      }
+      x.stuck = 0;
+    } else {
+      // nothing in reach: the stall check
+      x.stuck = !x.done && x.finite == 0 && x.nUF == 0;
+      if (x.stuck) any_stuck = 1;
+    }
+  }
+  __syncthreads();
+  const bool stuck = any_stuck != 0;
+  if (!stuck) {
+    // the ladder window holds rungs t0 .. t0 + FF_WIN + 1 (the next rung's t0)
+    const bool shift = t0 + FF_WIN + 1 >= s.base + LAD_WIN;
+    for (uint32_t g = tid; g < A.G; g += CTL_T) {
+      OpenG &x = A.og[g];
+      double *w = A.win + (size_t)g * LAD_WIN;
+      if (shift) {
+        double a = w[t0 - s.base];
+        for (uint32_t i = 0; i < LAD_WIN; ++i) {
+          w[i] = a;
+          a = a * A.one_eps;
+        }
+      }
+      if (x.done) continue;
+      const uint32_t o = shift ? 0u : t0 - s.base;
+      if (!isfinite(w[o])) {
+        x.rc = FL_ERANGE;
+        x.done = 1;
+        continue;
+      }
+      x.run = 1;
+      any_run = 1;
+      if (x.frz_prev) any_frz = 1;
+      if (!isfinite(w[o + FF_WIN])) any_inf = 1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      if (shift) s.base = t0;
+      if (!any_run) {
+        s.stop = OS_DONE;
+      } else {
+        // skip the quiet rungs before the next event (not the first rung, which
+        // uses Eq. 2, and not right after a freeze, which changes N)
+        s.ff = t0 > 1 && A.nF > 0 && !any_frz && !any_inf;
+        s.t0 = t0;
+        s.tev = s.ff ? t0 + FF_WIN : t0;
+      }
+    }
+  } else if (tid == 0) {
+    s.stop = OS_STUCK;
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < A.G * (uint32_t)OC_NFIELD * A.stripes; i += CTL_T) A.ctr[(size_t)i * A.sstride] = 0;
+  if (tid == 0) {
+    s.pending = s.stop == OS_RUN;
+    s.heavy_cnt = s.opened_cnt = 0;
+    *A.ctl = s;
+  }
+}
+
 // opening test and bookkeeping of a facility that opens at rung t
 __device__ inline bool try_open(const OpenArgs &A, uint32_t fi, uint32_t f, double qn, uint32_t t) {
   if (qn >= (double)A.fac_cost[f]) {
@@ -169,19 +317,32 @@ __device__ inline bool try_open(const OpenArgs &A, uint32_t fi, uint32_t f, doub
 constexpr uint32_t LIGHT_RESCAN = 32;
 
 // 256 threads per block (block_append)
-__global__ __launch_bounds__(256) void k_open_light(OpenArgs A, uint32_t t) {
+__global__ __launch_bounds__(256) void k_open_light(OpenArgs A) {
+  if (A.ctl->stop) return;
+  const uint32_t t = A.ctl->tev, t0 = A.ctl->t0;
   const uint32_t fi = blockIdx.x * blockDim.x + threadIdx.x;
   bool heavy = false, opened = false, nuf = false;
   uint32_t f = 0, g = 0;
   if (fi < A.nF && !A.state[fi]) {
     f = A.fac_list[fi];
     g = seg_of(A.gid, f);
-    const RungParam &R = A.rp[g];
-    if (R.run) {
+    const OpenG &x = A.og[g];
+    if (x.run) {
+      const double alpha = lad_at(A, g, t);
+      double q0 = A.q[fi];
+      if (t > t0) {
+        // the quiet rungs t0 .. t - 1
+        const double nh = A.nhat[fi];
+        for (uint32_t i = t0; i < t; ++i) {
+          const double ea = A.eps * lad_at(A, g, i);
+          q0 = q0 + ea * nh;
+        }
+        A.q[fi] = q0;
+      }
       const uint32_t nx = A.nxt[fi];
       const uint32_t nl = A.nlive[fi];
-      const bool rescan = R.frz_prev && nl > 0;
-      heavy = (nx != INF32 && (double)nx <= R.alpha) || (rescan && nl > LIGHT_RESCAN);
+      const bool rescan = x.frz_prev && nl > 0;
+      heavy = (nx != INF32 && (double)nx <= alpha) || (rescan && nl > LIGHT_RESCAN);
       if (!heavy) {
         double nh = A.nhat[fi];
         if (rescan) {
@@ -217,8 +378,8 @@ __global__ __launch_bounds__(256) void k_open_light(OpenArgs A, uint32_t t) {
         // Eq. 3 with the current estimate (0 when nothing is live; at the
         // first rung nothing is live on this path, and an empty Eq. 2 sum is
         // 0 as well)
-        const double inc = R.eps_alpha * nh;
-        const double qn = A.q[fi] + inc;
+        const double inc = (A.eps * alpha) * nh;
+        const double qn = q0 + inc;
         A.q[fi] = qn;
         opened = try_open(A, fi, f, qn, t);
         nuf = opened && A.ceff[f] && A.frz[f] == FL_RUNG_NONE;
@@ -226,8 +387,8 @@ __global__ __launch_bounds__(256) void k_open_light(OpenArgs A, uint32_t t) {
     }
   }
   // late rungs open facilities in most waves: block-level appends and counts
-  block_append(A.heavy, A.heavy_cnt, heavy, fi);
-  block_append(A.opened, A.opened_cnt, opened, f);
+  block_append(A.heavy, &A.ctl->heavy_cnt, heavy, fi);
+  block_append(A.opened, &A.ctl->opened_cnt, opened, f);
   if (A.gid) {
     if (opened) ctr_add(A, g, OC_OPENED, 1);
     if (nuf) ctr_add(A, g, OC_NUF_DEC, 1);
@@ -253,7 +414,9 @@ __device__ inline uint64_t group_sum_u64(uint64_t x) {
   return x;
 }
 
-__global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
+__global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A) {
+  if (A.ctl->stop) return;
+  const uint32_t t = A.ctl->tev;
   const int lane = lane_id();
   const int sub = lane % OPEN_G;
   const int lead = lane - sub;  // the group's first lane
@@ -262,7 +425,7 @@ __global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
   auto gballot = [&](bool cond) -> uint32_t {
     return (uint32_t)(__ballot(cond) >> lead) & ((1u << OPEN_G) - 1u);
   };
-  const uint32_t nh = *A.heavy_cnt;
+  const uint32_t nh = A.ctl->heavy_cnt;
   constexpr uint32_t GPW = WAVE / OPEN_G;
   const uint64_t h0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE * GPW + (uint64_t)(lane / OPEN_G);
   const uint64_t ng = ((uint64_t)gridDim.x * blockDim.x) / WAVE * GPW;
@@ -270,10 +433,10 @@ __global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
     const uint32_t fi = A.heavy[h];
     const uint32_t f = A.fac_list[fi];
     const uint32_t g = seg_of(A.gid, f);
-    const RungParam &R = A.rp[g];
+    const OpenG &x = A.og[g];
     const RankMap rm = rank_map(A.seg[g]);
-    const double alpha = R.alpha;
-    const int any_freeze_prev = R.frz_prev;
+    const double alpha = lad_at(A, g, t);
+    const uint32_t any_freeze_prev = x.frz_prev;
     const size_t base = (size_t)f * A.cap;
     const size_t trow = (size_t)fi * A.cap;
     const uint32_t c = A.cnt[f];
@@ -356,15 +519,16 @@ __global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
       if (t == 1) {
         // Eq. 2: sum over the live entries, in sketch order, of
         // a_j ((1+eps) alpha - beta(d_j)); beta is a[0] or a[1] here
+        const double ae = A.one_eps * alpha;
         double s = 0.0;
         for (uint32_t i = 0; i < nl; ++i) {
           const double dj = (double)A.sk_dist[base + i];
-          const double b = dj <= R.a0 ? R.a0 : R.a1;
-          s = s + hip_weight(A.thr[trow + i]) * (R.ae - b);
+          const double b = dj <= x.a0 ? x.a0 : x.a1;
+          s = s + hip_weight(A.thr[trow + i]) * (ae - b);
         }
         inc = s;
       } else {
-        inc = R.eps_alpha * nh_;
+        inc = (A.eps * alpha) * nh_;
       }
       A.shi[fi] = shi;
       A.slo[fi] = slo;
@@ -375,7 +539,7 @@ __global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
       const double qn = A.q[fi] + inc;
       A.q[fi] = qn;
       if (try_open(A, fi, f, qn, t)) {
-        const uint32_t p = atomicAdd(A.opened_cnt, 1u);
+        const uint32_t p = atomicAdd(&A.ctl->opened_cnt, 1u);
         A.opened[p] = f;
         ctr_add(A, g, OC_OPENED, 1);
         if (A.ceff[f] && A.frz[f] == FL_RUNG_NONE) ctr_add(A, g, OC_NUF_DEC, 1);
@@ -389,98 +553,103 @@ __global__ __launch_bounds__(256) void k_open_heavy(OpenArgs A, uint32_t t) {
 // facility crosses its next sketch entry, none reaches its cost and no client
 // comes within (1 + eps) alpha of the open set changes nothing but q:
 // q += (eps alpha_t) N for every unopened facility, with N fixed.  The next
-// rung with an event is found on the device and the quiet rungs before it
-// are applied in one pass, in the same floating-point order as rung by rung.
+// rung with an event is found on the device, and the quiet rungs before it
+// are applied by that rung's light kernel, in the same floating-point order as
+// rung by rung.
 // ---------------------------------------------------------------------------
-constexpr uint32_t FF_WIN = 256;  // ladder rungs held on the device per look-ahead
+// rung i of graph g's look-ahead (i < FF_WIN): the first with d <= f * a[t0 + i],
+// or FF_WIN (the ladder does not decrease)
+__device__ inline uint32_t ff_first(const double *a, double d, double f, bool scaled) {
+  uint32_t lo = 0, n = FF_WIN;
+  while (n) {
+    const uint32_t h = n / 2;
+    if (d <= (scaled ? f * a[lo + h] : a[lo + h])) {
+      n = h;
+    } else {
+      lo += h + 1;
+      n -= h + 1;
+    }
+  }
+  return lo;
+}
 
-struct FFArgs {
-  const double *lw;     // [G * FF_WIN] a_g[t0 + i] of running graphs
-  const uint8_t *run;   // [G] the graph is still in the loop
-  uint32_t t0, nw;      // rungs t0 .. t0 + nw - 1
-  double eps, one_eps;
-  uint32_t *tev;        // earliest event rung (atomic min), t0 + nw if none
-};
-
-__global__ __launch_bounds__(256) void k_ff_scan_fac(OpenArgs A, FFArgs F) {
-  const uint32_t fi = blockIdx.x * blockDim.x + threadIdx.x;
-  if (fi >= A.nF || A.state[fi]) return;
-  const uint32_t f = A.fac_list[fi];
-  const uint32_t g = seg_of(A.gid, f);
-  if (!F.run[g]) return;
-  const double *a = F.lw + (size_t)g * FF_WIN;
-  uint32_t ev = F.nw;
-  const uint32_t nx = A.nxt[fi];
-  if (nx != INF32)
-    for (uint32_t i = 0; i < F.nw; ++i)
-      if ((double)nx <= a[i]) {
+// The look-ahead: blocks below fblocks take facilities, the others clients.
+// Only the earliest event counts, so a facility stops adding at the earliest
+// one found so far (read again every FF_CHECK rungs): with every facility
+// going to its own event the scan took 80 us on R-MAT 2^18 and 0.9 ms on 2^22
+// (unit weights).
+constexpr uint32_t FF_CHECK = 8;
+__global__ __launch_bounds__(256) void k_ff_scan(OpenArgs A, uint32_t fblocks, const uint64_t *dlab) {
+  if (A.ctl->stop || !A.ctl->ff) return;
+  const uint32_t t0 = A.ctl->t0;
+  uint32_t *tev = &A.ctl->tev;
+  uint32_t ev = FF_WIN;
+  if (blockIdx.x < fblocks) {
+    const uint32_t fi = blockIdx.x * blockDim.x + threadIdx.x;
+    if (fi >= A.nF || A.state[fi]) return;
+    const uint32_t f = A.fac_list[fi];
+    const uint32_t g = seg_of(A.gid, f);
+    if (!A.og[g].run) return;
+    const double *a = A.win + (size_t)g * LAD_WIN + (t0 - A.ctl->base);
+    const uint32_t nx = A.nxt[fi];
+    if (nx != INF32) ev = ff_first(a, (double)nx, 0.0, false);
+    double q = A.q[fi];
+    const double nh = A.nhat[fi], c = (double)A.fac_cost[f];
+    for (uint32_t i = 0; i < ev; ++i) {
+      if (i % FF_CHECK == 0 && t0 + i >= __hip_atomic_load(tev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+      const double ea = A.eps * a[i];
+      q = q + ea * nh;
+      if (q >= c) {
         ev = i;
         break;
       }
-  double q = A.q[fi];
-  const double nh = A.nhat[fi], c = (double)A.fac_cost[f];
-  for (uint32_t i = 0; i < ev; ++i) {
-    const double ea = F.eps * a[i];
-    q = q + ea * nh;
-    if (q >= c) {
-      ev = i;
-      break;
     }
+  } else {
+    const uint64_t c = (uint64_t)(blockIdx.x - fblocks) * blockDim.x + threadIdx.x;
+    if (c >= A.n || !A.ceff[c] || A.frz[c] != FL_RUNG_NONE) return;
+    const uint64_t L = dlab[c];
+    if (L == INF64) return;
+    const uint32_t g = seg_of(A.gid, (uint32_t)c);
+    if (!A.og[g].run) return;
+    const double *a = A.win + (size_t)g * LAD_WIN + (t0 - A.ctl->base);
+    ev = ff_first(a, (double)(uint32_t)(L >> 32), A.one_eps, true);
   }
-  if (ev < F.nw) atomicMin(F.tev, F.t0 + ev);
+  if (ev < FF_WIN && t0 + ev < __hip_atomic_load(tev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMin(tev, t0 + ev);
 }
 
-__global__ __launch_bounds__(256) void k_ff_scan_cli(OpenArgs A, FFArgs F, const uint64_t *dlab) {
-  const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= A.n || !A.ceff[c] || A.frz[c] != FL_RUNG_NONE) return;
-  const uint32_t g = seg_of(A.gid, (uint32_t)c);
-  if (!F.run[g]) return;
-  const uint64_t L = dlab[c];
-  if (L == INF64) return;
-  const double d = (double)(uint32_t)(L >> 32);
-  const double *a = F.lw + (size_t)g * FF_WIN;
-  for (uint32_t i = 0; i < F.nw; ++i)
-    if (d <= F.one_eps * a[i]) {
-      atomicMin(F.tev, F.t0 + i);
-      return;
-    }
-}
-
-// the quiet rungs t0 .. t0 + nr - 1
-__global__ __launch_bounds__(256) void k_ff_apply(OpenArgs A, FFArgs F, uint32_t nr) {
-  const uint32_t fi = blockIdx.x * blockDim.x + threadIdx.x;
-  if (fi >= A.nF || A.state[fi]) return;
-  const uint32_t g = seg_of(A.gid, A.fac_list[fi]);
-  if (!F.run[g]) return;
-  const double *a = F.lw + (size_t)g * FF_WIN;
-  double q = A.q[fi];
-  const double nh = A.nhat[fi];
-  for (uint32_t i = 0; i < nr; ++i) {
-    const double ea = F.eps * a[i];
-    q = q + ea * nh;
-  }
-  A.q[fi] = q;
-}
-
-// opened facilities become sources at distance 0 (tie = own id)
-__global__ void k_seed_opened(const uint32_t *opened, const uint32_t *cnt, uint64_t *lab) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < *cnt) {
-    const uint32_t f = opened[i];
+// Opened facilities become sources at distance 0 (tie = own id) and the first
+// frontier of the search; for rungs whose searches take wide iterations (the
+// one-block kernel seeds itself otherwise).
+__global__ __launch_bounds__(256) void k_seed_opened(OpenArgs A, uint64_t *lab, SsspWork wk) {
+  if (A.ctl->stop) return;
+  const uint32_t cnt = A.ctl->opened_cnt;
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += stride) {
+    const uint32_t f = A.opened[i];
     lab[f] = (uint64_t)f;
+    wk.front[0][i] = f;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *wk.st = SsspState{cnt, 0u, wk.st->iter, 0u, 0u, wk.st->wide};
 }
 
-__global__ __launch_bounds__(256) void k_freeze(OpenArgs A, const uint64_t *dlab, uint32_t t,
+__global__ __launch_bounds__(256) void k_freeze(OpenArgs A, const uint64_t *dlab, const SsspState *sst,
                                                 const uint32_t *fac_idx) {
+  const uint32_t stop = A.ctl->stop;
+  if (stop != OS_RUN && stop != OS_SSSP) return;
+  // (a block that starts after block 0 has written reads the other of the two
+  // and does the same)
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.ctl->stop = sst->nf ? OS_SSSP : OS_RUN;
+  if (sst->nf) return;  // the search has not ended
+  const uint32_t t = A.ctl->tev;
   const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool froze = false, finite = false, nuf = false;
   uint32_t g = 0;
-  if (c < A.n && A.ceff[c] && A.frz[c] == FL_RUNG_NONE && A.rp[g = seg_of(A.gid, (uint32_t)c)].freeze) {
+  if (c < A.n && A.ceff[c] && A.frz[c] == FL_RUNG_NONE && A.og[g = seg_of(A.gid, (uint32_t)c)].run) {
     const uint64_t L = dlab[c];
     if (L != INF64) {
       const uint32_t d = (uint32_t)(L >> 32);
-      if ((double)d <= A.rp[g].rho) {
+      if ((double)d <= A.one_eps * lad_at(A, g, t)) {
         A.frz[c] = t;
         froze = true;
         const uint32_t fi = fac_idx[c];
@@ -510,7 +679,7 @@ __global__ __launch_bounds__(256) void k_stuck_scan(OpenArgs A) {
   if (fi >= A.nF || A.state[fi]) return;
   const uint32_t f = A.fac_list[fi];
   const uint32_t g = seg_of(A.gid, f);
-  if (!A.rp[g].stuck) return;
+  if (!A.og[g].stuck) return;
   const RankMap rm = rank_map(A.seg[g]);
   const size_t base = (size_t)f * A.cap;
   const uint32_t nl = A.nlive[fi], cur = A.cursor[fi], c = A.cnt[f];
@@ -539,16 +708,6 @@ __global__ void k_endphase(uint32_t n, const uint32_t *gid, const uint8_t *gflag
   if (c < n && (gflag[seg_of(gid, (uint32_t)c)] & 2) && ceff[c] && frz[c] == FL_RUNG_NONE) frz[c] = FL_RUNG_END;
 }
 
-// per-graph sums of the striped counters
-static void read_ctr(Ctx &c, const OpenArgs &A, uint32_t G, std::vector<uint64_t> &out) {
-  std::vector<uint32_t> h((size_t)G * OC_NFIELD * A.stripes * A.sstride);
-  FL_HIP(hipMemcpyAsync(h.data(), A.ctr, h.size() * 4, hipMemcpyDeviceToHost, c.s));
-  c.sync();
-  out.assign((size_t)G * OC_NFIELD, 0);
-  for (size_t i = 0; i < out.size(); ++i)
-    for (uint32_t s = 0; s < A.stripes; ++s) out[i] += h[(i * A.stripes + s) * A.sstride];
-}
-
 int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   const Graph &g = *in.g;
   const uint32_t n = g.n, nF = in.nF, G = in.G;
@@ -558,7 +717,7 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   A.cap = in.ads->cap;
   // one graph: 64 stripes, 32 words (128 B) apart; a union: one plain
   // counter per graph and field (seg_add32 indexes it unstrided)
-  A.stripes = G == 1 ? 64 : 1;
+  A.stripes = G == 1 ? (uint32_t)WAVE : 1;
   A.sstride = G == 1 ? 32 : 1;
   A.gid = in.gid;
   A.seg = in.seg;
@@ -581,19 +740,15 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   A.state = c.arena->get<uint8_t>(nF);
   A.heavy = c.arena->get<uint32_t>(nF);
   A.opened = c.arena->get<uint32_t>(nF);
-  uint32_t *cnts = c.arena->get<uint32_t>(2);
-  A.heavy_cnt = cnts;
-  A.opened_cnt = cnts + 1;
   const size_t ctr_words = (size_t)G * OC_NFIELD * A.stripes * A.sstride;
   A.ctr = c.arena->get<uint32_t>(ctr_words);
-  RungParam *d_rp = c.arena->get<RungParam>(G);
-  A.rp = d_rp;
+  A.G = G;
+  A.eps = in.eps;
+  A.one_eps = 1.0 + in.eps;
+  A.og = c.arena->get<OpenG>(G);
+  A.ctl = c.arena->get<OpenCtl>(1);
+  A.win = c.arena->get<double>((size_t)G * LAD_WIN);
   uint8_t *d_gflag = c.arena->get<uint8_t>(G);
-  double *d_lw = c.arena->get<double>((size_t)G * FF_WIN);
-  uint8_t *d_run = c.arena->get<uint8_t>(G);
-  uint32_t *d_tev = c.arena->get<uint32_t>(1);
-  std::vector<double> h_lw((size_t)G * FF_WIN);
-  std::vector<uint8_t> h_run(G);
   uint64_t *dlab = c.arena->get<uint64_t>(n);
   fill_u64(c, dlab, n, INF64);
   fill_u32(c, out.frz, n, FL_RUNG_NONE);
@@ -605,162 +760,104 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   SsspWork wk;
   sssp_alloc(c, wk, n, g.m);
 
-  const double one_eps = 1.0 + in.eps;
-  // host state per graph
-  std::vector<uint64_t> nO(G, 0), nU(in.nCeff), nUF(in.nUF0), finite_unfrozen(G, 0);
-  std::vector<uint8_t> frz_prev(G, 0), done(G, 0), gflag(G, 0);
-  std::vector<RungParam> rp(G);
-  out.rungs.assign(G, 0);
-  out.rc.assign(G, FL_OK);
-  for (uint32_t q = 0; q < G; ++q) done[q] = !(nO[q] < in.nF_g[q] && nU[q] > 0);
-  uint32_t t = 0;
+  std::vector<OpenG> og(G);
+  for (uint32_t q = 0; q < G; ++q) {
+    OpenG &x = og[q];
+    x = OpenG{};
+    x.nF = (uint32_t)in.nF_g[q];
+    x.nU = (uint32_t)in.nCeff[q];
+    x.nUF = (uint32_t)in.nUF0[q];
+    x.done = !(x.nF > 0 && x.nU > 0);
+    x.a0 = (*in.lad)[q][0];
+    x.a1 = (*in.lad)[q][1];
+  }
+  FL_HIP(hipMemcpyAsync(A.og, og.data(), G * sizeof(OpenG), hipMemcpyHostToDevice, c.s));
+  fill_u32(c, reinterpret_cast<uint32_t *>(A.ctl), sizeof(OpenCtl) / 4, 0);
+  fill_u32(c, A.ctr, ctr_words, 0);
+  k_ladder_init<<<(uint32_t)ceil_div(G, 64), 64, 0, c.s>>>(A);
+  FL_LAUNCH_CHECK();
   const uint32_t fblocks = (uint32_t)ceil_div(nF ? nF : 1, 256);
-  const uint32_t hblocks = (uint32_t)std::min<uint64_t>(ceil_div((uint64_t)(nF ? nF : 1) * WAVE, 256), 4096);
+  const uint32_t hblocks = (uint32_t)std::min<uint64_t>(ceil_div((uint64_t)(nF ? nF : 1) * OPEN_G, 256), 4096);
   const uint32_t vblocks = (uint32_t)ceil_div(n, 256);
-  std::vector<uint64_t> ctr;
-  auto upload = [&]() {
-    FL_HIP(hipMemcpyAsync(d_rp, rp.data(), G * sizeof(RungParam), hipMemcpyHostToDevice, c.s));
+  auto ctl = [&](int stuck_done) {
+    k_open_ctl<<<1, CTL_T, 0, c.s>>>(A, stuck_done);
+    FL_LAUNCH_CHECK();
   };
-  for (;;) {
-    // stall check for the running graphs with nothing in reach
-    bool any_stuck = false;
-    for (uint32_t q = 0; q < G; ++q) {
-      rp[q] = RungParam{};
-      rp[q].stuck = !done[q] && finite_unfrozen[q] == 0 && nUF[q] == 0;
-      any_stuck |= rp[q].stuck != 0;
+  auto freeze = [&]() {
+    k_freeze<<<vblocks, 256, 0, c.s>>>(A, dlab, wk.st, in.fac_idx);
+    FL_LAUNCH_CHECK();
+  };
+  // the rest of a rung that k_open_ctl opened; wide: iterations of the search
+  // launched for frontiers beyond one block.  A search that needs more goes on
+  // in the launches of the next rung, whose other kernels exit.
+  auto rung = [&](int wide) {
+    k_ff_scan<<<fblocks + vblocks, 256, 0, c.s>>>(A, fblocks, dlab);
+    FL_LAUNCH_CHECK();
+    k_open_light<<<fblocks, 256, 0, c.s>>>(A);
+    FL_LAUNCH_CHECK();
+    k_open_heavy<<<hblocks, 256, 0, c.s>>>(A);
+    FL_LAUNCH_CHECK();
+    if (wide) {
+      k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
+      FL_LAUNCH_CHECK();
+      sssp_chain(c, g, dlab, wk, wide);
+    } else {
+      sssp_opened(c, g, dlab, A.opened, &A.ctl->opened_cnt, &A.ctl->stop, wk);
     }
-    if (any_stuck) {
-      upload();
-      fill_u32(c, A.ctr, ctr_words, 0);
+    freeze();
+  };
+  // Rungs are launched OPEN_CHUNK at a time, with wide iterations as long as a
+  // fair share of a chunk's rungs took some.
+  constexpr uint32_t OPEN_CHUNK = 8;
+  constexpr int OPEN_WIDE = 2;
+  OpenCtl st{};
+  SsspState sst{};
+  uint32_t wide_seen = 0;
+  int wide = nF > NARROW_V ? OPEN_WIDE : 0;
+  for (;;) {
+    for (uint32_t r = 0; r < OPEN_CHUNK; ++r) {
+      ctl(0);
+      rung(wide);
+    }
+    FL_HIP(hipMemcpyAsync(c.h_status, A.ctl, sizeof(OpenCtl), hipMemcpyDeviceToHost, c.s));
+    FL_HIP(hipMemcpyAsync(c.h_status + 64, wk.st, sizeof(SsspState), hipMemcpyDeviceToHost, c.s));
+    c.sync();
+    std::memcpy(&st, c.h_status, sizeof(OpenCtl));
+    std::memcpy(&sst, c.h_status + 64, sizeof(SsspState));
+    if (st.stop == OS_DONE) break;
+    if (st.stop == OS_STUCK) {
       k_stuck_scan<<<(uint32_t)ceil_div((uint64_t)(nF ? nF : 1) * WAVE, 256), 256, 0, c.s>>>(A);
       FL_LAUNCH_CHECK();
-      read_ctr(c, A, G, ctr);
-      for (uint32_t q = 0; q < G; ++q)
-        if (rp[q].stuck && ctr[(size_t)q * OC_NFIELD + OC_LIVE] == 0) {
-          gflag[q] |= 1;  // stall guard
-          nU[q] = 0;
-          done[q] = 1;
-        }
-    }
-    bool any = false;
-    for (uint32_t q = 0; q < G; ++q) any |= !done[q];
-    if (!any) break;
-    // skip the quiet rungs before the next event (not the first rung, which
-    // uses Eq. 2, and not right after a freeze, which changes N)
-    bool can_ff = t >= 1 && nF > 0;
-    bool any_open = false;
-    for (uint32_t q = 0; q < G && can_ff; ++q) {
-      if (done[q]) continue;
-      can_ff = !frz_prev[q];
-      any_open |= nO[q] > 0;
-    }
-    if (can_ff) {
-      const uint32_t t0 = t + 1;
-      for (uint32_t q = 0; q < G && can_ff; ++q) {
-        h_run[q] = !done[q];
-        std::vector<double> &lad = (*in.lad)[q];
-        if (!h_run[q]) continue;
-        while (lad.size() < (size_t)t0 + FF_WIN) lad.push_back(lad.back() * one_eps);
-        for (uint32_t i = 0; i < FF_WIN; ++i) {
-          const double a = lad[t0 + i];
-          if (!std::isfinite(a)) can_ff = false;  // the rung loop reports the overflow
-          h_lw[(size_t)q * FF_WIN + i] = a;
-        }
-      }
-      if (can_ff) {
-        FL_HIP(hipMemcpyAsync(d_lw, h_lw.data(), h_lw.size() * 8, hipMemcpyHostToDevice, c.s));
-        FL_HIP(hipMemcpyAsync(d_run, h_run.data(), G, hipMemcpyHostToDevice, c.s));
-        fill_u32(c, d_tev, 1, t0 + FF_WIN);
-        FFArgs F{d_lw, d_run, t0, FF_WIN, in.eps, one_eps, d_tev};
-        k_ff_scan_fac<<<fblocks, 256, 0, c.s>>>(A, F);
-        FL_LAUNCH_CHECK();
-        if (any_open) {
-          k_ff_scan_cli<<<vblocks, 256, 0, c.s>>>(A, F, dlab);
-          FL_LAUNCH_CHECK();
-        }
-        FL_HIP(hipMemcpyAsync(c.h_status, d_tev, 4, hipMemcpyDeviceToHost, c.s));
-        c.sync();
-        const uint32_t tev = (uint32_t)(c.h_status[0] & 0xFFFFFFFFu);
-        if (tev > t0) {
-          k_ff_apply<<<fblocks, 256, 0, c.s>>>(A, F, tev - t0);
-          FL_LAUNCH_CHECK();
-          t = tev - 1;
-          for (uint32_t q = 0; q < G; ++q)
-            if (!done[q]) out.rungs[q] = t;
-        }
-      }
-    }
-    ++t;
-    for (uint32_t q = 0; q < G; ++q) {
-      RungParam &R = rp[q];
-      R = RungParam{};
-      if (done[q]) continue;
-      std::vector<double> &lad = (*in.lad)[q];
-      while (lad.size() <= t) lad.push_back(lad.back() * one_eps);
-      const double alpha = lad[t];
-      if (!std::isfinite(alpha)) {
-        out.rc[q] = FL_ERANGE;
-        done[q] = 1;
-        continue;
-      }
-      R.alpha = alpha;
-      R.eps_alpha = in.eps * alpha;
-      R.ae = one_eps * alpha;
-      R.a0 = lad[0];
-      R.a1 = lad[1];
-      R.rho = one_eps * alpha;
-      R.run = 1;
-      R.frz_prev = frz_prev[q];
-      out.rungs[q] = t;
-    }
-    upload();
-    fill_u32(c, cnts, 2, 0);
-    fill_u32(c, A.ctr, ctr_words, 0);
-    k_open_light<<<fblocks, 256, 0, c.s>>>(A, t);
-    FL_LAUNCH_CHECK();
-    k_open_heavy<<<hblocks, 256, 0, c.s>>>(A, t);
-    FL_LAUNCH_CHECK();
-    read_ctr(c, A, G, ctr);
-    uint64_t opened = 0;
-    bool any_freeze = false;
-    for (uint32_t q = 0; q < G; ++q) {
-      if (!rp[q].run) continue;
-      const uint64_t o = ctr[(size_t)q * OC_NFIELD + OC_OPENED];
-      opened += o;
-      nO[q] += o;
-      nUF[q] -= ctr[(size_t)q * OC_NFIELD + OC_NUF_DEC];
-      frz_prev[q] = 0;
-      rp[q].freeze = nO[q] > 0;
-      any_freeze |= rp[q].freeze != 0;
-    }
-    if (opened) {
-      k_seed_opened<<<(uint32_t)ceil_div(opened, 256), 256, 0, c.s>>>(A.opened, A.opened_cnt, dlab);
+      ctl(1);
+      rung(wide);
+    } else if (st.stop == OS_SSSP && !wide && st.opened_cnt > NARROW_V) {
+      // the one-block kernel left these seeds to the wide form
+      fill_u32(c, &A.ctl->stop, 1, OS_RUN);
+      k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
       FL_LAUNCH_CHECK();
-      sssp_run(c, g, dlab, A.opened, (uint32_t)opened, wk);
+      fill_u32(c, &A.ctl->stop, 1, OS_SSSP);
     }
-    if (any_freeze) {
-      upload();
-      fill_u32(c, A.ctr, ctr_words, 0);
-      k_freeze<<<vblocks, 256, 0, c.s>>>(A, dlab, t, in.fac_idx);
-      FL_LAUNCH_CHECK();
-      read_ctr(c, A, G, ctr);
-      for (uint32_t q = 0; q < G; ++q) {
-        if (!rp[q].freeze) continue;
-        const uint64_t *cq = &ctr[(size_t)q * OC_NFIELD];
-        nU[q] -= cq[OC_FROZEN];
-        nUF[q] -= cq[OC_NUF_DEC];
-        finite_unfrozen[q] = cq[OC_FINITE];
-        frz_prev[q] = cq[OC_FROZEN] > 0;
-      }
-    }
-    for (uint32_t q = 0; q < G; ++q)
-      if (rp[q].run && !(nO[q] < in.nF_g[q] && nU[q] > 0)) done[q] = 1;
+    wide = st.stop == OS_SSSP || sst.wide - wide_seen >= OPEN_CHUNK / 4 ? OPEN_WIDE : 0;
+    wide_seen = sst.wide;
   }
-  out.nO = nO;
+  FL_HIP(hipMemcpyAsync(og.data(), A.og, G * sizeof(OpenG), hipMemcpyDeviceToHost, c.s));
+  c.sync();
+  out.rungs.resize(G);
+  out.rc.resize(G);
+  out.nO.resize(G);
+  std::vector<uint8_t> gflag(G, 0);
   bool any_flag = false;
   for (uint32_t q = 0; q < G; ++q) {
-    if (nO[q] == in.nF_g[q] && nU[q] > 0 && out.rc[q] == FL_OK) gflag[q] |= 2;  // end phase
+    out.rungs[q] = og[q].rungs;
+    out.rc[q] = og[q].rc;
+    out.nO[q] = og[q].nO;
+    gflag[q] = (uint8_t)og[q].gflag;
+    // end phase
+    if (og[q].nO == og[q].nF && og[q].nU > 0 && og[q].rc == FL_OK) gflag[q] |= 2;
     any_flag |= gflag[q] != 0;
+    // the host's ladder reaches every rung evaluated (the radii of the selection)
+    std::vector<double> &lad = (*in.lad)[q];
+    while (lad.size() <= og[q].rungs) lad.push_back(lad.back() * A.one_eps);
   }
   if (any_flag) {
     FL_HIP(hipMemcpyAsync(d_gflag, gflag.data(), G, hipMemcpyHostToDevice, c.s));
