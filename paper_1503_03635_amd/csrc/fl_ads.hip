@@ -234,6 +234,46 @@ __device__ inline void wave_sort_lds(uint32_t *s, uint32_t n) {
   }
 }
 
+// Sort the distinct ranks s[0..n), none above `most`, ascending in place (tmp:
+// n words, s_b: WAVE words).  A counting sort into 64 buckets, four to each
+// octave below `most`, then each rank's place among its bucket's.  A level's
+// accepted ranks are about as many in every octave above the bottom-k's, so a
+// bucket holds some ten of a few hundred: a tenth of the instructions of a
+// bitonic network over LDS, and a few waits instead of 45 (levels of more than
+// 64 ids, 314 on average on R-MAT 2^22, unit, k = 64: with the copies dropped
+// from large buckets, round kernels 540 -> 514 ms).
+__device__ inline void wave_sort_ranks(uint32_t *s, uint32_t *tmp, uint32_t n, uint32_t most, uint32_t *s_b) {
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t z0 = (uint32_t)__clz((int)(most | 1u));
+  auto bucket = [&](uint32_t r) -> uint32_t {
+    const uint32_t x = r | 1u, z = (uint32_t)__clz((int)x);
+    const uint32_t o = z - z0;  // octaves below `most`
+    return o > 15u ? 0u : 60u - 4u * o + ((x << z) >> 29 & 3u);
+  };
+  s_b[lane] = 0;
+  wave_lds_sync();
+  for (uint32_t i = lane; i < n; i += WAVE) atomicAdd(&s_b[bucket(s[i])], 1u);
+  wave_lds_sync();
+  const uint32_t c = s_b[lane];
+  const uint32_t st = wave_scan_incl(c) - c;
+  wave_lds_sync();
+  s_b[lane] = st;
+  wave_lds_sync();
+  for (uint32_t i = lane; i < n; i += WAVE) {
+    const uint32_t r = s[i];
+    tmp[atomicAdd(&s_b[bucket(r)], 1u)] = r;
+  }
+  wave_lds_sync();
+  for (uint32_t i = lane; i < n; i += WAVE) {
+    const uint32_t r = tmp[i], b = bucket(r);
+    const uint32_t b0 = b ? s_b[b - 1] : 0u, b1 = s_b[b];  // s_b[b] is the bucket's end now
+    uint32_t at = b0;
+    for (uint32_t j = b0; j < b1; ++j) at += tmp[j] < r ? 1u : 0u;
+    s[at] = r;
+  }
+  wave_lds_sync();
+}
+
 // Sort one value per lane ascending across the wave (bitonic network).
 __device__ inline uint32_t wave_sort_reg(uint32_t x) {
   const int lane = lane_id();
@@ -402,10 +442,8 @@ __device__ inline uint64_t chunk_accept(uint32_t id, uint32_t k, const RankMap &
   bool valid = id != INF32 && id != left;
   const uint32_t r = valid ? rank_of(id, rm) : INF32;
   const uint32_t q = kset_below(set, r);
-  // a candidate already in the set (same vertex at a shorter distance) is
-  // not new; one that dropped out of the set is rejected by the count
-  const uint32_t atq = kset_at(set, q < 64u * KR - 1u ? q : 64u * KR - 1u);
-  if (q < nset && atq == r) valid = false;
+  // (none is in the set at the level's start, the offers saw to that, and a
+  // repeated id is next to its first)
   // one with k set elements below it is rejected, and so is any it could count
   // for: only those below the set's k-th rank remain
   if (q >= k) valid = false;
@@ -432,7 +470,7 @@ __device__ inline uint64_t chunk_accept(uint32_t id, uint32_t k, const RankMap &
   return am;
 }
 
-// Prune of one distance level.  s_id[0..ns) holds candidate ids (unsorted,
+// Prune of one distance level.  s_id[0..ns) holds candidate ranks (unsorted,
 // duplicates allowed); set/nset the running set.  Accepted ids end in
 // s_tmp[0..m) in increasing id order; returns m.  s_id is clobbered.
 // s_cnt holds (2 + KR) WAVE words: [0, WAVE) bucket offsets, then the
@@ -450,7 +488,7 @@ __device__ inline uint32_t prune_level(uint32_t *s_id, uint32_t *s_tmp, uint32_t
   uint32_t *s_r = s_cnt + (1 + KR) * WAVE;
   uint32_t m = 0, prev = INF32;
   if (ns <= (uint32_t)WAVE && !tbk) {
-    uint32_t x = (uint32_t)lane < ns ? s_id[lane] : INF32;
+    uint32_t x = (uint32_t)lane < ns ? id_of(s_id[lane], rm) : INF32;
     x = ns <= COUNT_SORT_MAX ? wave_sort_few(x, ns, s_r) : wave_sort_reg(x);
     const uint64_t am = chunk_accept(x, k, rm, set, nset, prev, s_r);
     if ((am >> lane) & 1) s_tmp[lanes_below(am)] = x;
@@ -460,7 +498,11 @@ __device__ inline uint32_t prune_level(uint32_t *s_id, uint32_t *s_tmp, uint32_t
   // counting sort by id bucket (bucket order is id order)
   s_cnt[lane] = 0;
   wave_lds_sync();
-  for (uint32_t i = lane; i < ns; i += WAVE) atomicAdd(&s_cnt[bucket_of(s_id[i], rm)], 1u);
+  for (uint32_t i = lane; i < ns; i += WAVE) {
+    const uint32_t id = id_of(s_id[i], rm);
+    s_id[i] = id;
+    atomicAdd(&s_cnt[bucket_of(id, rm)], 1u);
+  }
   wave_lds_sync();
   const uint32_t bc = s_cnt[lane];
   const uint32_t bstart = wave_scan_incl(bc) - bc;
@@ -523,8 +565,13 @@ __device__ inline uint32_t prune_level(uint32_t *s_id, uint32_t *s_tmp, uint32_t
         for (uint32_t j0 = 0; j0 < cb; j0 += WAVE) {
           const uint32_t id = j0 + lane < cb ? s_tmp[sb + j0 + lane] : INF32;
           const bool pass = j0 + lane < cb && (open || rank_of(id, rm) < T);
-          const uint64_t pm = __ballot(pass);
-          if (pass) s_tmp[sb + cnt + lanes_below(pm)] = id;
+          // most of a large bucket are copies of a few ids (a vertex reaches u
+          // over many arcs): each 64 keep one of each
+          const uint32_t x = wave_sort_reg(pass ? id : INF32);
+          const uint32_t left = __shfl_up(x, 1, WAVE);
+          const bool keep = x != INF32 && (lane == 0 || x != left);
+          const uint64_t pm = __ballot(keep);
+          if (keep) s_tmp[sb + cnt + lanes_below(pm)] = x;
           cnt += (uint32_t)__popcll(pm);
         }
         wave_lds_sync();
@@ -635,23 +682,31 @@ __device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, u
       if (s_set0[lo + s - 1] < r) lo += s;
     if (lo < L.nset0 && s_set0[lo] == r) pass = false;
   }
-  // bucket bound from the last prune: all candidates of earlier id buckets
-  // come first, and k of them (or of the set) already rank below it
-  const uint32_t cid = pass ? id_of(r, L.rm) : L.rm.base;
-  const uint32_t bnd = __shfl(L.tb, (int)bucket_of(cid, L.rm), WAVE);
-  if (pass && r >= bnd) pass = false;
+  // Bucket bound from the last prune: all candidates of earlier id buckets
+  // come first, and k of them (or of the set) already rank below it.  Until
+  // there has been one the bound is T0, and the candidate's id is not needed:
+  // the buffer holds ranks, and a prune turns all of them into ids, 64 at a
+  // time, where an offer would do so for the 20 or so lanes that pass (round
+  // kernels of R-MAT 2^22, unit, k = 64: 545 -> 540 ms).
+  uint32_t bkt = 0;
+  if (L.nprune) {
+    bkt = bucket_of(pass ? id_of(r, L.rm) : L.rm.base, L.rm);
+    const uint32_t bnd = __shfl(L.tb, (int)bkt, WAVE);
+    if (pass && r >= bnd) pass = false;
+  }
   uint64_t msk = __ballot(pass);
   if (!msk) return;
   uint32_t np = (uint32_t)__popcll(msk);
   if (L.ns + np > SB) {
     KSet<KR> tv = L.set0;
     uint32_t tn = L.nset0;
+    if (!L.nprune) bkt = bucket_of(pass ? id_of(r, L.rm) : L.rm.base, L.rm);
     ++L.nprune;
     L.ns = prune_level(s_id, s_tmp, s_cnt, L.ns, P.k, L.rm, tv, tn, &L.tb);
-    for (uint32_t i = lane; i < L.ns; i += WAVE) s_id[i] = s_tmp[i];
+    for (uint32_t i = lane; i < L.ns; i += WAVE) s_id[i] = rank_of(s_tmp[i], L.rm);
     wave_lds_sync();
     // the new bounds may reject some of this chunk too
-    const uint32_t bnd2 = __shfl(L.tb, (int)bucket_of(cid, L.rm), WAVE);
+    const uint32_t bnd2 = __shfl(L.tb, (int)bkt, WAVE);
     if (pass && r >= bnd2) pass = false;
     msk = __ballot(pass);
     np = (uint32_t)__popcll(msk);
@@ -660,7 +715,7 @@ __device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, u
       return;
     }
   }
-  if (pass) s_id[L.ns + lanes_below(msk)] = cid;
+  if (pass) s_id[L.ns + lanes_below(msk)] = r;
   L.ns += np;
   L.nsurv += np;
   wave_lds_sync();
@@ -692,7 +747,8 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
           r0 = rec.y;
           r1 = rec.z;
           st = rec.w & 0xFFFFu;
-          cn = rec.w >> 16;
+          // (one whose second smallest is not has one entry for u)
+          cn = L.full0 && r1 >= L.T0 ? 1u : rec.w >> 16;
         }
       }
     }
@@ -861,7 +917,8 @@ __device__ inline bool level_commit(const AdsArgs &P, uint32_t u, uint32_t D, Le
     x1 = __shfl(x, 1, WAVE);
   } else {
     for (uint32_t i = lane; i < m; i += WAVE) s_id[i] = rank_of(s_tmp[i], L.rm);
-    wave_sort_lds(s_id, m);  // m <= SB
+    wave_lds_sync();
+    wave_sort_ranks(s_id, s_tmp, m, L.T0, s_cnt);
     for (uint32_t i = lane; i < m; i += WAVE) {
       P.sk_rank[base + i] = s_id[i];
       P.sk_dist[base + i] = D;
@@ -1084,7 +1141,7 @@ void k_ads_pairs(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
             r0 = rec.y;
             r1 = rec.z;
             st = rec.w & 0xFFFFu;
-            cn = rec.w >> 16;
+            cn = full0 && r1 >= T0 ? 1u : rec.w >> 16;  // a second entry not below T0 ends the list
           }
         }
       }
