@@ -76,6 +76,17 @@ static_assert(TASK_ARCS_SPARSE >= TASK_ARCS, "scratch slots are sized for TASK_A
 // follows those, not its length: rows are cut far less often.
 constexpr uint32_t TASK_ARCS_FLAGGED = 8192;
 static_assert(TASK_ARCS_FLAGGED >= TASK_ARCS, "scratch slots are sized for TASK_ARCS");
+// A vertex that is new to u at this level arrives over every arc whose tail
+// holds it, hundreds of times for the lowest ranks, and until the next prune
+// each copy passes the offer's other filters.  The last rank buffered under
+// each low-bits key is kept (no atomics: a lost entry only lets a copy pass).
+// Round kernels of R-MAT 2^22 (unit, k = 64): 514 ms without, 467 with 128 keys,
+// 440 with 256, 467 with 512 (LDS for fewer waves then); 2^18 at k = 128: 85, 78
+// with 128 keys, 82 with 256.  (The two-task kernel's levels are small: there 64
+// keys per task cost 224 -> 248 ms on R-MAT 2^21, weights 1..100, and are not
+// kept.)
+constexpr uint32_t seen_keys(int KR) { return KR == 1 ? 256 : 128; }
+constexpr uint32_t level_words(int KR) { return (2 + KR) * WAVE + seen_keys(KR); }  // s_cnt of the round kernels
 constexpr uint32_t NBKT = 64;       // id buckets of the level prune (one per lane)
 constexpr uint32_t LONG_LIST = 64;  // entry lists at least this long are streamed one arc at a time
 
@@ -473,9 +484,9 @@ __device__ inline uint64_t chunk_accept(uint32_t id, uint32_t k, const RankMap &
 // Prune of one distance level.  s_id[0..ns) holds candidate ranks (unsorted,
 // duplicates allowed); set/nset the running set.  Accepted ids end in
 // s_tmp[0..m) in increasing id order; returns m.  s_id is clobbered.
-// s_cnt holds (2 + KR) WAVE words: [0, WAVE) bucket offsets, then the
-// pending chunk; [WAVE, (1 + KR) WAVE) belongs to the caller; the last WAVE
-// hold chunk ranks.
+// s_cnt holds level_words(KR) words: [0, WAVE) bucket offsets, then the
+// pending chunk; [WAVE, (1 + KR) WAVE) belongs to the caller; the next WAVE
+// hold chunk ranks, the rest is the caller's.
 // With tbk, lane b of *tbk receives a rank bound for id bucket b: the running
 // k-th smallest rank when the bucket was reached, which no later candidate of
 // that bucket can beat.
@@ -652,6 +663,7 @@ __device__ inline void level_init(const AdsArgs &P, uint32_t u, Level<KR> &L, ui
     L.set0.v[g] = e < L.nset0 ? P.bk[(size_t)u * k + e] : INF32;
     s_cnt[WAVE + e] = L.set0.v[g];
   }
+  for (uint32_t i = lane; i < seen_keys(KR); i += WAVE) s_cnt[(2 + KR) * WAVE + i] = INF32;
   wave_lds_sync();
   L.full0 = L.nset0 == k;
   L.T0 = L.full0 ? kset_at(L.set0, k - 1) : INF32;
@@ -668,6 +680,7 @@ template <int KR, uint32_t SB>
 __device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, uint32_t r, uint32_t *s_id,
                                    uint32_t *s_tmp, uint32_t *s_cnt) {
   const uint32_t *s_set0 = s_cnt + WAVE;  // LDS copy of the set at the level start
+  uint32_t *s_seen = s_cnt + (2 + KR) * WAVE;
   const int lane = lane_id();
   bool pass = valid && (!L.full0 || r < L.T0);
   if (!__ballot(pass)) return;
@@ -676,11 +689,13 @@ __device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, u
     // fixed length over the padded set, without branches: a loop that each
     // lane leaves at its own step cost more (round kernels of R-MAT 2^22, k =
     // 64: 743 -> 703 ms)
+    const uint32_t seen = s_seen[r % seen_keys(KR)];
     uint32_t lo = 0;
 #pragma unroll
     for (uint32_t s = 32 * KR; s >= 1; s >>= 1)
       if (s_set0[lo + s - 1] < r) lo += s;
     if (lo < L.nset0 && s_set0[lo] == r) pass = false;
+    if (seen == r && r != INF32) pass = false;  // buffered in this level already
   }
   // Bucket bound from the last prune: all candidates of earlier id buckets
   // come first, and k of them (or of the set) already rank below it.  Until
@@ -715,7 +730,10 @@ __device__ inline void level_offer(const AdsArgs &P, Level<KR> &L, bool valid, u
       return;
     }
   }
-  if (pass) s_id[L.ns + lanes_below(msk)] = r;
+  if (pass) {
+    s_id[L.ns + lanes_below(msk)] = r;
+    s_seen[r % seen_keys(KR)] = r;
+  }
   L.ns += np;
   L.nsurv += np;
   wave_lds_sync();
@@ -1464,7 +1482,7 @@ void k_ads_tasks(AdsArgs P, uint32_t D, const uint32_t *task_u, const uint32_t *
                  const uint32_t *left, uint64_t *ts) {
   __shared__ uint32_t lds_id[TASK_WPB][SB];
   __shared__ uint32_t lds_tmp[TASK_WPB][SB];
-  __shared__ __align__(16) uint32_t lds_cnt[TASK_WPB][(2 + KR) * WAVE];
+  __shared__ __align__(16) uint32_t lds_cnt[TASK_WPB][level_words(KR)];
   const int wv = threadIdx.x / WAVE;
   const uint64_t total = tot ? (left ? tot->left : tot->tasks) : ntasks;
   if (ts && blockIdx.x == 0 && threadIdx.x == 0) *ts = wall_clock64();
@@ -1489,7 +1507,7 @@ __global__ __launch_bounds__(MERGE_WPB * WAVE) void k_ads_merge(AdsArgs P, uint3
   constexpr uint32_t NW = MERGE_WPB - 1;  // waves that build partial sets
   __shared__ uint32_t lds_id[MERGE_WPB][SB];
   __shared__ uint32_t lds_tmp[MERGE_WPB][SB];
-  __shared__ __align__(16) uint32_t lds_cnt[MERGE_WPB][(2 + KR) * WAVE];
+  __shared__ __align__(16) uint32_t lds_cnt[MERGE_WPB][level_words(KR)];
   __shared__ uint32_t part_n[MERGE_WPB];
   __shared__ uint32_t s_mark;  // the item committed a level: its out-arcs are marked
   const int lane = lane_id();
