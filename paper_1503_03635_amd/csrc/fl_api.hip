@@ -671,7 +671,9 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
   // ---- MIS per rung (Sec. 4.3, Alg. 6)
   MisIn mi{&g, G, gid, seg, oo.rungs, &lad, eps, orung, frz, (flags & FL_FLAG_LUBY_MIS) != 0};
   std::vector<uint32_t> mis_rounds;
+  const size_t mis_mark = c.arena->used();
   rc = mis_phase(c, mi, open_u, mis_rounds);
+  c.arena->rewind(mis_mark);
   if (rc) {
     for (auto &r : rc_out) r = rc;
     return;
