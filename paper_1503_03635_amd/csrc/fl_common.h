@@ -286,6 +286,50 @@ __device__ inline void wave_push(uint32_t *list, uint32_t *count, bool want, uin
   base = __shfl(base, lead, WAVE);
   if (want) list[base + lanes_below(m)] = x;
 }
+// The arcs [b, c1) of a CSR, 64 at a time, with their tails: f(valid, arc,
+// tail), every lane calls, converged.  Ranges of equal length go to the waves
+// of a launch, whatever the rows' lengths: with a wave per row the launch ends
+// with one wave in the longest row.  Any row_ptr[0..n] is safe: a tail is
+// below n, and only an ascending row_ptr gives every arc its own.
+template <class F>
+__device__ inline void wave_arcs(uint64_t n, const uint64_t *row_ptr, uint64_t b, uint64_t c1, F &&f) {
+  const uint32_t lane = (uint32_t)lane_id();
+  if (b >= c1) return;
+  uint64_t r = 0, hi = n;  // the last row that starts at or before b, 64 probes a turn
+  while (hi - r > 1) {
+    const uint64_t step = (hi - r + WAVE - 1) / WAVE, p = r + lane * step;
+    const uint32_t c = (uint32_t)__popcll(__ballot(p < hi && row_ptr[p] <= b));
+    r += (c > 1 ? c - 1 : 0u) * step;
+    hi = r + step < hi ? r + step : hi;
+  }
+  while (b < c1 && r < n) {
+    const uint64_t i = r + 1 + lane;
+    const uint64_t e = i <= n ? row_ptr[i] : ~0ull;  // ends of 64 rows
+    const uint64_t last = shfl_u64(e, WAVE - 1);
+    if (last <= b) {
+      r += WAVE;
+      continue;
+    }
+    uint64_t end = b + WAVE < c1 ? b + WAVE : c1;
+    end = end < last ? end : last;
+    const uint32_t rel = e <= b ? 0u : e - b < (uint64_t)WAVE ? (uint32_t)(e - b) : (uint32_t)WAVE;
+    uint32_t pos = 0;  // rows that end at or before this lane's arc
+#pragma unroll
+    for (uint32_t s = WAVE / 2; s >= 1; s >>= 1)
+      if ((uint32_t)__shfl(rel, (int)(pos + s - 1), WAVE) <= lane) pos += s;
+    f(b + lane < end && r + pos < n, b + lane, (uint32_t)(r + pos));
+    r += (uint32_t)__popcll(__ballot(e <= end));
+    b = end;
+  }
+}
+// this wave's range of m arcs among the waves of the launch: whole groups of 64
+__device__ inline void wave_range(uint64_t m, uint64_t *b0, uint64_t *b1) {
+  const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / WAVE);
+  const uint64_t wv = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+  const uint64_t len = (m / WAVE + nw) / nw * WAVE;
+  *b0 = wv * len < m ? wv * len : m;
+  *b1 = *b0 + len < m ? *b0 + len : m;
+}
 // Frontier expansion: rows up to FLAT_MAX arcs are flattened over the wave
 // (step c takes arcs c*64 .. c*64+63 of the concatenated rows, each lane
 // finding its row by binary search over the running degree sum); longer rows

@@ -1,7 +1,8 @@
-"""GPU: MIS sweeps over rows in weight-class order.  Rows up to 4,096 arcs are
-ordered by a wave, longer ones by a block; a workspace without room for the
-ordered rows leaves them as they are.  Whole-number outputs, so all must be
-equal."""
+"""GPU: the passes over rows.  Validation and the reverse arcs take equal ranges
+of arcs, whatever rows they cross.  MIS sweeps read rows in weight-class order:
+rows up to 4,096 arcs are ordered by a wave, longer ones by a block; a
+workspace without room for the ordered rows leaves them as they are.
+Whole-number outputs, so all must be equal."""
 import numpy as np
 import pytest
 import torch
@@ -58,3 +59,38 @@ def test_no_room_for_the_copy():
     for key in ("mis_rounds", "rungs", "gamma"):
         assert a["stats"][key] == b["stats"][key], key
     assert a["n_open"] == b["n_open"] and a["total_cost"] == b["total_cost"]
+
+
+def _spread(n, gap, extra):
+    """A star on every gap-th vertex, so that whole groups of 64 rows are empty,
+    and a path over the first `extra` vertices."""
+    at = np.arange(0, n, gap)
+    a = np.concatenate([np.zeros(len(at) - 1, np.int64), np.arange(extra - 1)])
+    b = np.concatenate([at[1:], np.arange(1, extra)])
+    return gg.from_edges(n, a, b, 7, np.random.Generator(np.random.PCG64(n)), name="spread")
+
+
+@pytest.mark.parametrize("n,gap,extra", [(9000, 63, 2), (9000, 64, 65), (9000, 65, 130), (70000, 1000, 3)])
+def test_empty_rows_between(n, gap, extra):
+    print(f"[rows] spread {n} {gap} {extra}", flush=True)
+    g = gg.with_problem(_spread(n, gap, extra), n, cost="uniform", cost_hi=30)
+    assert_solve_equal(g, 8, 3)
+
+
+@pytest.mark.parametrize("what", ["weight", "head", "loop"])
+@pytest.mark.parametrize("at", ["first", "group", "next", "last"])
+def test_one_wrong_arc_is_refused(at, what):
+    import paper_1503_03635_amd as fl
+    g = gg.with_problem(gg.er(3000, 9, 2, wmax=10), 2, cost="uniform", cost_hi=30)
+    dg = fl.to_device(g)
+    assert fl.solve(dg, 8, 1)["status"] == 0
+    m = dg.n_arcs
+    i = {"first": 0, "group": m // 128 * 64 - 1, "next": m // 128 * 64, "last": m - 1}[at]
+    if what == "weight":
+        dg.w[i] = 11
+    elif what == "head":
+        dg.col[i] = dg.n
+    else:
+        dg.col[i] = int(np.searchsorted(np.asarray(g.row_ptr, np.int64), i, side="right") - 1)
+    out = fl.solve(dg, 8, 1, check=False)
+    assert out["rc"] == fl._lib.FL_EINVAL
