@@ -42,7 +42,7 @@ HBM_PEAK_GBS = 8000.0
 # 4 cycles each, i.e. one per CU per cycle: 256 CUs x 2.4 GHz
 VALU_PEAK_INSTS = 256 * 2.4e9
 # The sketch-round kernels of one distance round: the two-task kernel (k <=
-# 32, rounds run from worklists) and the one-wave kernel that runs after it
+# 32, rounds run from marks) and the one-wave kernel that runs after it
 # on the tasks it leaves (or on every task).  A "launch" below is one round:
 # per-dispatch counters of both are summed and divided by the rounds (the
 # one-wave kernel's dispatches).
@@ -175,8 +175,8 @@ def roofline(stats, arcs, weighted, workload):
     sketch rounds: 8 B per relaxation (each final entry read once by each
     neighbour), 8 B per entry written, and one read of the arcs (4 B per arc,
     8 B with weights); per launch they are divided by the solve's launches,
-    and `achieved` is that over the average launch duration (HIP events on the
-    launch stream).  `traffic` is the measured HBM bytes per launch (committed
+    and `achieved` is that over the average launch duration (device clock read
+    by the kernels as they start).  `traffic` is the measured HBM bytes per launch (committed
     counter runs of the same kernel source, else null)."""
     launches = sum(s["ads_kernel_launches"] for s in stats)
     kern_ms = sum(s["ms_ads_kernel"] for s in stats)
@@ -300,7 +300,7 @@ def batch_leg(count, plain_count, seed):
             "plain_sample": plain_count, "speedup": round(batch_sps / plain_sps, 2),
             "batched_relax_per_s": round(relax / t_batch, 1), "batched_s": round(t_batch, 3),
             "design": "disjoint unions within a device-memory budget, up to 3 sub-unions at once on worker "
-                      "streams; the host drives rungs and MIS steps (not one persistent captured launch)"}
+                      "streams; rungs and MIS steps controlled on the device (not one persistent captured launch)"}
 
 
 def _serve_point(fl, srv, dgs, arrivals, seed):

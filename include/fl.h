@@ -88,7 +88,7 @@ typedef struct {
   uint32_t flags; /* FL_FLAG_* below */
 } fl_params;
 
-#define FL_FLAG_NO_DENSE 1u  /* always use frontier worklists in the ADS rounds */
+#define FL_FLAG_NO_DENSE 1u  /* always run the ADS rounds from marks (never over all vertices) */
 #define FL_FLAG_LUBY_MIS 2u  /* Luby's MIS variant (the baseline the paper compares
                                 against, Sec. 5.4): the same rounds as Alg. 6, but
                                 round r of a rung draws fresh priorities, a
@@ -122,7 +122,8 @@ typedef struct {
   uint64_t gamma;       /* max over served clients of min_f c(f) + d(c,f) */
   double alpha0;        /* first ladder value */
   double ms_validate, ms_ads, ms_gamma, ms_open, ms_mis, ms_assign, ms_total;
-  double ms_ads_kernel;          /* summed device time of the sketch-round kernel launches
+  double ms_ads_kernel;          /* summed device time of the sketch-round kernel launches, by
+                                    the device clock the kernels read as they start
                                     (k_ads_tasks, one per distance round; rounds launched 16
                                     at a time also count the empty rounds that end their last
                                     chunk) */
