@@ -87,7 +87,6 @@ static_assert(TASK_ARCS_FLAGGED >= TASK_ARCS, "scratch slots are sized for TASK_
 // kept.)
 constexpr uint32_t seen_keys(int KR) { return KR == 1 ? 256 : 128; }
 constexpr uint32_t level_words(int KR) { return (2 + KR) * WAVE + seen_keys(KR); }  // s_cnt of the round kernels
-constexpr uint32_t NBKT = 64;       // id buckets of the level prune (one per lane)
 constexpr uint32_t LONG_LIST = 64;  // entry lists at least this long are streamed one arc at a time
 
 // Statistics counters of the sketch rounds, cumulative over a build: one
@@ -643,7 +642,7 @@ struct Level {
   bool full0;
   uint32_t cu;           // entries of u so far
   uint32_t ns;           // buffered candidates
-  uint32_t tb;           // lane b < NBKT: rank bound for candidates of id bucket b
+  uint32_t tb;           // lane b: rank bound for candidates of id bucket b
   RankMap rm;            // ranks and id buckets of u's graph
   bool overflow;
   uint32_t nsurv, nprune;  // statistics

@@ -21,7 +21,6 @@ constexpr uint64_t INF64 = 0xFFFFFFFFFFFFFFFFull;
 constexpr uint32_t MAX_K = 128;  // the running bottom-k set: at most two registers per lane
 constexpr uint32_t MAX_W = 255;      // largest edge weight handled by the slot ring
 constexpr uint32_t MAX_CAP = 65535;  // largest per-vertex sketch capacity
-constexpr int NCTR = 1024;           // strided counters (spread atomics over addresses)
 
 // ---------------------------------------------------------------------------
 // Error plumbing
@@ -462,15 +461,6 @@ struct Graph {
 // of a weighted graph share a few lines and every append of the round queues
 // on them.
 constexpr uint32_t CNT_PAD = 32;
-// host copy of `count` padded counters (dense in `host`); waits.  The slot
-// ring has at most MAX_W + 1 counters, so the padded array is at most 32 KB.
-inline void fetch_padded(Ctx &c, uint32_t *host, const uint32_t *dev, uint32_t count) {
-  std::vector<uint32_t> tmp((size_t)count * CNT_PAD);
-  FL_HIP(hipMemcpyAsync(tmp.data(), dev, tmp.size() * 4, hipMemcpyDeviceToHost, c.s));
-  c.sync();
-  for (uint32_t i = 0; i < count; ++i) host[i] = tmp[(size_t)i * CNT_PAD];
-}
-
 // fill / utility launches (fl_graph.hip)
 void fill_u32(Ctx &c, uint32_t *p, uint64_t n, uint32_t v);
 void fill_u64(Ctx &c, uint64_t *p, uint64_t n, uint64_t v);
