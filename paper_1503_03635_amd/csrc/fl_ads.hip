@@ -2091,7 +2091,8 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
   P.thr = o.thr;
   P.thr_idx = o.thr ? cfg.thr_idx : nullptr;
   // marks by arc where arc positions fit 32 bits, by vertex otherwise
-  P.by_arc = g.m < 0xFFFFFFFFull ? 1u : 0u;
+  // (FL_TEST_MARK_VERTICES: always by vertex, so that the tests run both)
+  P.by_arc = g.m < 0xFFFFFFFFull && !std::getenv("FL_TEST_MARK_VERTICES") ? 1u : 0u;
   P.pw = (((P.by_arc ? g.m : (uint64_t)n) / 32 + 2) + 3) & ~3ull;
   P.plane = c.arena->get<uint32_t>((size_t)NS * P.pw);
   fill_u32(c, P.plane, (size_t)NS * P.pw, 0);

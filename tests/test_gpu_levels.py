@@ -43,3 +43,23 @@ def test_copies_of_every_candidate(k, dense):
         v = a + np.tile(np.arange(b), a)
         g = gg.from_edges(a + b, u, v, wmax, np.random.Generator(np.random.PCG64(a)), name="bipartite")
         assert_sketch_equal(g, k, a, flags=_flags(dense))
+
+
+@pytest.mark.parametrize("k", [16, 64, 128])
+@pytest.mark.parametrize("make", [
+    lambda: gg.er(2000, 8, 2, wmax=10), lambda: gg.rmat(11, 16 << 11, 9), lambda: gg.star(3001, 7, 1),
+    lambda: gg.grid(40, 41, wmax=4), lambda: gg.rmat(11, 16 << 11, 4, wmax=100, directed=True)],
+    ids=["er w10", "rmat unit", "star w7", "grid w4", "rmat directed w100"])
+def test_marks_by_vertex(make, k, monkeypatch):
+    """Graphs whose arc positions exceed 32 bits mark vertices; the hook takes
+    small ones there."""
+    import paper_1503_03635_amd as fl
+    g = make()
+    directed = fl.FL_FLAG_DIRECTED if getattr(g, "directed", False) else 0
+    monkeypatch.setenv("FL_TEST_MARK_VERTICES", "1")
+    print(f"[levels] marks by vertex n {g.n} k {k}", flush=True)
+    got = assert_sketch_equal(g, k, 7, flags=fl.FL_FLAG_NO_DENSE | directed)
+    monkeypatch.delenv("FL_TEST_MARK_VERTICES")
+    want = assert_sketch_equal(g, k, 7, flags=fl.FL_FLAG_NO_DENSE | directed)
+    for key in got:
+        assert np.array_equal(got[key], want[key]), key
