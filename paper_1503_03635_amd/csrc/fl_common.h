@@ -506,14 +506,21 @@ struct SsspWork {
 };
 void sssp_alloc(Ctx &c, SsspWork &wk, uint32_t n, uint64_t m);
 void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, uint32_t nseeds, SsspWork &wk);
-// Without a host check, for the opening loop (all device pointers): a search
-// from the *d_nseeds vertices of seeds, which also get their labels (their own
-// id at distance 0), as far as one block goes; nothing if *stop is set.  A
-// search that needs wide iterations is left with wk.st->nf != 0; if the seeds
-// themselves are too many, unlabelled.
+// Without a host check, for the opening loop (all device pointers).  *unseeded
+// says that the search's seeds have no labels and are in no frontier list yet;
+// whoever sets it up (k_open_ctl, one search per rung) sets the flag, and
+// whatever labels the seeds clears it, so a search under way is never seeded
+// again and one whose frontier was never written never runs.
+// A search from the *d_nseeds vertices of seeds, which also get their labels
+// (their own id at distance 0), as far as one block goes; nothing unless
+// *unseeded.  A search that needs wide iterations is left with wk.st->nf != 0.
+// If the seeds themselves are too many for one block, *unseeded stays set and
+// wk.st->nf is their number.
 void sssp_opened(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, const uint32_t *d_nseeds,
-                 const uint32_t *stop, SsspWork &wk);
-// the search that wk.st describes: narrow iterations and up to `wide` wide ones
-void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, SsspWork &wk, int wide);
+                 uint32_t *unseeded, SsspWork &wk);
+// The search that wk.st describes, labelled and listed by the launch before if
+// *unseeded was set: narrow iterations and up to `wide` wide ones.  Clears
+// *unseeded.
+void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, uint32_t *unseeded, SsspWork &wk, int wide);
 
 }  // namespace fl

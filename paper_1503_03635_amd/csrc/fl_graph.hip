@@ -576,9 +576,10 @@ __global__ __launch_bounds__(256) void k_sssp_heavy(SsspArgs S) {
 // Narrow iterations (see fl_frontier.h), by one block, until the frontier is
 // empty or too large.  SE_SEEDS: start from the nseeds <= NARROW_V vertices of
 // seeds; SE_WIDE: first close the wide iteration that ran before (its frontier
-// is the list it appended to); SE_STATE: go on from the state; SE_OPENED: start
-// from the *d_nseeds vertices of seeds and label them, unless *stop is set
-// (more than NARROW_V are left to the host).  Labels are read and lowered at the
+// is the list it appended to); SE_STATE: go on from the state (and clear
+// *unseeded); SE_OPENED: if *unseeded, start from the *d_nseeds vertices of
+// seeds, label them and clear the flag (more than NARROW_V are left as they
+// are, the flag set).  Labels are read and lowered at the
 // device's L2 (agent scope); the frontier lists are written and read by this
 // block only, a barrier apart.
 // Bound by latency: an iteration is the chain list -> row and label ->
@@ -587,13 +588,14 @@ __global__ __launch_bounds__(256) void k_sssp_heavy(SsspArgs S) {
 // graph of 50,000 vertices 20 -> 13 ms, against 8 wide iterations per check.
 enum SsspEntry : int { SE_SEEDS = 0, SE_WIDE, SE_STATE, SE_OPENED };
 __global__ __launch_bounds__(NARROW_T) void k_sssp_narrow(SsspArgs S, const uint32_t *seeds, uint32_t nseeds,
-                                                          int entry, const uint32_t *d_nseeds, const uint32_t *stop) {
+                                                          int entry, const uint32_t *d_nseeds, uint32_t *unseeded) {
   __shared__ uint64_t s_a0[NARROW_V], s_L[NARROW_V];
   __shared__ uint32_t s_excl[NARROW_V], s_tmp[NARROW_WAVES], s_nn;
   const uint32_t tid = threadIdx.x;
   uint32_t nf = nseeds, cur = S.st->cur, iter = S.st->iter, wide = S.st->wide;
   const uint32_t *list = seeds;
   if (entry == SE_WIDE || entry == SE_STATE) {
+    if (entry == SE_STATE && tid == 0) *unseeded = 0;
     nf = S.st->nf;
     if (nf == 0) return;  // the search had ended before the wide launches
     if (entry == SE_WIDE) {
@@ -604,12 +606,13 @@ __global__ __launch_bounds__(NARROW_T) void k_sssp_narrow(SsspArgs S, const uint
     }
     list = S.front[cur];
   } else if (entry == SE_OPENED) {
-    if (*stop) return;
+    if (!*unseeded) return;
     nf = *d_nseeds;
     if (nf <= NARROW_V)
       for (uint32_t p = tid; p < nf; p += NARROW_T) S.labels[seeds[p]] = (uint64_t)seeds[p];
   }
-  __syncthreads();  // every thread has read the state before it is rewritten
+  __syncthreads();  // every thread has read the state and the flag before they are rewritten
+  if (entry == SE_OPENED && nf <= NARROW_V && tid == 0) *unseeded = 0;
   while (nf && nf <= NARROW_V) {
     uint32_t v[2] = {0, 0}, deg[2] = {0, 0}, ex[2];
     uint64_t a0[2] = {0, 0}, L[2] = {0, 0};
@@ -698,8 +701,8 @@ static SsspArgs sssp_args(const Graph &g, uint64_t *labels, const SsspWork &wk) 
   return SsspArgs{g.in_ptr, g.in_col, g.in_w, labels, {wk.front[0], wk.front[1]}, wk.flag, wk.heavy, wk.st};
 }
 static void sssp_narrow(Ctx &c, const SsspArgs &S, const uint32_t *seeds, uint32_t nseeds, SsspEntry e,
-                        const uint32_t *d_nseeds = nullptr, const uint32_t *stop = nullptr) {
-  k_sssp_narrow<<<1, NARROW_T, 0, c.s>>>(S, seeds, nseeds, e, d_nseeds, stop);
+                        const uint32_t *d_nseeds = nullptr, uint32_t *unseeded = nullptr) {
+  k_sssp_narrow<<<1, NARROW_T, 0, c.s>>>(S, seeds, nseeds, e, d_nseeds, unseeded);
   FL_LAUNCH_CHECK();
 }
 // a frontier can grow by orders of magnitude within a chain: every launch gets
@@ -738,13 +741,13 @@ void sssp_run(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, u
 }
 
 void sssp_opened(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds, const uint32_t *d_nseeds,
-                 const uint32_t *stop, SsspWork &wk) {
-  sssp_narrow(c, sssp_args(g, labels, wk), seeds, 0, SE_OPENED, d_nseeds, stop);
+                 uint32_t *unseeded, SsspWork &wk) {
+  sssp_narrow(c, sssp_args(g, labels, wk), seeds, 0, SE_OPENED, d_nseeds, unseeded);
 }
 
-void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, SsspWork &wk, int wide) {
+void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, uint32_t *unseeded, SsspWork &wk, int wide) {
   const SsspArgs S = sssp_args(g, labels, wk);
-  sssp_narrow(c, S, nullptr, 0, SE_STATE);
+  sssp_narrow(c, S, nullptr, 0, SE_STATE, nullptr, unseeded);
   for (int b = 0; b < wide; ++b) sssp_wide(c, g, S, 0);
 }
 

@@ -75,6 +75,7 @@ struct OpenCtl {
   uint32_t tev;      // the rung to evaluate (the first with an event)
   uint32_t base;     // rung of the ladder window's first entry
   uint32_t heavy_cnt, opened_cnt;
+  uint32_t unseeded; // the facilities the rung opened are not labelled yet (see sssp_opened)
 };
 
 struct OpenArgs {
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(CTL_T) void k_open_ctl(OpenArgs A, int stuck_done) 
   __syncthreads();
   for (uint32_t i = tid; i < A.G * (uint32_t)OC_NFIELD * A.stripes; i += CTL_T) A.ctr[(size_t)i * A.sstride] = 0;
   if (tid == 0) {
-    s.pending = s.stop == OS_RUN;
+    s.pending = s.unseeded = s.stop == OS_RUN;
     s.heavy_cnt = s.opened_cnt = 0;
     *A.ctl = s;
   }
@@ -633,10 +634,11 @@ __global__ __launch_bounds__(256) void k_ff_scan(OpenArgs A, uint32_t fblocks, c
 }
 
 // Opened facilities become sources at distance 0 (tie = own id) and the first
-// frontier of the search; for rungs whose searches take wide iterations (the
-// one-block kernel seeds itself otherwise).
+// frontier of the search, unless they are already; for rungs whose searches
+// take wide iterations (the one-block kernel seeds itself otherwise, up to its
+// limit).  The flag is cleared by the next launch (sssp_chain).
 __global__ __launch_bounds__(256) void k_seed_opened(OpenArgs A, uint64_t *lab, SsspWork wk) {
-  if (A.ctl->stop) return;
+  if (!A.ctl->unseeded) return;
   const uint32_t cnt = A.ctl->opened_cnt;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += stride) {
@@ -821,14 +823,14 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     if (wide) {
       k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
       FL_LAUNCH_CHECK();
-      sssp_chain(c, g, dlab, wk, wide);
+      sssp_chain(c, g, dlab, &A.ctl->unseeded, wk, wide);
     } else {
-      sssp_opened(c, g, dlab, A.opened, &A.ctl->opened_cnt, &A.ctl->stop, wk);
+      sssp_opened(c, g, dlab, A.opened, &A.ctl->opened_cnt, &A.ctl->unseeded, wk);
     }
     freeze();
   };
   // Rungs are launched OPEN_CHUNK at a time, with wide iterations as long as a
-  // fair share of a chunk's rungs took some.
+  // fair share of a chunk's rungs took some, or where a search has not ended.
   constexpr uint32_t OPEN_CHUNK = 8;
   constexpr int OPEN_WIDE = 2;
   OpenCtl st{};
@@ -851,12 +853,7 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
       FL_LAUNCH_CHECK();
       ctl(1);
       rung(wide);
-    } else if (st.stop == OS_SSSP && !wide && st.opened_cnt > NARROW_V) {
-      // the one-block kernel left these seeds to the wide form
-      fill_u32(c, &A.ctl->stop, 1, OS_RUN);
-      k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
-      FL_LAUNCH_CHECK();
-      fill_u32(c, &A.ctl->stop, 1, OS_SSSP);
+      continue;  // st and sst are from before this rung
     }
     wide = st.stop == OS_SSSP || sst.wide - wide_seen >= OPEN_CHUNK / 4 ? OPEN_WIDE : 0;
     wide_seen = sst.wide;
