@@ -65,7 +65,7 @@ struct OpenG {
 enum OpenStop : uint32_t {
   OS_RUN = 0,
   OS_DONE,   // no graph is left in the loop
-  OS_STUCK,  // a stall check is due
+  OS_STUCK,  // a stall check is due: k_stuck_scan, then this kernel again
   OS_SSSP    // the search of the current rung has not ended: the next rung's launches go on with it
 };
 struct OpenCtl {
@@ -75,6 +75,7 @@ struct OpenCtl {
   uint32_t tev;      // the rung to evaluate (the first with an event)
   uint32_t base;     // rung of the ladder window's first entry
   uint32_t heavy_cnt, opened_cnt;
+  uint32_t stalls;   // stall checks asked for so far
   uint32_t unseeded; // the facilities the rung opened are not labelled yet (see sssp_opened)
 };
 
@@ -220,11 +221,10 @@ __global__ __launch_bounds__(CTL_T) void k_open_ctl(OpenArgs A, int stuck_done) 
   const uint32_t tid = threadIdx.x;
   if (tid == 0) {
     s = *A.ctl;
-    if (stuck_done) s.stop = OS_RUN;
     any_stuck = any_run = any_frz = any_inf = 0;
   }
   __syncthreads();
-  if (s.stop != OS_RUN) return;
+  if (s.stop != (stuck_done ? OS_STUCK : OS_RUN)) return;
   const uint32_t t0 = s.tev + 1;
   if (A.stripes > 1) {
     // one graph: a wave per field sums its stripes, a lane each
@@ -293,6 +293,7 @@ __global__ __launch_bounds__(CTL_T) void k_open_ctl(OpenArgs A, int stuck_done) 
     }
     __syncthreads();
     if (tid == 0) {
+      s.stop = OS_RUN;
       if (shift) s.base = t0;
       if (!any_run) {
         s.stop = OS_DONE;
@@ -306,6 +307,7 @@ __global__ __launch_bounds__(CTL_T) void k_open_ctl(OpenArgs A, int stuck_done) 
     }
   } else if (tid == 0) {
     s.stop = OS_STUCK;
+    ++s.stalls;
   }
   __syncthreads();
   for (uint32_t i = tid; i < A.G * (uint32_t)OC_NFIELD * A.stripes; i += CTL_T) A.ctr[(size_t)i * A.sstride] = 0;
@@ -691,25 +693,31 @@ __global__ __launch_bounds__(256) void k_freeze(OpenArgs A, const uint64_t *dlab
 }
 
 // Does some unopened facility still have an unfrozen served client anywhere
-// in its sketch?  (Stall check; run only when no unfrozen client can be
-// reached by an open facility and no unopened facility is itself one.)
+// in its sketch?  (Stall check; due only when no unfrozen client can be
+// reached by an open facility and no unopened facility is itself one.)  One
+// such facility answers for its graph, so a wave skips the rest.
 __global__ __launch_bounds__(256) void k_stuck_scan(OpenArgs A) {
+  if (A.ctl->stop != OS_STUCK) return;
   const int lane = lane_id();
-  const uint64_t fi = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  if (fi >= A.nF || A.state[fi]) return;
-  const uint32_t f = A.fac_list[fi];
-  const uint32_t g = seg_of(A.gid, f);
-  if (!A.og[g].stuck) return;
-  const RankMap rm = rank_map(A.seg[g]);
-  const size_t base = (size_t)f * A.cap;
-  const uint32_t nl = A.nlive[fi], cur = A.cursor[fi], c = A.cnt[f];
-  bool live = false;
-  for (uint32_t i = lane; i < nl; i += WAVE) live |= is_live(A, A.sk_rank[base + i]);
-  for (uint32_t j = cur + lane; j < c; j += WAVE) {
-    const uint32_t id = id_of(A.sk_rank[base + j], rm);
-    live |= is_live(A, id);
+  const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / WAVE);
+  for (uint64_t fi = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; fi < A.nF; fi += nw) {
+    if (A.state[fi]) continue;
+    const uint32_t f = A.fac_list[fi];
+    const uint32_t g = seg_of(A.gid, f);
+    if (!A.og[g].stuck) continue;
+    uint32_t *found = &A.ctr[((size_t)g * OC_NFIELD + OC_LIVE) * A.stripes * A.sstride];
+    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) continue;
+    const RankMap rm = rank_map(A.seg[g]);
+    const size_t base = (size_t)f * A.cap;
+    const uint32_t nl = A.nlive[fi], cur = A.cursor[fi], c = A.cnt[f];
+    bool live = false;
+    for (uint32_t i = lane; i < nl; i += WAVE) live |= is_live(A, A.sk_rank[base + i]);
+    for (uint32_t j = cur + lane; j < c; j += WAVE) {
+      const uint32_t id = id_of(A.sk_rank[base + j], rm);
+      live |= is_live(A, id);
+    }
+    if (__ballot(live) && lane == 0) atomicAdd(found, 1u);
   }
-  if (__ballot(live) && lane == 0) atomicAdd(&A.ctr[((size_t)g * OC_NFIELD + OC_LIVE) * A.stripes * A.sstride], 1u);
 }
 
 // graphs flagged in gflag[g] & 1: stall guard; & 2: end phase
@@ -802,6 +810,7 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   const uint32_t fblocks = (uint32_t)ceil_div(nF ? nF : 1, 256);
   const uint32_t hblocks = (uint32_t)std::min<uint64_t>(ceil_div((uint64_t)(nF ? nF : 1) * OPEN_G, 256), 4096);
   const uint32_t vblocks = (uint32_t)ceil_div(n, 256);
+  const uint32_t sblocks = (uint32_t)std::min<uint64_t>(ceil_div((uint64_t)(nF ? nF : 1) * WAVE, 256), 4096);
   auto ctl = [&](int stuck_done) {
     k_open_ctl<<<1, CTL_T, 0, c.s>>>(A, stuck_done);
     FL_LAUNCH_CHECK();
@@ -810,10 +819,17 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     k_freeze<<<vblocks, 256, 0, c.s>>>(A, dlab, wk.st, in.fac_idx);
     FL_LAUNCH_CHECK();
   };
-  // the rest of a rung that k_open_ctl opened; wide: iterations of the search
-  // launched for frontiers beyond one block.  A search that needs more goes on
-  // in the launches of the next rung, whose other kernels exit.
-  auto rung = [&](int wide) {
+  // One rung.  stall: with the launches of a stall check (without them a check
+  // that falls due stops the chunk).  wide: iterations of the search launched
+  // for frontiers beyond one block; a search that needs more goes on in the
+  // launches of the next rung, whose other kernels exit.
+  auto rung = [&](bool stall, int wide) {
+    ctl(0);
+    if (stall) {
+      k_stuck_scan<<<sblocks, 256, 0, c.s>>>(A);
+      FL_LAUNCH_CHECK();
+      ctl(1);
+    }
     k_ff_scan<<<fblocks + vblocks, 256, 0, c.s>>>(A, fblocks, dlab);
     FL_LAUNCH_CHECK();
     k_open_light<<<fblocks, 256, 0, c.s>>>(A);
@@ -830,31 +846,28 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     freeze();
   };
   // Rungs are launched OPEN_CHUNK at a time, with wide iterations as long as a
-  // fair share of a chunk's rungs took some, or where a search has not ended.
+  // fair share of a chunk's rungs took some, or where a search has not ended,
+  // and with stall checks where the chunk before had any due.  They are due in
+  // every rung until a client is in finite reach of an open facility where no
+  // facility is a client, and hardly ever elsewhere.
   constexpr uint32_t OPEN_CHUNK = 8;
   constexpr int OPEN_WIDE = 2;
   OpenCtl st{};
   SsspState sst{};
-  uint32_t wide_seen = 0;
+  uint32_t wide_seen = 0, stalls_seen = 0;
   int wide = nF > NARROW_V ? OPEN_WIDE : 0;
+  bool stall = false;
+  for (const OpenG &x : og) stall |= !x.done && x.nUF == 0;
   for (;;) {
-    for (uint32_t r = 0; r < OPEN_CHUNK; ++r) {
-      ctl(0);
-      rung(wide);
-    }
+    for (uint32_t r = 0; r < OPEN_CHUNK; ++r) rung(stall, wide);
     FL_HIP(hipMemcpyAsync(c.h_status, A.ctl, sizeof(OpenCtl), hipMemcpyDeviceToHost, c.s));
     FL_HIP(hipMemcpyAsync(c.h_status + 64, wk.st, sizeof(SsspState), hipMemcpyDeviceToHost, c.s));
     c.sync();
     std::memcpy(&st, c.h_status, sizeof(OpenCtl));
     std::memcpy(&sst, c.h_status + 64, sizeof(SsspState));
     if (st.stop == OS_DONE) break;
-    if (st.stop == OS_STUCK) {
-      k_stuck_scan<<<(uint32_t)ceil_div((uint64_t)(nF ? nF : 1) * WAVE, 256), 256, 0, c.s>>>(A);
-      FL_LAUNCH_CHECK();
-      ctl(1);
-      rung(wide);
-      continue;  // st and sst are from before this rung
-    }
+    stall = st.stalls != stalls_seen;
+    stalls_seen = st.stalls;
     wide = st.stop == OS_SSSP || sst.wide - wide_seen >= OPEN_CHUNK / 4 ? OPEN_WIDE : 0;
     wide_seen = sst.wide;
   }

@@ -67,6 +67,21 @@ def test_equal_sites(n, deg, wmax):
     assert t > 8 and count > BLOCK_SEEDS
 
 
+@pytest.mark.parametrize("eps", [0.1, 0.01])
+def test_checks_fall_due_late(eps):
+    """Two components: in one every vertex is a client and a cheap facility and
+    freezes early, in the other the facilities are no clients and dear, so that
+    the check first falls due many rungs into the loop."""
+    a, b = gg.er(400, 5, 1, wmax=4), gg.grid(25, 40, wmax=9, seed=2)
+    g = gg.disjoint_union(a, b)
+    at = a.n + np.arange(0, b.n, 7)
+    _sites(g, at, np.random.default_rng(3).integers(500, 4000, len(at)))
+    g.fac_cost[:a.n] = 3
+    print(f"[sites] late, eps {eps}", flush=True)
+    got, _ = assert_solve_equal(g, 8, 2, eps=eps)
+    assert got["freeze_rung"][:a.n].max() + 20 < got["open_rung"][at][got["open_rung"][at] < fl.FL_RUNG_END].min()
+
+
 def test_sites_in_a_union():
     gs = [_existing_sites(3), gg.with_problem(gg.er(300, 5, 1, wmax=10), 1, cost="uniform", cost_hi=200),
           _equal_sites(17000, 3, 4), _existing_sites(),
