@@ -397,11 +397,13 @@ static size_t estimate_bytes(uint32_t n, uint64_t m, uint64_t nF, uint32_t k, ui
   b += (size_t)64 << 20;                   // counters, scans
   return b;
 }
-// extra bytes of a union of several graphs: CSR copy, graph ids, inputs and outputs
+// extra bytes of a union of several graphs: CSR copy, graph ids, inputs and
+// outputs, the opening loop's state of each graph (16 KB, most of it the ladder
+// window: more than everything else where graphs have some tens of vertices)
 static size_t union_bytes(uint32_t G, uint64_t n, uint64_t m, bool weighted) {
   if (G <= 1) return 0;
   return (size_t)(n + 1) * 8 + (size_t)m * (weighted ? 8 : 4) + (size_t)n * (4 + 4 + 1) +
-         (size_t)n * (1 + 4 + 4 + 4 + 4 + 8) + (size_t)G * 256 + ((size_t)4 << 20);
+         (size_t)n * (1 + 4 + 4 + 4 + 4 + 8) + (size_t)G * (256 + open_graph_bytes()) + ((size_t)4 << 20);
 }
 
 static double ms_between(hipEvent_t a, hipEvent_t b) {

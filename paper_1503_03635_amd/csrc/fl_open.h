@@ -35,6 +35,8 @@ struct OpenOut {
   std::vector<int> rc;          // per graph (FL_ERANGE if the ladder overflows)
 };
 
+// workspace the loop keeps for each graph of a union, besides what it keeps per vertex
+size_t open_graph_bytes();
 int open_phase(Ctx &c, const OpenIn &in, OpenOut &out);
 
 }  // namespace fl

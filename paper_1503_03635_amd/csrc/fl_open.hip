@@ -736,6 +736,8 @@ __global__ void k_endphase(uint32_t n, const uint32_t *gid, const uint8_t *gflag
   if (c < n && (gflag[seg_of(gid, (uint32_t)c)] & 2) && ceff[c] && frz[c] == FL_RUNG_NONE) frz[c] = FL_RUNG_END;
 }
 
+size_t open_graph_bytes() { return LAD_WIN * sizeof(double) + sizeof(OpenG) + OC_NFIELD * 4 + 1; }
+
 int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   const Graph &g = *in.g;
   const uint32_t n = g.n, nF = in.nF, G = in.G;
