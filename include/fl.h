@@ -131,7 +131,7 @@ typedef struct {
                                     chunk) */
   double ms_ads_merge;           /* summed device time of the merges of split hub vertices */
   uint32_t ads_kernel_launches;  /* number of sketch-round kernel launches */
-  uint64_t workspace_bytes;
+  uint64_t workspace_bytes;      /* workspace of all phases, without the scratch of the sketch rounds */
   uint32_t n_reach_guard;  /* facilities added because a served client reached no
                               facility of S (directed graphs only: each such client
                               opens its gamma minimiser, argmin_f c(f) + d(c,f),

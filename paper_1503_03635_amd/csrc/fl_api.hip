@@ -675,6 +675,7 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
   std::vector<uint32_t> mis_rounds;
   const size_t mis_mark = c.arena->used();
   rc = mis_phase(c, mi, open_u, mis_rounds);
+  const size_t mis_bytes = c.arena->used() - mis_mark;
   c.arena->rewind(mis_mark);
   if (rc) {
     for (auto &r : rc_out) r = rc;
@@ -758,7 +759,7 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
     st.ms_mis = ms_between(ev[4], ev[5]);
     st.ms_assign = ms_between(ev[5], ev[6]);
     st.ms_total = ms_between(ev[0], ev[6]);
-    st.workspace_bytes = c.arena->used();
+    st.workspace_bytes = c.arena->used() + mis_bytes;
   }
 }
 
