@@ -510,6 +510,7 @@ static void solve_group(const fl_problem *const *ps, const fl_params *const *pr,
     dc.arena.reserve(need);
     return solve_group(ps, pr, outs, G0, s, dc, rc_out, depth + 1);  // restart with the larger arena
   }
+  c.budget = dc.arena.fixed() ? dc.arena.capacity() : need;
 
   // ---- the union (one graph: the caller's arrays as they are)
   std::vector<uint32_t> hbase(G);

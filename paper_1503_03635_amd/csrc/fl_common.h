@@ -421,6 +421,7 @@ class Arena {
 struct Ctx {
   hipStream_t s = nullptr;
   Arena *arena = nullptr;
+  size_t budget = 0;             // what this call reserved of the arena, which a call before may have made larger
   bool timing = true;            // per-phase HIP events (none when false)
   uint64_t *h_status = nullptr;  // pinned, 4096 u64
   uint64_t *d_status = nullptr;  // device, 4096 u64

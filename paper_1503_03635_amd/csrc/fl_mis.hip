@@ -1095,16 +1095,22 @@ static void by_rung(Ctx &c, uint32_t n, const uint32_t *rung, const uint32_t *gi
 constexpr uint32_t SWEEP_HEAVY_BLOCKS = 2 * HEAVY_BLOCKS;
 
 // Copies of a weighted graph's rows in class order, for both directions, if
-// the arena has room for them: a call that only just fits its workspace runs
-// the sweeps on the rows as they are.  The reservation does not count the
-// copies; the sketch rounds before need more than the sweeps do, and what they
-// leave holds them (at 32 arcs per vertex from weights of about 10 on).
+// what the call reserved has room for them: a call that only just fits its
+// workspace runs the sweeps on the rows as they are.  The reservation does not
+// count the copies; the sketch rounds before need more than the sweeps do, and
+// what they leave holds them: always on undirected graphs of 4 to 32 arcs per
+// vertex; on directed ones, whose two copies are larger, below a million
+// vertices or from weights of about 10 on (32 arcs per vertex, every vertex a
+// facility).  Room that an earlier, larger call left in the cached arena does
+// not count: the same call takes the same sweeps every time.  Small weights
+// lose nothing by it: 1..4 on a directed graph of 60,000 rows of 640 arcs, MIS
+// 2.05 ms without the copies, 2.35 with them.
 static void class_rows(Ctx &c, const Graph &g, MisArgs &A) {
   const uint32_t n = g.n, C = weight_class(g.max_w) + 1;
   const bool one = g.in_ptr == g.row_ptr && g.in_col == g.col && g.in_w == g.w;
   const uint32_t dirs = one ? 1 : 2;
   const size_t need = dirs * ((size_t)g.m * 8 + (size_t)n * C * 4) + (size_t)n * 4 + 4096;
-  if (c.arena->capacity() - c.arena->used() < need) return;
+  if (c.arena->used() + need > std::min(c.budget, c.arena->capacity())) return;
   A.S.C = C;
   uint32_t *hubs = c.arena->get<uint32_t>(n);
   uint32_t *nhubs = c.arena->get<uint32_t>(2);
