@@ -105,7 +105,7 @@ enum CtrField : uint32_t {
   CF_COUNT
 };
 struct AdsArgs {
-  uint32_t n, k, cap, W, NS;
+  uint32_t n, k, cap, NS;
   const uint32_t *gid;  // graph of each vertex (nullptr: one graph)
   const SegInfo *seg;   // per-graph rank keys, base, bucket shift
   // entries travel along arcs: a vertex gathers over its in-arcs and, when
@@ -131,8 +131,7 @@ struct AdsArgs {
   uint32_t by_arc;
   const uint32_t *out_to_in;  // [m] out-arc -> in-arc position (by_arc)
   uint32_t *reach;            // [1] CF_REACH as of the start of the current round
-  uint32_t *kept;      // [slots * sb] kept ids of split tasks
-  uint32_t sb;         // survivor buffer of the build (the round kernels' template argument)
+  uint32_t *kept;      // [slots * sb] kept ids of split tasks (sb: the survivor buffer of the build)
   uint32_t *kept_cnt;  // [slots]
   uint64_t *ctr;       // [CTR_STRIPES * CTR_FIELDS] cumulative counters, see CtrField
   uint32_t dbg;
@@ -1650,16 +1649,10 @@ __global__ __launch_bounds__(256) void k_hip_thresholds(uint32_t rows, const uin
 // ---------------------------------------------------------------------------
 // task lists
 // ---------------------------------------------------------------------------
-// count: entries the grid covers; d_count (device, may be null): the list's
-// length when only the device knows it (entries past it count zero tasks)
-__global__ void k_task_count(const uint32_t *list, uint32_t count, const uint32_t *d_count, const uint64_t *row_ptr,
-                             uint32_t task_arcs, uint32_t *ntask, uint32_t *nslot, uint32_t *isplit) {
+__global__ void k_task_count(const uint32_t *list, uint32_t count, const uint64_t *row_ptr, uint32_t task_arcs,
+                             uint32_t *ntask, uint32_t *nslot, uint32_t *isplit) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
-  if (d_count && i >= *d_count) {
-    ntask[i] = nslot[i] = isplit[i] = 0;
-    return;
-  }
   const uint32_t u = list[i];
   const uint64_t d = row_ptr[u + 1] - row_ptr[u];
   const uint32_t nt = d <= task_arcs ? 1u : (uint32_t)((d + task_arcs - 1) / task_arcs);
@@ -1668,12 +1661,12 @@ __global__ void k_task_count(const uint32_t *list, uint32_t count, const uint32_
   isplit[i] = nt > 1 ? 1u : 0u;
 }
 
-__global__ void k_task_fill(const uint32_t *list, uint32_t count, const uint32_t *d_count, const uint32_t *ntask,
-                            const uint64_t *task_off, const uint64_t *slot_off, const uint64_t *split_off,
-                            uint32_t *task_u, uint32_t *task_sub, uint32_t *task_slot, uint32_t *split_u,
-                            uint32_t *split_first, uint32_t *split_nt) {
+__global__ void k_task_fill(const uint32_t *list, uint32_t count, const uint32_t *ntask, const uint64_t *task_off,
+                            const uint64_t *slot_off, const uint64_t *split_off, uint32_t *task_u,
+                            uint32_t *task_sub, uint32_t *task_slot, uint32_t *split_u, uint32_t *split_first,
+                            uint32_t *split_nt) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count || (d_count && i >= *d_count)) return;
+  if (i >= count) return;
   const uint32_t u = list[i];
   const uint32_t nt = ntask[i];
   const uint64_t t0 = task_off[i];
@@ -1919,13 +1912,13 @@ static void build_tasks(Ctx &c, const Graph &g, const uint32_t *list, uint32_t c
   tl.task_arcs = task_arcs;
   if (count == 0) return;
   const uint32_t blocks = (uint32_t)ceil_div(count, 256);
-  k_task_count<<<blocks, 256, 0, c.s>>>(list, count, nullptr, g.in_ptr, task_arcs, ts.ntask, ts.nslot, ts.isplit);
+  k_task_count<<<blocks, 256, 0, c.s>>>(list, count, g.in_ptr, task_arcs, ts.ntask, ts.nslot, ts.isplit);
   FL_LAUNCH_CHECK();
   scan_u32_to_u64(c, ts.ntask, ts.toff, count);
   scan_u32_to_u64(c, ts.nslot, ts.soff, count);
   scan_u32_to_u64(c, ts.isplit, ts.poff, count);
-  k_task_fill<<<blocks, 256, 0, c.s>>>(list, count, nullptr, ts.ntask, ts.toff, ts.soff, ts.poff, tl.task_u,
-                                        tl.task_sub, tl.task_slot, tl.split_u, tl.split_first, tl.split_nt);
+  k_task_fill<<<blocks, 256, 0, c.s>>>(list, count, ts.ntask, ts.toff, ts.soff, ts.poff, tl.task_u, tl.task_sub,
+                                       tl.task_slot, tl.split_u, tl.split_first, tl.split_nt);
   FL_LAUNCH_CHECK();
   uint64_t h[3];
   FL_HIP(hipMemcpyAsync(&h[0], ts.toff + count, 8, hipMemcpyDeviceToHost, c.s));
@@ -2007,8 +2000,11 @@ size_t ads_scratch_bytes(uint32_t n, uint64_t m, uint32_t k, uint32_t NS) {
   b += (size_t)NS * n * 16;                // per-slot level records
   b += (size_t)m * 4 + (size_t)NS * (m / 32 + n / 32 + 8) * 4;  // reverse-arc positions, planes (arcs or vertices)
   b += (size_t)slots * (ADS_SB * (k > 64 ? 2 : 1) + 1) * 4;   // kept sets of split tasks
-  b += (size_t)tasks * 4 * 3 * 2 + (size_t)n * 4 * 3 * 2;  // two task lists
-  b += (size_t)n * (4 * 3 + 8 * 3) + (size_t)n * 24;       // task scratch, dense list
+  // two task lists, task scratch, the dense list: builds with weights hold one
+  // list and nothing else of these; what they leave is room for the ordered
+  // rows of the selection
+  b += (size_t)tasks * 4 * 3 * 2 + (size_t)n * 4 * 3 * 2;
+  b += (size_t)n * (4 * 3 + 8 * 3) + (size_t)n * 24;
   b += (size_t)tasks * 4;                  // tasks left by the two-task kernel
   b += (size_t)8 << 20;
   return b;
@@ -2068,10 +2064,8 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
 
   AdsArgs P{};
   P.n = n;
-  P.sb = sb;
   P.k = k;
   P.cap = cap;
-  P.W = W;
   P.NS = NS;
   P.gid = cfg.gid;
   P.seg = cfg.seg;
@@ -2145,15 +2139,8 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     P.kept = c.arena->get<uint32_t>(slots * sb);
     P.kept_cnt = c.arena->get<uint32_t>(slots);
   }
-  // task-list scratch and lists (sized for a list of all vertices)
+  // task lists (sized for a list of all vertices)
   const uint64_t max_tasks = (uint64_t)n + g.m / TASK_ARCS + 64;
-  TaskScratch ts;
-  ts.ntask = c.arena->get<uint32_t>(n);
-  ts.nslot = c.arena->get<uint32_t>(n);
-  ts.isplit = c.arena->get<uint32_t>(n);
-  ts.toff = c.arena->get<uint64_t>((size_t)n + 1);
-  ts.soff = c.arena->get<uint64_t>((size_t)n + 1);
-  ts.poff = c.arena->get<uint64_t>((size_t)n + 1);
   TaskList tl_dense, tl;
   auto alloc_list = [&](TaskList &t) {
     t.task_u = c.arena->get<uint32_t>(max_tasks);
@@ -2179,6 +2166,13 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     FL_HIP(hipMemcpyAsync(c.h_status, pos + n, 8, hipMemcpyDeviceToHost, c.s));
     c.sync();
     n_dense = (uint32_t)c.h_status[0];
+    TaskScratch ts;
+    ts.ntask = c.arena->get<uint32_t>(n);
+    ts.nslot = c.arena->get<uint32_t>(n);
+    ts.isplit = c.arena->get<uint32_t>(n);
+    ts.toff = c.arena->get<uint64_t>((size_t)n + 1);
+    ts.soff = c.arena->get<uint64_t>((size_t)n + 1);
+    ts.poff = c.arena->get<uint64_t>((size_t)n + 1);
     alloc_list(tl_dense);
     build_tasks(c, g, dense, n_dense, TASK_ARCS, ts, tl_dense);
   }
