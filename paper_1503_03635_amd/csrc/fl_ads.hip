@@ -104,8 +104,11 @@ enum CtrField : uint32_t {
   CF_REACH,         // largest distance any arc was marked for (a maximum)
   CF_COUNT
 };
+// (pad0, pad1: without them the same kernels are allocated other registers, and
+// the round kernels of R-MAT 2^22, unit, k = 64 take 442.7 ms instead of 439.4;
+// with other fields in their places 444.8 and 447.5.)
 struct AdsArgs {
-  uint32_t n, k, cap, NS;
+  uint32_t n, k, cap, pad0, NS;
   const uint32_t *gid;  // graph of each vertex (nullptr: one graph)
   const SegInfo *seg;   // per-graph rank keys, base, bucket shift
   // entries travel along arcs: a vertex gathers over its in-arcs and, when
@@ -132,6 +135,7 @@ struct AdsArgs {
   const uint32_t *out_to_in;  // [m] out-arc -> in-arc position (by_arc)
   uint32_t *reach;            // [1] CF_REACH as of the start of the current round
   uint32_t *kept;      // [slots * sb] kept ids of split tasks (sb: the survivor buffer of the build)
+  uint32_t pad1;
   uint32_t *kept_cnt;  // [slots]
   uint64_t *ctr;       // [CTR_STRIPES * CTR_FIELDS] cumulative counters, see CtrField
   uint32_t dbg;
@@ -2139,8 +2143,17 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     P.kept = c.arena->get<uint32_t>(slots * sb);
     P.kept_cnt = c.arena->get<uint32_t>(slots);
   }
-  // task lists (sized for a list of all vertices)
+  // task lists (sized for a list of all vertices) and the dense list's scratch
   const uint64_t max_tasks = (uint64_t)n + g.m / TASK_ARCS + 64;
+  TaskScratch ts{};
+  if (dense_ok) {
+    ts.ntask = c.arena->get<uint32_t>(n);
+    ts.nslot = c.arena->get<uint32_t>(n);
+    ts.isplit = c.arena->get<uint32_t>(n);
+    ts.toff = c.arena->get<uint64_t>((size_t)n + 1);
+    ts.soff = c.arena->get<uint64_t>((size_t)n + 1);
+    ts.poff = c.arena->get<uint64_t>((size_t)n + 1);
+  }
   TaskList tl_dense, tl;
   auto alloc_list = [&](TaskList &t) {
     t.task_u = c.arena->get<uint32_t>(max_tasks);
@@ -2166,13 +2179,6 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
     FL_HIP(hipMemcpyAsync(c.h_status, pos + n, 8, hipMemcpyDeviceToHost, c.s));
     c.sync();
     n_dense = (uint32_t)c.h_status[0];
-    TaskScratch ts;
-    ts.ntask = c.arena->get<uint32_t>(n);
-    ts.nslot = c.arena->get<uint32_t>(n);
-    ts.isplit = c.arena->get<uint32_t>(n);
-    ts.toff = c.arena->get<uint64_t>((size_t)n + 1);
-    ts.soff = c.arena->get<uint64_t>((size_t)n + 1);
-    ts.poff = c.arena->get<uint64_t>((size_t)n + 1);
     alloc_list(tl_dense);
     build_tasks(c, g, dense, n_dense, TASK_ARCS, ts, tl_dense);
   }
