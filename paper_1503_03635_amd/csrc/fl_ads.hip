@@ -104,11 +104,8 @@ enum CtrField : uint32_t {
   CF_REACH,         // largest distance any arc was marked for (a maximum)
   CF_COUNT
 };
-// (pad0, pad1: without them the same kernels are allocated other registers, and
-// the round kernels of R-MAT 2^22, unit, k = 64 take 442.7 ms instead of 439.4;
-// with other fields in their places 444.8 and 447.5.)
 struct AdsArgs {
-  uint32_t n, k, cap, pad0, NS;
+  uint32_t n, k, cap, NS;
   const uint32_t *gid;  // graph of each vertex (nullptr: one graph)
   const SegInfo *seg;   // per-graph rank keys, base, bucket shift
   // entries travel along arcs: a vertex gathers over its in-arcs and, when
@@ -135,7 +132,6 @@ struct AdsArgs {
   const uint32_t *out_to_in;  // [m] out-arc -> in-arc position (by_arc)
   uint32_t *reach;            // [1] CF_REACH as of the start of the current round
   uint32_t *kept;      // [slots * sb] kept ids of split tasks (sb: the survivor buffer of the build)
-  uint32_t pad1;
   uint32_t *kept_cnt;  // [slots]
   uint64_t *ctr;       // [CTR_STRIPES * CTR_FIELDS] cumulative counters, see CtrField
   uint32_t dbg;
@@ -657,7 +653,7 @@ __device__ inline void level_init(const AdsArgs &P, uint32_t u, Level<KR> &L, ui
   const int lane = lane_id();
   const uint32_t k = P.k;
   L.rm = rank_map(P.seg[seg_of(P.gid, u)]);
-  L.cu = P.cnt[u];
+  L.cu = __builtin_amdgcn_readfirstlane(P.cnt[u]);
   L.nset0 = L.cu < k ? L.cu : k;
 #pragma unroll
   for (int g = 0; g < KR; ++g) {
@@ -668,7 +664,7 @@ __device__ inline void level_init(const AdsArgs &P, uint32_t u, Level<KR> &L, ui
   for (uint32_t i = lane; i < seen_keys(KR); i += WAVE) s_cnt[(2 + KR) * WAVE + i] = INF32;
   wave_lds_sync();
   L.full0 = L.nset0 == k;
-  L.T0 = L.full0 ? kset_at(L.set0, k - 1) : INF32;
+  L.T0 = L.full0 ? __builtin_amdgcn_readfirstlane(kset_at(L.set0, k - 1)) : INF32;
   L.ns = 0;
   L.tb = L.T0;
   L.overflow = false;
@@ -783,9 +779,9 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
     while (lm && !L.overflow) {
       const int j = __ffsll((long long)lm) - 1;
       lm &= lm - 1;
-      const uint32_t vj = __shfl(v, j, WAVE);
-      const uint32_t stj = __shfl(st, j, WAVE);
-      const uint32_t cnj = __shfl(cn, j, WAVE);
+      const uint32_t vj = __builtin_amdgcn_readlane(v, j);
+      const uint32_t stj = __builtin_amdgcn_readlane(st, j);
+      const uint32_t cnj = __builtin_amdgcn_readlane(cn, j);
       const uint32_t *src = P.sk_rank + (size_t)vj * P.cap + stj;
       auto load = [&](uint32_t i) -> uint32_t { return i < cnj ? src[i] : INF32; };
       uint32_t q0 = load(lane), q1 = load(lane + WAVE), q2 = load(lane + 2 * WAVE), q3 = load(lane + 3 * WAVE);
@@ -806,7 +802,7 @@ __device__ inline uint64_t gather_batch(const AdsArgs &P, uint32_t D, uint64_t a
     // record.
     const uint32_t cs = cn < LONG_LIST ? cn : 0u;
     const uint32_t incl = wave_scan_incl(cs);
-    const uint32_t total = __shfl(incl, WAVE - 1, WAVE);
+    const uint32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
     const uint32_t excl = incl - cs;
     examined += total;
     for (uint32_t c0 = 0; c0 < total && !L.overflow; c0 += WAVE) {
@@ -960,11 +956,21 @@ __device__ inline bool level_commit(const AdsArgs &P, uint32_t u, uint32_t D, Le
 
 // One task, by one wave.  slot == INF32: the task is the whole vertex and
 // commits; otherwise it leaves its kept set in scratch slot `slot`.
+// What is the same in every lane (the task, its count and threshold, the list a
+// wave walks) is read into scalar registers.  As vector registers it made the
+// five-wave instance (k <= 32) spill 29 registers, 5.6 KB of scratch traffic a
+// task; 3 now: sketches of ER 1,000,000 (unit, average degree 4, k = 8) 44.4 ->
+// 28.5 ms, ER 300,000 11.6 -> 8.5, R-MAT 2^18 (unit, k = 32) 15.5 -> 13.5.  The
+// four-wave and three-wave instances did not spill but do less work per lane:
+// R-MAT 2^22 (unit, k = 64) 469 -> 447, 2^18 at k = 128 77.1 -> 72.5.
 template <bool UNITW, int KR, uint32_t SB>
 __device__ inline void ads_task(const AdsArgs &P, uint32_t D, uint32_t u, uint32_t sub, uint32_t slot,
                                 uint32_t task_arcs, int sparse, int mark, uint32_t *s_id, uint32_t *s_tmp,
                                 uint32_t *s_cnt) {
   const int lane = lane_id();
+  u = __builtin_amdgcn_readfirstlane(u);
+  sub = __builtin_amdgcn_readfirstlane(sub);
+  slot = __builtin_amdgcn_readfirstlane(slot);
   Level<KR> L;
   level_init(P, u, L, s_cnt);
   const uint64_t r0 = P.row_ptr[u], r1 = P.row_ptr[u + 1];
