@@ -487,16 +487,27 @@ __device__ inline void wq_push(WaveQ &q, bool add, uint32_t y) {
   wave_lds_sync();
 }
 
-// the staged remainder (every lane calls, converged, before the wave exits)
+// The staged remainders of a block's 4 waves (every thread of the block calls,
+// once, before it exits): one atomic on the count for all of them.  A frontier
+// of some thousand vertices of low degree is spread over 2,048 waves of 4
+// vertices, each with a handful of appends; with an atomic per wave they queued
+// on the one count (opening loop of a grid of 1,200 x 1,200, weights 1..9, 320 ->
+// 226 to 255 ms; assignment on 600 x 600 2.8 -> 2.0; R-MAT 2^20 directed, weights
+// 1..100, gamma 1.5 -> 1.2, opening loop 28.7 -> 27.5).
 __device__ inline void wq_flush(WaveQ &q) {
-  if (!q.cnt) return;
-  const int lane = lane_id();
-  wave_lds_sync();
-  uint32_t base = 0;
-  if (lane == 0) base = atomicAdd(q.nnext, q.cnt);
-  base = __shfl(base, 0, WAVE);
-  if ((uint32_t)lane < q.cnt) q.next[base + lane] = q.buf[lane];
-  q.cnt = 0;
+  __shared__ uint32_t s_n[256 / WAVE], s_base;
+  const uint32_t lane = (uint32_t)lane_id(), wv = threadIdx.x / WAVE;
+  if (lane == 0) s_n[wv] = q.cnt;
+  __syncthreads();
+  uint32_t at = 0, tot = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 256 / WAVE; ++i) {
+    at += i < wv ? s_n[i] : 0u;
+    tot += s_n[i];
+  }
+  if (threadIdx.x == 0 && tot) s_base = atomicAdd(q.nnext, tot);
+  __syncthreads();
+  if (lane < q.cnt) q.next[s_base + at + lane] = q.buf[lane];
 }
 
 // one arc step (every lane calls, converged): relax arc a with label L
