@@ -523,5 +523,7 @@ void sssp_opened(Ctx &c, const Graph &g, uint64_t *labels, const uint32_t *seeds
 // *unseeded was set: narrow iterations and up to `wide` wide ones.  Clears
 // *unseeded.
 void sssp_chain(Ctx &c, const Graph &g, uint64_t *labels, uint32_t *unseeded, SsspWork &wk, int wide);
+// The same search to its end, with host checks.
+void sssp_finish(Ctx &c, const Graph &g, uint64_t *labels, uint32_t *unseeded, SsspWork &wk);
 
 }  // namespace fl

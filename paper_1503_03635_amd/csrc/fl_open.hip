@@ -821,6 +821,10 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     k_freeze<<<vblocks, 256, 0, c.s>>>(A, dlab, wk.st, in.fac_idx);
     FL_LAUNCH_CHECK();
   };
+  auto seed = [&]() {
+    k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
+    FL_LAUNCH_CHECK();
+  };
   // One rung.  stall: with the launches of a stall check (without them a check
   // that falls due stops the chunk).  wide: iterations of the search launched
   // for frontiers beyond one block; a search that needs more goes on in the
@@ -839,29 +843,33 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     k_open_heavy<<<hblocks, 256, 0, c.s>>>(A);
     FL_LAUNCH_CHECK();
     if (wide) {
-      k_seed_opened<<<std::min<uint32_t>(fblocks, 256), 256, 0, c.s>>>(A, dlab, wk);
-      FL_LAUNCH_CHECK();
+      seed();
       sssp_chain(c, g, dlab, &A.ctl->unseeded, wk, wide);
     } else {
       sssp_opened(c, g, dlab, A.opened, &A.ctl->opened_cnt, &A.ctl->unseeded, wk);
     }
     freeze();
   };
-  // Rungs are launched OPEN_CHUNK at a time, with wide iterations as long as a
-  // fair share of a chunk's rungs took some, or where a search has not ended,
-  // and with stall checks where the chunk before had any due.  They are due in
-  // every rung until a client is in finite reach of an open facility where no
-  // facility is a client, and hardly ever elsewhere.
+  // Rungs are launched up to OPEN_CHUNK at a time, with wide iterations as long
+  // as a fair share of a chunk's rungs took some, or where a search has not
+  // ended, and with stall checks where the chunk before had any due.  They are
+  // due in every rung until a client is in finite reach of an open facility
+  // where no facility is a client, and hardly ever elsewhere.
+  // A search that has not ended by the end of a chunk runs on its own, and the
+  // next chunk is half as long: the launches of a chunk's other rungs advance it
+  // by OPEN_WIDE iterations in fourteen launches (a grid of 1,200 x 1,200, weights
+  // 1..9, 1% facilities, 7,700 wide iterations: opening loop 226 to 260 ms with
+  // them, 172 to 182 without).
   constexpr uint32_t OPEN_CHUNK = 8;
   constexpr int OPEN_WIDE = 2;
   OpenCtl st{};
   SsspState sst{};
-  uint32_t wide_seen = 0, stalls_seen = 0;
+  uint32_t wide_seen = 0, stalls_seen = 0, chunk = OPEN_CHUNK;
   int wide = nF > NARROW_V ? OPEN_WIDE : 0;
   bool stall = false;
   for (const OpenG &x : og) stall |= !x.done && x.nUF == 0;
   for (;;) {
-    for (uint32_t r = 0; r < OPEN_CHUNK; ++r) rung(stall, wide);
+    for (uint32_t r = 0; r < chunk; ++r) rung(stall, wide);
     FL_HIP(hipMemcpyAsync(c.h_status, A.ctl, sizeof(OpenCtl), hipMemcpyDeviceToHost, c.s));
     FL_HIP(hipMemcpyAsync(c.h_status + 64, wk.st, sizeof(SsspState), hipMemcpyDeviceToHost, c.s));
     c.sync();
@@ -872,6 +880,14 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
     stalls_seen = st.stalls;
     wide = st.stop == OS_SSSP || sst.wide - wide_seen >= OPEN_CHUNK / 4 ? OPEN_WIDE : 0;
     wide_seen = sst.wide;
+    if (st.stop == OS_SSSP) {
+      seed();
+      sssp_finish(c, g, dlab, &A.ctl->unseeded, wk);
+      freeze();
+      chunk = std::max(chunk / 2, 1u);
+    } else {
+      chunk = std::min(2 * chunk, OPEN_CHUNK);
+    }
   }
   FL_HIP(hipMemcpyAsync(og.data(), A.og, G * sizeof(OpenG), hipMemcpyDeviceToHost, c.s));
   c.sync();
