@@ -415,7 +415,7 @@ __device__ inline uint32_t kset_below(const KSet<KR> &s, uint32_t r) {
 // lane (after some 13 bits for 64 random ranks, 10 instructions each).
 // Comparing all pairs out of LDS took 13 instructions per 4 candidates and
 // then a sort of the accepted ranks, which here have their places: round
-// kernels of R-MAT 2^22 (unit, k = 64) 576 -> 544 ms with it for every chunk,
+// kernels of R-MAT 2^22 (unit, k = 64) 576 -> 547 ms with it for every chunk,
 // also small ones (700 -> 668 ms when first used, for more than 24).
 __device__ inline uint64_t wave_smaller(uint32_t r, bool valid, uint64_t vm, uint32_t most) {
   uint32_t el = valid ? (uint32_t)vm : 0u, eh = valid ? (uint32_t)(vm >> 32) : 0u, ll = 0, lh = 0;

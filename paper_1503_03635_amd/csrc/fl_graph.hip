@@ -41,7 +41,7 @@ void fill_f64(Ctx &c, double *p, uint64_t n, double v) { fill_t(c, p, n, v); }
 // vertex.  Bound by the reads of the searches (row bounds and columns of the
 // other end): R-MAT 2^22, 127 million arcs, 8.0 ms; a wave per vertex, which
 // ends with one wave in the longest row, 19.4 (R-MAT 2^21 11.2 -> 4.4, 2^18 1.6 ->
-// 0.37, 64 graphs of a few thousand vertices 3.5 -> 1.3).  err bits: 1 =
+// 0.37, 64 graphs of 500 to 200,000 vertices 3.5 -> 1.3).  err bits: 1 =
 // structural error.  Also reduces max weight and max facility
 // cost.  Each block reduces its waves' results in LDS and adds them to
 // stripe blockIdx.x % stripes, one 128-byte line per stripe: v32[32 s + 0]
