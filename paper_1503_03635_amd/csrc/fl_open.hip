@@ -857,7 +857,7 @@ int open_phase(Ctx &c, const OpenIn &in, OpenOut &out) {
   // where no facility is a client, and hardly ever elsewhere.
   // A search that has not ended by the end of a chunk runs on its own, and the
   // next chunk is half as long: the launches of a chunk's other rungs advance it
-  // by OPEN_WIDE iterations in fourteen launches (a grid of 1,200 x 1,200, weights
+  // by OPEN_WIDE iterations in thirteen launches (a grid of 1,200 x 1,200, weights
   // 1..9, 1% facilities, 7,700 wide iterations: opening loop 226 to 260 ms with
   // them, 172 to 182 without).
   constexpr uint32_t OPEN_CHUNK = 8;
