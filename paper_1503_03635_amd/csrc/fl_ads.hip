@@ -956,21 +956,26 @@ __device__ inline bool level_commit(const AdsArgs &P, uint32_t u, uint32_t D, Le
 
 // One task, by one wave.  slot == INF32: the task is the whole vertex and
 // commits; otherwise it leaves its kept set in scratch slot `slot`.
-// What is the same in every lane (the task, its count and threshold, the list a
-// wave walks) is read into scalar registers.  As vector registers it made the
-// five-wave instance (k <= 32) spill 29 registers, 5.6 KB of scratch traffic a
-// task; 3 now: sketches of ER 1,000,000 (unit, average degree 4, k = 8) 44.4 ->
-// 28.5 ms, ER 300,000 11.6 -> 8.5, R-MAT 2^18 (unit, k = 32) 15.5 -> 13.5.  The
-// four-wave and three-wave instances did not spill but do less work per lane:
-// R-MAT 2^22 (unit, k = 64) 469 -> 447, 2^18 at k = 128 77.1 -> 72.5.
+// What is the same in every lane (its count and threshold, the list a wave
+// walks, in the five-wave instance for unit weights the task itself) is read
+// into scalar registers.  As vector registers it made the five-wave instances
+// (k <= 32) spill 29 of them, 5.6 KB of scratch traffic a task; 3 now (7 with
+// weights): sketches of ER 1,000,000 (unit, average degree 4, k = 8) 44.4 -> 28.4
+// ms, ER 300,000 11.6 -> 8.5, R-MAT 2^18 (unit, k = 32) 15.5 -> 13.5.  The others did
+// not spill but do less work per lane: R-MAT 2^22 (unit, k = 64) 489 -> 465, 2^18 at
+// k = 128 75 -> 70.  A scalar task costs them 2% in rounds run from marks (k = 64:
+// R-MAT 2^20, weights 1..100, 255 -> 262 ms; a grid of 150 x 220, unit, 21.8 -> 22.2)
+// and gives nothing in dense ones; without it ER 1,000,000 above takes 31.6.
 template <bool UNITW, int KR, uint32_t SB>
 __device__ inline void ads_task(const AdsArgs &P, uint32_t D, uint32_t u, uint32_t sub, uint32_t slot,
                                 uint32_t task_arcs, int sparse, int mark, uint32_t *s_id, uint32_t *s_tmp,
                                 uint32_t *s_cnt) {
   const int lane = lane_id();
-  u = __builtin_amdgcn_readfirstlane(u);
-  sub = __builtin_amdgcn_readfirstlane(sub);
-  slot = __builtin_amdgcn_readfirstlane(slot);
+  if (UNITW && SB <= ADS_SB / 2) {
+    u = __builtin_amdgcn_readfirstlane(u);
+    sub = __builtin_amdgcn_readfirstlane(sub);
+    slot = __builtin_amdgcn_readfirstlane(slot);
+  }
   Level<KR> L;
   level_init(P, u, L, s_cnt);
   const uint64_t r0 = P.row_ptr[u], r1 = P.row_ptr[u + 1];
