@@ -2301,8 +2301,9 @@ static int ads_run(Ctx &c, const Graph &g, const AdsConfig &cfg, AdsOut &o, bool
         std::fprintf(stderr, "[fl] rounds %u-%u: tasks of the first %llu, left to the one-wave kernel %llu, reach %llu\n",
                      D0, D0 + RCHUNK - 1, h.tot[0].tasks, h.tot[0].left, (unsigned long long)h.info.reach);
       if (h.info.reach < (uint64_t)D0 + RCHUNK) break;  // no mark beyond this chunk
-      // a settled entry is at most (n-1) max_w away: more rounds mean a bug
-      if ((uint64_t)D0 + RCHUNK > (uint64_t)(n - 1) * W + 2 + RCHUNK) return FL_EHIP;
+      // a settled entry is at most (n-1) max_w away, and its vertex marks its
+      // neighbours once more: marks beyond n max_w mean a bug
+      if ((uint64_t)D0 > (uint64_t)n * W) return FL_EHIP;
     }
   }
   uint64_t active_prev = n;
